@@ -2,7 +2,7 @@
 // unquantized mixer over the calibration batch with absmax observers, the percentile maximum
 // for the scan input x, the Hadamard-space scale of the scan output and the folding of H_n
 // into W_out, followed by the per-tensor symmetric quantization of every weight (Eq. 2).
-// This runs once per layer, so the kernels here are plain tiled fp32 code, not tuned.
+// This runs once per layer.  4 x 256 tokens of the 2.8B layer: 54 GFLOP of fp32 input projection are the floor.
 #include <cmath>
 #include <cstring>
 #include <vector>
@@ -18,51 +18,122 @@ namespace {
 
 constexpr float LOG2E = 1.44269504088896340736f;
 
+// Pieces of four values of master weights and outputs, which promise no more than their own alignment.
+typedef float f4 __attribute__((ext_vector_type(4)));
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
 // ---------------------------------------------------------------- fp32 GEMM, C = A W^T
-constexpr int GT = 64, GK = 16;
-__global__ __launch_bounds__(256) void sgemm_tn_kernel(const float *__restrict__ A, int lda,
-                                                       const float *__restrict__ W, int ldw,
-                                                       float *__restrict__ C, int ldc, int M, int N, int K) {
-  __shared__ float sa[GK][GT + 4], sw[GK][GT + 4];
-  const int m0 = blockIdx.y * GT, n0 = blockIdx.x * GT;
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += GK) {
-    for (int i = threadIdx.x; i < GT * GK; i += 256) {
-      const int r = i / GK, k = i % GK;
-      sa[k][r] = (m0 + r < M && k0 + k < K) ? A[(size_t)(m0 + r) * lda + k0 + k] : 0.f;
-      sw[k][r] = (n0 + r < N && k0 + k < K) ? W[(size_t)(n0 + r) * ldw + k0 + k] : 0.f;
+// fp32 matrix units (v_mfma_f32_32x32x2_f32: fp32 operands, fp32 sums, 256 flop per clock and CU).  A wave owns 32 rows
+// x 64 columns of the output: the weight rows are the MFMA A operand, so a lane ends with four consecutive columns
+// of one row.  A slice is 32 of K, register-prefetched into one padded LDS buffer; a lane reads four consecutive k as
+// 16 bytes and spends them in four products (the half-wave h takes k = 4h .. 4h + 3 of every eight: both operands
+// agree, so the order of the sum over k is all that changes), so LDS gives 0.75 reads per four products and the
+// matrix pipe is what bounds it.  Small tiles on purpose: 1024 x 10240 is 1280 workgroups of 128 x 64, five on every
+// CU, whose waves cover each other's barriers.  WM x WN waves: 128 x 64, 64 x 128, 32 x 256 outputs per workgroup.
+// 1024 x 10240 x 2560: 511 us = 105 TFLOP/s of the 157 that fp32 matrix products reach at most (a 64 x 64 tile on the
+// vector units: 935 us); 1024 x 192 x 5120 with K in 20 ranges 26 + 6 us (one range of 48 tiles on the vector units: 728).
+constexpr int GK = 32, GLD = GK + 4;
+
+template <int WM, int WN>
+__global__ __launch_bounds__(256) void sgemm_tn_kernel(const float *__restrict__ A, int lda, const float *__restrict__ W,
+                                                       int ldw, float *__restrict__ C, int ldc, int M, int N, int K,
+                                                       int kper, size_t cstride) {
+  constexpr int BM = 32 * WM, BN = 64 * WN;
+  __shared__ __attribute__((aligned(16))) float sa[BM * GLD], sw[BN * GLD];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave % WM, wn = wave / WM, l31 = lane & 31, h = lane >> 5;
+  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
+  const int k0 = blockIdx.z * kper, k1 = min(K, k0 + kper);
+
+  f4 ra[WM], rw[2 * WN];
+  const int prow = tid >> 3, pk = (tid & 7) * 4;  // eight 16-byte pieces per row and slice
+  auto fetch = [&](int k) {                        // K and kper are multiples of 16: a piece is in range or out of it
+#pragma unroll
+    for (int i = 0; i < WM; ++i) {
+      const int r = m0 + prow + 32 * i;
+      ra[i] = f4{0.f, 0.f, 0.f, 0.f};
+      if (r < M && k + pk < k1) ra[i] = *reinterpret_cast<const f4u *>(A + (size_t)r * lda + k + pk);
     }
+#pragma unroll
+    for (int i = 0; i < 2 * WN; ++i) {
+      const int r = n0 + prow + 32 * i;
+      rw[i] = f4{0.f, 0.f, 0.f, 0.f};
+      if (r < N && k + pk < k1) rw[i] = *reinterpret_cast<const f4u *>(W + (size_t)r * ldw + k + pk);
+    }
+  };
+
+  f32x16 acc[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
+  fetch(k0);
+  for (int k = k0; k < k1; k += GK) {
+    __syncthreads();  // the previous slice has been read
+#pragma unroll
+    for (int i = 0; i < WM; ++i) *reinterpret_cast<f4 *>(&sa[(prow + 32 * i) * GLD + pk]) = ra[i];
+#pragma unroll
+    for (int i = 0; i < 2 * WN; ++i) *reinterpret_cast<f4 *>(&sw[(prow + 32 * i) * GLD + pk]) = rw[i];
     __syncthreads();
+    if (k + GK < k1) fetch(k + GK);
 #pragma unroll
-    for (int k = 0; k < GK; ++k) {
-      float a[4], w[4];
+    for (int kk = 0; kk < GK / 8; ++kk) {
+      const f4 fa = *reinterpret_cast<const f4 *>(&sa[(wm * 32 + l31) * GLD + kk * 8 + 4 * h]);
+      const f4 f0 = *reinterpret_cast<const f4 *>(&sw[(wn * 64 + l31) * GLD + kk * 8 + 4 * h]);
+      const f4 f1 = *reinterpret_cast<const f4 *>(&sw[(wn * 64 + 32 + l31) * GLD + kk * 8 + 4 * h]);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        a[i] = sa[k][ty * 4 + i];
-        w[i] = sw[k][tx * 4 + i];
+      for (int e = 0; e < 4; ++e) {
+        acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(f0[e], fa[e], acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(f1[e], fa[e], acc[1], 0, 0, 0);
       }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] += a[i] * w[j];
     }
-    __syncthreads();
   }
+  const int m = m0 + wm * 32 + l31;
+  if (m >= M) return;
+  float *row = C + blockIdx.z * cstride + (size_t)m * ldc;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int j = 0; j < 2; ++j)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int m = m0 + ty * 4 + i, n = n0 + tx * 4 + j;
-      if (m < M && n < N) C[(size_t)m * ldc + n] = acc[i][j];
+    for (int q = 0; q < 4; ++q) {
+      const int n = n0 + wn * 64 + j * 32 + 8 * q + 4 * h;  // N is a multiple of 16
+      if (n < N) *reinterpret_cast<f4u *>(row + n) = f4u{acc[j][4 * q], acc[j][4 * q + 1], acc[j][4 * q + 2], acc[j][4 * q + 3]};
     }
 }
 
-int sgemm(const float *A, int lda, const float *W, int ldw, float *C, int ldc, int M, int N, int K,
-          hipStream_t st) {
-  dim3 grid((N + GT - 1) / GT, (M + GT - 1) / GT);
-  hipLaunchKernelGGL(sgemm_tn_kernel, grid, dim3(256), 0, st, A, lda, W, ldw, C, ldc, M, N, K);
+// C[i] = sum over the K ranges of part[s * n + i], in order of s; n is a multiple of 16
+__global__ __launch_bounds__(256) void sgemm_sum_kernel(const float *__restrict__ part, int splits, size_t n,
+                                                        float *__restrict__ C) {
+  const size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;
+  if (i >= n) return;
+  f4 v = *reinterpret_cast<const f4 *>(part + i);
+  for (int s = 1; s < splits; ++s) v += *reinterpret_cast<const f4 *>(part + s * n + i);
+  *reinterpret_cast<f4u *>(C + i) = v;
+}
+
+// K and N multiples of 16, ldc == N.  `scratch` (16-byte aligned, scratch_floats long) takes the partial sums where K is split:
+// a skinny output (x_proj, 1024 x 192 x 5120: 24 tiles) would leave nine CUs of ten idle.
+int sgemm(const float *A, int lda, const float *W, int ldw, float *C, int M, int N, int K, float *scratch,
+          size_t scratch_floats, hipStream_t st) {
+  const int wm = M > 64 ? 4 : (M > 32 ? 2 : 1), wn = 4 / wm;
+  const int tm = (M + 32 * wm - 1) / (32 * wm), tn = (N + 64 * wn - 1) / (64 * wn);
+  // as many K ranges as bring three workgroups to every CU, none shorter than eight slices
+  const size_t mn = (size_t)M * N;
+  int splits = (int)std::min<size_t>(768 / ((size_t)tm * tn) + 1, (size_t)std::max(1, K / (8 * GK)));
+  splits = (int)std::min<size_t>(splits, scratch_floats / mn);
+  if (splits < 2) splits = 1;
+  const int kper = (int)align_up((size_t)(K + splits - 1) / splits, GK);
+  splits = (K + kper - 1) / kper;
+  float *dst = splits > 1 ? scratch : C;
+  const dim3 grid(tn, tm, splits), block(256);
+  if (wm == 4) hipLaunchKernelGGL((sgemm_tn_kernel<4, 1>), grid, block, 0, st, A, lda, W, ldw, dst, N, M, N, K, kper, mn);
+  else if (wm == 2) hipLaunchKernelGGL((sgemm_tn_kernel<2, 2>), grid, block, 0, st, A, lda, W, ldw, dst, N, M, N, K, kper, mn);
+  else hipLaunchKernelGGL((sgemm_tn_kernel<1, 4>), grid, block, 0, st, A, lda, W, ldw, dst, N, M, N, K, kper, mn);
   QUAMBA_LAUNCH_CHECK();
+  if (splits > 1) {
+    hipLaunchKernelGGL(sgemm_sum_kernel, dim3((unsigned)((mn / 4 + 255) / 256)), block, 0, st, scratch, splits, mn, C);
+    QUAMBA_LAUNCH_CHECK();
+  }
   return QUAMBA_OK;
 }
 
@@ -82,94 +153,243 @@ __global__ void fill_u32_kernel(unsigned *p, size_t n, unsigned v) {
   if (i < n) p[i] = v;
 }
 
-// max |x| over the column range [c0, c1) of a [rows, ld] matrix, as the bit pattern of a
-// non-negative float (which orders like an unsigned integer) combined with atomicMax.
-__global__ __launch_bounds__(256) void absmax_kernel(const float *__restrict__ x, size_t rows, int ld, int c0,
-                                                     int c1, unsigned *slot) {
-  const int w = c1 - c0;
-  const size_t total = rows * (size_t)w;
+// max |x| over column ranges of matrices, each as the bit pattern of a non-negative float (which orders like an unsigned
+// integer) combined with atomicMax, once per workgroup: thousands of waves on one word took 100 us per tensor.  All
+// tensors of a calibration go in one launch, in which a segment has workgroups in proportion to its size and a row as
+// many threads as it has pieces of four (the 16 columns of B: 64 rows at once; one row at a time took 490 us).  4 x 256
+// tokens of the 2.8B layer, 320 MB: 63 us, fifteen launches before it 980.
+constexpr int MAX_SEGS = 16;
+struct AbsmaxSegs {
+  const float *p[MAX_SEGS];  // first element of the range
+  size_t rows[MAX_SEGS], total[MAX_SEGS];
+  int ld[MAX_SEGS], w[MAX_SEGS], slot[MAX_SEGS];
+  int lt[MAX_SEGS];        // log2 of the threads per row
+  unsigned end[MAX_SEGS];  // workgroups up to and with this segment
+};
+
+__global__ __launch_bounds__(256) void absmax_kernel(AbsmaxSegs s, unsigned *slots) {
+  int i = 0;
+  while (blockIdx.x >= s.end[i]) ++i;
+  const unsigned first = i ? s.end[i - 1] : 0u, nb = s.end[i] - first;
+  const int w = s.w[i], lt = s.lt[i], at = threadIdx.x & ((1 << lt) - 1);
   float m = 0.f;
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (size_t)gridDim.x * 256) {
-    const size_t r = i / w;
-    const int c = static_cast<int>(i % w);
-    m = fmaxf(m, fabsf(x[r * ld + c0 + c]));
+  for (size_t r = ((blockIdx.x - first) << (8 - lt)) + (threadIdx.x >> lt); r < s.rows[i]; r += (size_t)nb << (8 - lt)) {
+    const float *row = s.p[i] + r * s.ld[i];
+    const int n = (int)min((size_t)w, s.total[i] - r * w);
+#pragma unroll 4
+    for (int c = at * 4; c < n; c += 4 << lt) {  // every range is a multiple of four long
+      const f4 v = *reinterpret_cast<const f4u *>(row + c);
+      m = fmaxf(fmaxf(m, fmaxf(fabsf(v[0]), fabsf(v[1]))), fmaxf(fabsf(v[2]), fabsf(v[3])));
+    }
   }
+  __shared__ float part[4];
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
-  if ((threadIdx.x & 63) == 0) atomicMax(slot, __float_as_uint(m));
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0)
+    atomicMax(slots + s.slot[i], __float_as_uint(fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3]))));
 }
 
-int absmax(const float *x, size_t rows, int ld, int c0, int c1, unsigned *slot, hipStream_t st) {
-  const size_t total = rows * (size_t)(c1 - c0);
-  const unsigned blocks = (unsigned)std::min<size_t>((total + 255) / 256, 2048);
-  hipLaunchKernelGGL(absmax_kernel, dim3(blocks ? blocks : 1), dim3(256), 0, st, x, rows, ld, c0, c1, slot);
+struct Obs {
+  const float *p;
+  size_t rows;
+  int ld, c0, c1, slot;
+};
+
+int absmax(const Obs *obs, int count, unsigned *slots, hipStream_t st) {
+  AbsmaxSegs s{};
+  unsigned end = 0;
+  for (int i = 0; i < count; ++i) {
+    const Obs &o = obs[i];
+    int w = o.c1 - o.c0, ld = o.ld;
+    size_t rows = o.rows;
+    const size_t total = rows * (size_t)w;
+    if (w == ld) {  // one long row: cut it into pieces of 4096
+      w = ld = 4096;
+      rows = (total + 4095) / 4096;
+    }
+    s.p[i] = o.p + o.c0; s.rows[i] = rows; s.total[i] = total; s.ld[i] = ld; s.w[i] = w; s.slot[i] = o.slot;
+    int lt = 2;
+    while (lt < 8 && (4 << lt) < w) ++lt;
+    s.lt[i] = lt;
+    // at least 8192 values per workgroup, at most 512 workgroups
+    s.end[i] = end += (unsigned)std::min<size_t>((total + 8191) / 8192, 512);
+  }
+  hipLaunchKernelGGL(absmax_kernel, dim3(end), dim3(256), 0, st, s, slots);
   QUAMBA_LAUNCH_CHECK();
   return QUAMBA_OK;
 }
 
-// causal conv (width 4, zero history) + bias + SiLU in fp32; xz has row stride ld
-__global__ void conv_silu_f32_kernel(const float *__restrict__ xz, int ld, const float *__restrict__ w,
-                                     const float *__restrict__ b, int L, int Di, float *__restrict__ x,
-                                     size_t total) {
+// causal conv (width 4, zero history) + bias + SiLU in fp32, four channels per thread; xz has row stride ld
+__global__ __launch_bounds__(256) void conv_silu_f32_kernel(const float *__restrict__ xz, int ld, const float *__restrict__ w,
+                                                            const float *__restrict__ b, int L, int Di,
+                                                            float *__restrict__ x, size_t total4) {
   const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= total) return;
-  const int d = static_cast<int>(i % Di);
-  const size_t row = i / Di;
-  const int t = static_cast<int>(row % L);
-  float v = b[d];
+  if (i >= total4) return;
+  const unsigned per = Di / 4;
+  const size_t row = i / per;
+  const int d = static_cast<int>(i % per) * 4, t = static_cast<int>(row % L);
+  f4 wv[4], v = *reinterpret_cast<const f4u *>(b + d);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) wv[c] = *reinterpret_cast<const f4u *>(w + (size_t)(d + c) * 4);
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    const int tj = t - 3 + j;
-    if (tj >= 0) v += w[d * 4 + j] * xz[(row - 3 + j) * ld + d];
-  }
-  x[i] = v / (1.f + expf(-v));
-}
-
-// sequential fp32 selective scan + gate, one thread per (sequence, channel)
-__global__ void scan_f32_kernel(const float *__restrict__ x, const float *__restrict__ dt_raw,
-                                const float *__restrict__ dt_bias, const float *__restrict__ A,
-                                const float *__restrict__ dbc, int nx, int R, const float *__restrict__ D,
-                                const float *__restrict__ xz, int Bt, int L, int Di, float *__restrict__ g) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= (size_t)Bt * Di) return;
-  const int d = static_cast<int>(i % Di), b = static_cast<int>(i / Di);
-  float a2[16], h[16];
+    if (t - 3 + j >= 0) {
+      const f4 s = *reinterpret_cast<const f4 *>(xz + (row - 3 + j) * ld + d);
 #pragma unroll
-  for (int n = 0; n < 16; ++n) {
-    a2[n] = A[(size_t)d * 16 + n] * LOG2E;
-    h[n] = 0.f;
-  }
-  const float bias = dt_bias[d], Dv = D[d];
-  for (int t = 0; t < L; ++t) {
-    const size_t row = (size_t)b * L + t;
-    const float xv = x[row * Di + d];
-    const float pre = dt_raw[row * Di + d] + bias;
-    const float dt = pre > 20.f ? pre : log1pf(expf(pre));
-    const float zv = xz[row * (2 * (size_t)Di) + Di + d];
-    const float *B = dbc + row * nx + R, *C = B + 16;
-    float y = 0.f;
-#pragma unroll
-    for (int n = 0; n < 16; ++n) {
-      h[n] = exp2f(dt * a2[n]) * h[n] + dt * xv * B[n];
-      y += C[n] * h[n];
+      for (int c = 0; c < 4; ++c) v[c] += wv[c][j] * s[c];
     }
-    y += Dv * xv;
-    g[row * Di + d] = y * zv / (1.f + expf(-zv));
+  }
+#pragma unroll
+  for (int c = 0; c < 4; ++c) v[c] = v[c] / (1.f + expf(-v[c]));
+  *reinterpret_cast<f4 *>(x + row * Di + d) = v;
+}
+
+// fp32 selective scan + gate.  A workgroup owns 32 channels of one sequence, 8 lanes per channel with two of the 16
+// states each, and walks the tokens in blocks of 32.  What is per (token, channel) is done once by all threads, a block
+// ahead of the recurrence, and handed over in LDS together with B and C; the C h sums of a token are added over
+// the eight lanes and gated by all threads again, so every access of global memory is a row of 32 channels.  With one
+// thread per channel (80 workgroups at 4 x 5120 channels, 256 tokens) the serial chain of loads and exponentials took 367
+// us; this takes 94.
+constexpr int ST = 32, SC = 32;
+
+__global__ __launch_bounds__(256) void scan_f32_kernel(const float *__restrict__ x, const float *__restrict__ dt_raw,
+                                                       const float *__restrict__ dt_bias, const float *__restrict__ A,
+                                                       const float *__restrict__ dbc, int nx, int R,
+                                                       const float *__restrict__ D, const float *__restrict__ xz, int L,
+                                                       int Di, float *__restrict__ g) {
+  __shared__ float2 sdt[ST][SC + 1];  // (dt, dt x)
+  __shared__ float sy[ST][SC + 1];
+  __shared__ __attribute__((aligned(16))) float sbc[ST][32];  // B then C of a token
+  const int tid = threadIdx.x;
+  const int nc = (Di + SC - 1) / SC;
+  const int c0 = (blockIdx.x % nc) * SC;
+  const size_t row0 = (size_t)(blockIdx.x / nc) * L;
+  // elementwise part: thread -> channel tid % 32, tokens tid / 32 + 8 i
+  const int ec = tid & 31, et = tid >> 5, ed = c0 + ec;
+  const bool eon = ed < Di;
+  const float bias = eon ? dt_bias[ed] : 0.f, Dv = eon ? D[ed] : 0.f;
+  // recurrence part: thread -> channel tid / 8, states 2 (tid % 8) and the next
+  const int rc = tid >> 3, rg = tid & 7, rd = c0 + rc;
+  float a0 = 0.f, a1 = 0.f, h0 = 0.f, h1 = 0.f;
+  if (rd < Di) {
+    a0 = A[(size_t)rd * 16 + 2 * rg] * LOG2E;
+    a1 = A[(size_t)rd * 16 + 2 * rg + 1] * LOG2E;
+  }
+  float xv[4], pv[4], zv[4], bc[4];
+  auto fetch = [&](int t0) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int t = t0 + et + 8 * i;
+      xv[i] = pv[i] = zv[i] = bc[i] = 0.f;
+      if (t < L) {
+        const size_t row = row0 + t;
+        bc[i] = dbc[row * nx + R + ec];
+        if (eon) {
+          xv[i] = x[row * Di + ed];
+          pv[i] = dt_raw[row * Di + ed];
+          zv[i] = xz[row * (2 * (size_t)Di) + Di + ed];
+        }
+      }
+    }
+  };
+  fetch(0);
+  for (int t0 = 0; t0 < L; t0 += ST) {
+    float dx[4], zg[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float pre = pv[i] + bias;
+      const float dt = pre > 20.f ? pre : log1pf(expf(pre));
+      sdt[et + 8 * i][ec] = make_float2(dt, dt * xv[i]);
+      sbc[et + 8 * i][ec] = bc[i];
+      dx[i] = Dv * xv[i];
+      zg[i] = zv[i];
+    }
+    __syncthreads();
+    if (t0 + ST < L) fetch(t0 + ST);
+    const int nt = min(ST, L - t0);
+    for (int t = 0; t < nt; ++t) {
+      const float2 d = sdt[t][rc];
+      const float2 B = *reinterpret_cast<const float2 *>(&sbc[t][2 * rg]);
+      const float2 C = *reinterpret_cast<const float2 *>(&sbc[t][16 + 2 * rg]);
+      h0 = exp2f(d.x * a0) * h0 + d.y * B.x;
+      h1 = exp2f(d.x * a1) * h1 + d.y * B.y;
+      float y = C.x * h0 + C.y * h1;
+      y += __shfl_xor(y, 1);
+      y += __shfl_xor(y, 2);
+      y += __shfl_xor(y, 4);
+      if (rg == 0) sy[t][rc] = y;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int t = et + 8 * i;
+      if (t < nt && eon) {
+        const float y = sy[t][ec] + dx[i];
+        g[(row0 + t0 + t) * Di + ed] = y * zg[i] / (1.f + expf(-zg[i]));
+      }
+    }
   }
 }
 
-// radix-select histogram: count byte `shift/8` of |x| bit patterns whose higher bits equal prefix
-__global__ void select_hist_kernel(const float *__restrict__ x, size_t n, unsigned prefix, unsigned mask,
-                                   int shift, unsigned long long *hist) {
+// Radix select: the value of 1-based rank `rank` among |x|, most significant byte first.  Pass p counts byte 3 - p of the bit
+// patterns whose higher bytes are those already found; every workgroup finds these again from the earlier histograms
+// (hist[4][256], cleared beforehand), so that the four passes follow one another without the host in between (it used
+// to read 2 KB and wait after each: four round trips of about 55 us).
+__device__ unsigned select_prefix(const unsigned long long *hist, int passes, unsigned long long rank,
+                                  unsigned long long *sum) {
+  __shared__ unsigned byte;
+  unsigned prefix = 0;
+  unsigned long long below = 0;  // elements known to be smaller than every candidate
+  const int t = threadIdx.x;
+  for (int p = 0; p < passes; ++p) {
+    const unsigned long long own = hist[p * 256 + t];
+    sum[t] = own;
+    if (t == 0) byte = 255u;
+    __syncthreads();
+    for (int off = 1; off < 256; off <<= 1) {  // inclusive scan
+      const unsigned long long v = t >= off ? sum[t - off] : 0ull;
+      __syncthreads();
+      sum[t] += v;
+      __syncthreads();
+    }
+    const unsigned long long upto = below + sum[t];
+    if (upto >= rank && upto - own < rank) byte = t;  // at most one bin
+    __syncthreads();
+    prefix |= byte << (24 - 8 * p);
+    below += byte ? sum[byte - 1] : 0ull;
+    __syncthreads();
+  }
+  return prefix;
+}
+
+__global__ __launch_bounds__(256) void select_hist_kernel(const float *__restrict__ x, size_t n, int pass,
+                                                          unsigned long long rank, unsigned long long *hist) {
+  __shared__ unsigned long long sum[256];
   __shared__ unsigned local[256];
   local[threadIdx.x] = 0;
+  const unsigned prefix = select_prefix(hist, pass, rank, sum);
+  const unsigned mask = pass ? ~0u << (32 - 8 * pass) : 0u;
+  const int shift = 24 - 8 * pass;
   __syncthreads();
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) {
-    const unsigned bits = __float_as_uint(fabsf(x[i]));
-    if ((bits & mask) == prefix) atomicAdd(&local[(bits >> shift) & 255u], 1u);
+  for (size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4; i < n; i += (size_t)gridDim.x * 1024) {  // n: a multiple of 16
+    const f4 v = *reinterpret_cast<const f4 *>(x + i);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const unsigned bits = __float_as_uint(fabsf(v[e]));
+      if ((bits & mask) == prefix) atomicAdd(&local[(bits >> shift) & 255u], 1u);
+    }
   }
   __syncthreads();
-  if (local[threadIdx.x]) atomicAdd(&hist[threadIdx.x], (unsigned long long)local[threadIdx.x]);
+  if (local[threadIdx.x]) atomicAdd(&hist[pass * 256 + threadIdx.x], (unsigned long long)local[threadIdx.x]);
+}
+
+__global__ __launch_bounds__(256) void select_finish_kernel(const unsigned long long *hist, unsigned long long rank,
+                                                            unsigned *out) {
+  __shared__ unsigned long long sum[256];
+  const unsigned prefix = select_prefix(hist, 4, rank, sum);
+  if (threadIdx.x == 0) *out = prefix;
 }
 
 // ---------------------------------------------------------------- model-optimal clipping scalar
@@ -260,17 +480,61 @@ __global__ void clip_init_kernel(double *state) {
 
 constexpr size_t CLIP_WS_BYTES = 256 + CLIP_BLOCKS * sizeof(ClipPart);
 
-__global__ void quantize_f32_kernel(const float *__restrict__ x, int8_t *__restrict__ q, size_t n, float inv_s) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
-  float v = __builtin_rintf(x[i] * inv_s);
-  v = fminf(fmaxf(v, -128.f), 127.f);
-  q[i] = static_cast<int8_t>(static_cast<int>(v));
+// Eq. 2 for several tensors in one launch: q = clamp(rne(x * inv_s)), four values per thread and step; every tensor is a
+// multiple of four long.  A segment marked `copy` is copied as fp32 instead.
+typedef unsigned u1u __attribute__((aligned(1)));
+struct QuantSegs {
+  const float *x[MAX_SEGS];
+  void *q[MAX_SEGS];
+  size_t n[MAX_SEGS];
+  float inv_s[MAX_SEGS];
+  int copy[MAX_SEGS];
+  unsigned end[MAX_SEGS];
+};
+constexpr int Q_PER_WG = 8192;
+
+__global__ __launch_bounds__(256) void quantize_f32_kernel(QuantSegs s) {
+  int i = 0;
+  while (blockIdx.x >= s.end[i]) ++i;
+  const size_t at = (size_t)(blockIdx.x - (i ? s.end[i - 1] : 0u)) * Q_PER_WG;
+  const size_t stop = min(s.n[i], at + Q_PER_WG);
+  const float *x = s.x[i], inv_s = s.inv_s[i];
+  const bool copy = s.copy[i];
+#pragma unroll 4
+  for (size_t k = at + threadIdx.x * 4; k < stop; k += 1024) {
+    const f4 v = *reinterpret_cast<const f4u *>(x + k);
+    if (copy) {
+      *reinterpret_cast<f4u *>(static_cast<float *>(s.q[i]) + k) = v;
+      continue;
+    }
+    unsigned word = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float r = fminf(fmaxf(__builtin_rintf(v[e] * inv_s), -128.f), 127.f);
+      word |= ((unsigned)static_cast<int>(r) & 255u) << (8 * e);
+    }
+    *reinterpret_cast<u1u *>(static_cast<int8_t *>(s.q[i]) + k) = word;
+  }
 }
 
-__global__ void copy_f32_kernel(const float *x, float *y, size_t n) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) y[i] = x[i];
+struct Quant {
+  const float *x;
+  void *q;
+  size_t n;
+  float inv_s;
+  int copy;
+};
+
+int quantize_f32(const Quant *qs, int count, hipStream_t st) {
+  QuantSegs s{};
+  unsigned end = 0;
+  for (int i = 0; i < count; ++i) {
+    s.x[i] = qs[i].x; s.q[i] = qs[i].q; s.n[i] = qs[i].n; s.inv_s[i] = qs[i].inv_s; s.copy[i] = qs[i].copy;
+    s.end[i] = end += (unsigned)((qs[i].n + Q_PER_WG - 1) / Q_PER_WG);
+  }
+  hipLaunchKernelGGL(quantize_f32_kernel, dim3(end), dim3(256), 0, st, s);
+  QUAMBA_LAUNCH_CHECK();
+  return QUAMBA_OK;
 }
 
 // max(0, -min x) over x[0, n), as the bit pattern of a non-negative float
@@ -320,7 +584,7 @@ CalPlan cal_plan(const quamba_dims *d, int nb, int Lc) {
   p.woh = take(Dm * Di * 4);
   p.a = take(Di * d->d_state * 4);
   p.slots = take(32 * 4);
-  p.hist = take(256 * 8);
+  p.hist = take(4 * 256 * 8);
   p.clip = take(CLIP_WS_BYTES);
   p.total = off;
   return p;
@@ -351,14 +615,15 @@ int fp_forward(const quamba_dims *d, const quamba_fp_weights *w, const __half *c
   hipLaunchKernelGGL(neg_exp_kernel, dim3(nblk((size_t)Di * N)), dim3(256), 0, st, w->A_log, b.A, (size_t)Di * N);
   QUAMBA_LAUNCH_CHECK();
   int rc;
-  if ((rc = sgemm(b.u32, Dm, w->W_in, Dm, b.xz, 2 * Di, (int)M, 2 * Di, Dm, st))) return rc;
-  hipLaunchKernelGGL(conv_silu_f32_kernel, dim3(nblk(M * Di)), dim3(256), 0, st, b.xz, 2 * Di, w->conv_w,
-                     w->conv_b, Lc, Di, b.x, M * Di);
+  // partial sums of a split K go to buffers that are written later
+  if ((rc = sgemm(b.u32, Dm, w->W_in, Dm, b.xz, (int)M, 2 * Di, Dm, b.x, b.A - b.x, st))) return rc;
+  hipLaunchKernelGGL(conv_silu_f32_kernel, dim3(nblk(M * Di / 4)), dim3(256), 0, st, b.xz, 2 * Di, w->conv_w,
+                     w->conv_b, Lc, Di, b.x, M * Di / 4);
   QUAMBA_LAUNCH_CHECK();
-  if ((rc = sgemm(b.x, Di, w->W_x, Di, b.dbc, NX, (int)M, NX, Di, st))) return rc;
-  if ((rc = sgemm(b.dbc, NX, w->W_dt, R, b.dtr, Di, (int)M, Di, R, st))) return rc;
-  hipLaunchKernelGGL(scan_f32_kernel, dim3(nblk((size_t)nb * Di)), dim3(256), 0, st, b.x, b.dtr, w->dt_bias, b.A,
-                     b.dbc, NX, R, w->D, b.xz, nb, Lc, Di, b.g);
+  if ((rc = sgemm(b.x, Di, w->W_x, Di, b.dbc, (int)M, NX, Di, b.gH, b.A - b.gH, st))) return rc;
+  if ((rc = sgemm(b.dbc, NX, w->W_dt, R, b.dtr, (int)M, Di, R, b.gH, b.A - b.gH, st))) return rc;
+  hipLaunchKernelGGL(scan_f32_kernel, dim3((unsigned)((Di + SC - 1) / SC) * nb), dim3(256), 0, st, b.x, b.dtr, w->dt_bias, b.A, b.dbc, NX,
+                     R, w->D, b.xz, Lc, Di, b.g);
   QUAMBA_LAUNCH_CHECK();
   return QUAMBA_OK;
 }
@@ -401,7 +666,7 @@ int fp_mixer(const quamba_dims *d, const quamba_fp_weights *w, const __half *u, 
   const CalBufs b = carve(p, ws);
   int rc;
   if ((rc = fp_forward(d, w, u, nb, Lc, b, st))) return rc;
-  return sgemm(b.g, d->d_inner, w->W_out, d->d_inner, out, d->d_model, nb * Lc, d->d_model, d->d_inner, st);
+  return sgemm(b.g, d->d_inner, w->W_out, d->d_inner, out, nb * Lc, d->d_model, d->d_inner, b.gH, b.A - b.gH, st);
 }
 
 int calibrate(const quamba_dims *d, const quamba_fp_weights *w, const __half *calib_u, int nb, int Lc,
@@ -460,16 +725,18 @@ int calibrate(const quamba_dims *d, const quamba_fp_weights *w, const __half *ca
   unsigned *slots = b.slots;
   unsigned long long *hist = b.hist;
 
-  hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(256), 0, st, slots, (size_t)32, 0u);
+  {  // observer slots and the histograms behind them
+    const size_t words = (p.hist - p.slots) / 4 + 4 * 256 * 2;
+    hipLaunchKernelGGL(fill_u32_kernel, dim3(nblk(words)), dim3(256), 0, st, slots, words, 0u);
+  }
   QUAMBA_LAUNCH_CHECK();
   int rc;
   if ((rc = fp_forward(d, w, calib_u, nb, Lc, b, st))) return rc;
+  if (out_f32 && (rc = sgemm(g, Di, w->W_out, Di, out_f32, (int)M, Dm, Di, gH, A - gH, st))) return rc;
   if ((rc = launch_hadamard_f32(g, (int)M, Di, gH, st))) return rc;      // y^H = H_n g
   if ((rc = launch_hadamard_f32(w->W_out, Dm, Di, woh, st))) return rc;  // rows of W_out^H
-  if (out_f32 && (rc = sgemm(g, Di, w->W_out, Di, out_f32, Dm, (int)M, Dm, Di, st))) return rc;
 
   // observers
-  struct Obs { const float *p; size_t rows; int ld, c0, c1, slot; };
   const Obs obs[] = {
       {u32, M, Dm, 0, Dm, S_U},         {xz, M, 2 * Di, 0, Di, S_XPRE},    {xz, M, 2 * Di, Di, 2 * Di, S_Z},
       {dbc, M, NX, 0, R, S_DTL},        {dbc, M, NX, R, R + N, S_B},       {dbc, M, NX, R + N, NX, S_C},
@@ -477,47 +744,27 @@ int calibrate(const quamba_dims *d, const quamba_fp_weights *w, const __half *ca
       {w->conv_w, (size_t)Di, 4, 0, 4, S_CW}, {w->W_x, (size_t)NX, Di, 0, Di, S_WX},
       {w->W_dt, (size_t)Di, R, 0, R, S_WDT},  {A, (size_t)Di, N, 0, N, S_A},   {w->D, 1, Di, 0, Di, S_D},
       {woh, (size_t)Dm, Di, 0, Di, S_WOH}};
-  for (const Obs &o : obs)
-    if ((rc = absmax(o.p, o.rows, o.ld, o.c0, o.c1, slots + o.slot, st))) return rc;
-
-  float mx[S_COUNT];
-  QUAMBA_HIP(hipMemcpyAsync(mx, slots, sizeof(mx), hipMemcpyDeviceToHost, st));
-  QUAMBA_HIP(hipStreamSynchronize(st));
+  if ((rc = absmax(obs, sizeof(obs) / sizeof(obs[0]), slots, st))) return rc;
 
   const size_t nx = M * Di;
-  float xp;
+  if (x_rule != QUAMBA_X_MSE_CLIP) {
+    // percentile maximum of |x| (Section 4.2): value of 1-based rank ceil(p/100 * n)
+    size_t rank = (size_t)std::ceil(x_percentile * (double)nx / 100.0);
+    if (rank < 1) rank = 1;
+    if (rank > nx) rank = nx;
+    for (int pass = 0; pass < 4; ++pass)
+      hipLaunchKernelGGL(select_hist_kernel, dim3(1024), dim3(256), 0, st, x, nx, pass, (unsigned long long)rank, hist);
+    hipLaunchKernelGGL(select_finish_kernel, dim3(1), dim3(256), 0, st, hist, (unsigned long long)rank, slots + S_COUNT);
+    QUAMBA_LAUNCH_CHECK();
+  }
+  float mx[S_COUNT + 1];
+  QUAMBA_HIP(hipMemcpyAsync(mx, slots, sizeof(mx), hipMemcpyDeviceToHost, st));
+  QUAMBA_HIP(hipStreamSynchronize(st));
+  float xp = mx[S_COUNT];
   if (x_rule == QUAMBA_X_MSE_CLIP) {
     double clip;
     if ((rc = clip_search(x, nx, 8, 32, &clip, nullptr, base + p.clip, CLIP_WS_BYTES, st))) return rc;
     xp = static_cast<float>(clip);
-  } else {
-  // percentile maximum of |x| (Section 4.2): value of 1-based rank ceil(p/100 * n), found by a
-  // most-significant-byte-first radix select on the bit patterns
-  size_t rank = (size_t)std::ceil(x_percentile * (double)nx / 100.0);
-  if (rank < 1) rank = 1;
-  if (rank > nx) rank = nx;
-  unsigned prefix = 0, mask = 0;
-  size_t below = 0;  // elements known to be smaller than every candidate
-  for (int shift = 24; shift >= 0; shift -= 8) {
-    hipLaunchKernelGGL(fill_u32_kernel, dim3(2), dim3(256), 0, st, reinterpret_cast<unsigned *>(hist),
-                       (size_t)512, 0u);
-    hipLaunchKernelGGL(select_hist_kernel, dim3(1024), dim3(256), 0, st, x, nx, prefix, mask, shift, hist);
-    QUAMBA_LAUNCH_CHECK();
-    unsigned long long h[256];
-    QUAMBA_HIP(hipMemcpyAsync(h, hist, sizeof(h), hipMemcpyDeviceToHost, st));
-    QUAMBA_HIP(hipStreamSynchronize(st));
-    int byte = 255;
-    for (int v = 0; v < 256; ++v) {
-      if (below + h[v] >= rank) {
-        byte = v;
-        break;
-      }
-      below += h[v];
-    }
-    prefix |= (unsigned)byte << shift;
-    mask |= 0xffu << shift;
-  }
-  std::memcpy(&xp, &prefix, 4);
   }
 
   if (x_clip_out) *x_clip_out = xp;  // the clipping value of x before it becomes a scale
@@ -544,19 +791,13 @@ int calibrate(const quamba_dims *d, const quamba_fp_weights *w, const __half *ca
   *os = s;
 
   // quantize the weights (Eq. 2) and copy the two fp32 bias vectors
-  struct QW { const float *src; int8_t *dst; size_t n; float sc; };
-  const QW qws[] = {{w->W_in, oq->W_in, (size_t)2 * Di * Dm, s.s_Win}, {w->conv_w, oq->conv_w, (size_t)Di * 4, s.s_cw},
-                    {w->W_x, oq->W_x, (size_t)NX * Di, s.s_Wx},        {w->W_dt, oq->W_dt, (size_t)Di * R, s.s_Wdt},
-                    {A, oq->A, (size_t)Di * N, s.s_A},                 {w->D, oq->D, (size_t)Di, s.s_D},
-                    {woh, oq->W_outH, (size_t)Dm * Di, s.s_WoutH}};
-  for (const QW &q : qws) {
-    hipLaunchKernelGGL(quantize_f32_kernel, dim3(nblk(q.n)), dim3(256), 0, st, q.src, q.dst, q.n,
-                       (float)(1.0 / (double)q.sc));
-    QUAMBA_LAUNCH_CHECK();
-  }
-  hipLaunchKernelGGL(copy_f32_kernel, dim3(nblk(Di)), dim3(256), 0, st, w->conv_b, oq->conv_b, (size_t)Di);
-  hipLaunchKernelGGL(copy_f32_kernel, dim3(nblk(Di)), dim3(256), 0, st, w->dt_bias, oq->dt_bias, (size_t)Di);
-  QUAMBA_LAUNCH_CHECK();
+  auto inv = [](float sc) { return (float)(1.0 / (double)sc); };
+  const Quant qws[] = {{w->W_in, oq->W_in, (size_t)2 * Di * Dm, inv(s.s_Win), 0}, {w->conv_w, oq->conv_w, (size_t)Di * 4, inv(s.s_cw), 0},
+                       {w->W_x, oq->W_x, (size_t)NX * Di, inv(s.s_Wx), 0},        {w->W_dt, oq->W_dt, (size_t)Di * R, inv(s.s_Wdt), 0},
+                       {A, oq->A, (size_t)Di * N, inv(s.s_A), 0},                 {w->D, oq->D, (size_t)Di, inv(s.s_D), 0},
+                       {woh, oq->W_outH, (size_t)Dm * Di, inv(s.s_WoutH), 0},     {w->conv_b, oq->conv_b, (size_t)Di, 0.f, 1},
+                       {w->dt_bias, oq->dt_bias, (size_t)Di, 0.f, 1}};
+  if ((rc = quantize_f32(qws, sizeof(qws) / sizeof(qws[0]), st))) return rc;
   QUAMBA_HIP(hipStreamSynchronize(st));
   return QUAMBA_OK;
 }
@@ -580,8 +821,8 @@ int calibrate_hadx(const quamba_dims *d, const quamba_fp_weights *w, const __hal
   QUAMBA_LAUNCH_CHECK();
   if ((rc = launch_hadamard_f32(b.x, (int)M, Di, b.gH, st))) return rc;
   if ((rc = launch_hadamard_f32(w->W_x, NX, Di, b.woh, st))) return rc;
-  if ((rc = absmax(b.gH, M, Di, 0, Di, b.slots + 0, st))) return rc;
-  if ((rc = absmax(b.woh, (size_t)NX, Di, 0, Di, b.slots + 1, st))) return rc;
+  const Obs obs[] = {{b.gH, M, Di, 0, Di, 0}, {b.woh, (size_t)NX, Di, 0, Di, 1}};
+  if ((rc = absmax(obs, 2, b.slots, st))) return rc;
   float mx[2];
   QUAMBA_HIP(hipMemcpyAsync(mx, b.slots, sizeof(mx), hipMemcpyDeviceToHost, st));
   QUAMBA_HIP(hipStreamSynchronize(st));
@@ -595,8 +836,8 @@ int calibrate_hadx(const quamba_dims *d, const quamba_fp_weights *w, const __hal
   oh->m_xh_C = (float)(a * c / ((double)Di * (double)os->s_C));
   oh->xhat_scale = (float)(a / (double)Di);
   const size_t nw = (size_t)NX * Di;
-  hipLaunchKernelGGL(quantize_f32_kernel, dim3(nblk(nw)), dim3(256), 0, st, b.woh, oh->W_xH, nw, (float)(1.0 / c));
-  QUAMBA_LAUNCH_CHECK();
+  const Quant qw{b.woh, oh->W_xH, nw, (float)(1.0 / c), 0};
+  if ((rc = quantize_f32(&qw, 1, st))) return rc;
   QUAMBA_HIP(hipStreamSynchronize(st));
   return QUAMBA_OK;
 }
@@ -657,7 +898,8 @@ int calibrate_xfmt(const quamba_dims *d, const quamba_fp_weights *w, const __hal
   } else {
     hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(256), 0, st, b.slots, (size_t)32, 0u);
     QUAMBA_LAUNCH_CHECK();
-    if ((rc = absmax(b.x, (size_t)nb * Lc, Di, 0, Di, b.slots + 0, st))) return rc;
+    const Obs obs{b.x, (size_t)nb * Lc, Di, 0, Di, 0};
+    if ((rc = absmax(&obs, 1, b.slots, st))) return rc;
     float mx;
     QUAMBA_HIP(hipMemcpyAsync(&mx, b.slots, sizeof(mx), hipMemcpyDeviceToHost, st));
     QUAMBA_HIP(hipStreamSynchronize(st));
