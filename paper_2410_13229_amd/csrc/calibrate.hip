@@ -24,43 +24,51 @@ typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 // ---------------------------------------------------------------- fp32 GEMM, C = A W^T
-// fp32 matrix units (v_mfma_f32_32x32x2_f32: fp32 operands, fp32 sums, 256 flop per clock and CU).  A wave owns 32 rows
-// x 64 columns of the output: the weight rows are the MFMA A operand, so a lane ends with four consecutive columns
-// of one row.  A slice is 32 of K, register-prefetched into one padded LDS buffer; a lane reads four consecutive k as
-// 16 bytes and spends them in four products (the half-wave h takes k = 4h .. 4h + 3 of every eight: both operands
-// agree, so the order of the sum over k is all that changes), so LDS gives 0.75 reads per four products and the
-// matrix pipe is what bounds it.  Small tiles on purpose: 1024 x 10240 is 1280 workgroups of 128 x 64, five on every
-// CU, whose waves cover each other's barriers.  WM x WN waves: 128 x 64, 64 x 128, 32 x 256 outputs per workgroup.
-// 1024 x 10240 x 2560: 511 us = 105 TFLOP/s of the 157 that fp32 matrix products reach at most (a 64 x 64 tile on the
-// vector units: 935 us); 1024 x 192 x 5120 with K in 20 ranges 26 + 6 us (one range of 48 tiles on the vector units: 728).
+// fp32 matrix units (fp32 operands, fp32 sums, 256 flop per clock and CU).  Every scale of the layer hangs on these sums, and a
+// scale that moves in its last bit moves int8 codes, so their order is fixed: an output is one chain of fused
+// multiply-adds over k = 0, 1, 2, ..., whatever the tile (the matrix instructions add their two or four products in the order
+// of k, each with one rounding: compared with v_fma_f32 bit for bit), and K is never split.
+//
+// Large outputs (v_mfma_f32_32x32x2_f32): a wave owns 32 rows x 64 columns; the weight rows are the MFMA A operand, so a
+// lane ends with four consecutive columns of one row.  A slice is 32 of K, register-prefetched into one padded LDS
+// buffer; a lane reads four consecutive k of every eight as 16 bytes, and two swaps between the halves of the wave make of
+// the four registers the operands of four products in the order of k (stored in that order instead, as pairs, the
+// products took 600 us at the size below), so LDS gives 0.75 reads per four products and the matrix pipe is what bounds it.
+// Small tiles on purpose: 1024 x 10240 is 1280 workgroups of 128 x 64, five on every CU, whose waves cover each other's barriers.
+// WM x WN waves: 128 x 64, 64 x 128, 32 x 256 outputs per workgroup.  1024 x 10240 x 2560: 553 us = 97 TFLOP/s of the
+// 157 that fp32 matrix products reach at most (a 64 x 64 tile on the vector units: 935 us).
 constexpr int GK = 32, GLD = GK + 4;
 
 template <int WM, int WN>
 __global__ __launch_bounds__(256) void sgemm_tn_kernel(const float *__restrict__ A, int lda, const float *__restrict__ W,
-                                                       int ldw, float *__restrict__ C, int ldc, int M, int N, int K,
-                                                       int kper, size_t cstride) {
+                                                       int ldw, float *__restrict__ C, int ldc, int M, int N, int K) {
   constexpr int BM = 32 * WM, BN = 64 * WN;
   __shared__ __attribute__((aligned(16))) float sa[BM * GLD], sw[BN * GLD];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave % WM, wn = wave / WM, l31 = lane & 31, h = lane >> 5;
   const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-  const int k0 = blockIdx.z * kper, k1 = min(K, k0 + kper);
 
   f4 ra[WM], rw[2 * WN];
   const int prow = tid >> 3, pk = (tid & 7) * 4;  // eight 16-byte pieces per row and slice
-  auto fetch = [&](int k) {                        // K and kper are multiples of 16: a piece is in range or out of it
+  auto fetch = [&](int k) {                        // K is a multiple of 16: a piece is in range or out of it
 #pragma unroll
     for (int i = 0; i < WM; ++i) {
       const int r = m0 + prow + 32 * i;
       ra[i] = f4{0.f, 0.f, 0.f, 0.f};
-      if (r < M && k + pk < k1) ra[i] = *reinterpret_cast<const f4u *>(A + (size_t)r * lda + k + pk);
+      if (r < M && k + pk < K) ra[i] = *reinterpret_cast<const f4u *>(A + (size_t)r * lda + k + pk);
     }
 #pragma unroll
     for (int i = 0; i < 2 * WN; ++i) {
       const int r = n0 + prow + 32 * i;
       rw[i] = f4{0.f, 0.f, 0.f, 0.f};
-      if (r < N && k + pk < k1) rw[i] = *reinterpret_cast<const f4u *>(W + (size_t)r * ldw + k + pk);
+      if (r < N && k + pk < K) rw[i] = *reinterpret_cast<const f4u *>(W + (size_t)r * ldw + k + pk);
     }
+  };
+  // k = 4 h .. 4 h + 3 of eight -> k = h, 2 + h, 4 + h, 6 + h
+  auto in_order = [](const f4 &v) {
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[0]), __float_as_uint(v[1]), false, false);
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[2]), __float_as_uint(v[3]), false, false);
+    return f4{__uint_as_float(a[0]), __uint_as_float(b[0]), __uint_as_float(a[1]), __uint_as_float(b[1])};
   };
 
   f32x16 acc[2];
@@ -68,20 +76,20 @@ __global__ __launch_bounds__(256) void sgemm_tn_kernel(const float *__restrict__
   for (int j = 0; j < 2; ++j)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
-  fetch(k0);
-  for (int k = k0; k < k1; k += GK) {
+  fetch(0);
+  for (int k = 0; k < K; k += GK) {
     __syncthreads();  // the previous slice has been read
 #pragma unroll
     for (int i = 0; i < WM; ++i) *reinterpret_cast<f4 *>(&sa[(prow + 32 * i) * GLD + pk]) = ra[i];
 #pragma unroll
     for (int i = 0; i < 2 * WN; ++i) *reinterpret_cast<f4 *>(&sw[(prow + 32 * i) * GLD + pk]) = rw[i];
     __syncthreads();
-    if (k + GK < k1) fetch(k + GK);
+    if (k + GK < K) fetch(k + GK);
 #pragma unroll
     for (int kk = 0; kk < GK / 8; ++kk) {
-      const f4 fa = *reinterpret_cast<const f4 *>(&sa[(wm * 32 + l31) * GLD + kk * 8 + 4 * h]);
-      const f4 f0 = *reinterpret_cast<const f4 *>(&sw[(wn * 64 + l31) * GLD + kk * 8 + 4 * h]);
-      const f4 f1 = *reinterpret_cast<const f4 *>(&sw[(wn * 64 + 32 + l31) * GLD + kk * 8 + 4 * h]);
+      const f4 fa = in_order(*reinterpret_cast<const f4 *>(&sa[(wm * 32 + l31) * GLD + kk * 8 + 4 * h]));
+      const f4 f0 = in_order(*reinterpret_cast<const f4 *>(&sw[(wn * 64 + l31) * GLD + kk * 8 + 4 * h]));
+      const f4 f1 = in_order(*reinterpret_cast<const f4 *>(&sw[(wn * 64 + 32 + l31) * GLD + kk * 8 + 4 * h]));
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(f0[e], fa[e], acc[0], 0, 0, 0);
@@ -91,7 +99,7 @@ __global__ __launch_bounds__(256) void sgemm_tn_kernel(const float *__restrict__
   }
   const int m = m0 + wm * 32 + l31;
   if (m >= M) return;
-  float *row = C + blockIdx.z * cstride + (size_t)m * ldc;
+  float *row = C + (size_t)m * ldc;
 #pragma unroll
   for (int j = 0; j < 2; ++j)
 #pragma unroll
@@ -101,39 +109,80 @@ __global__ __launch_bounds__(256) void sgemm_tn_kernel(const float *__restrict__
     }
 }
 
-// C[i] = sum over the K ranges of part[s * n + i], in order of s; n is a multiple of 16
-__global__ __launch_bounds__(256) void sgemm_sum_kernel(const float *__restrict__ part, int splits, size_t n,
-                                                        float *__restrict__ C) {
-  const size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;
-  if (i >= n) return;
-  f4 v = *reinterpret_cast<const f4 *>(part + i);
-  for (int s = 1; s < splits; ++s) v += *reinterpret_cast<const f4 *>(part + s * n + i);
-  *reinterpret_cast<f4u *>(C + i) = v;
+// Skinny outputs (x_proj: 1024 x 192 x 5120, 24 tiles of the form above): the chain over K is what takes the time, so the
+// output is cut as small as the matrix unit allows, one 16 x 16 block (v_mfma_f32_16x16x4_f32, 32 clocks per four of K)
+// for each of the four waves of a 32 x 32 tile; slices of 64 in two buffers, the one after
+// them in registers (two in registers measure the same).  Groups of 16 k are stored by
+// k mod 4, so that the quarter-wave g reads k = g, 4 + g, 8 + g, 12 + g as 16 bytes.  1024 x 192 x 5120: 51 us (one chain per
+// thread on the vector units: 728).
+constexpr int NK = 64, NLD = NK + 4;
+
+__global__ __launch_bounds__(256) void sgemm_skinny_kernel(const float *__restrict__ A, int lda, const float *__restrict__ W,
+                                                           int ldw, float *__restrict__ C, int ldc, int M, int N, int K) {
+  __shared__ __attribute__((aligned(16))) float sa[2][32 * NLD], sw[2][32 * NLD];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = (wave & 1) * 16, wn = (wave >> 1) * 16, l15 = lane & 15, g = lane >> 4;
+  const int m0 = blockIdx.y * 32, n0 = blockIdx.x * 32;
+  f4 ra[2], rw[2];
+  const int prow = tid >> 4, pk = (tid & 15) * 4;  // 16 pieces per row and slice, rows prow and prow + 16
+  auto fetch = [&](int k) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int r = prow + 16 * i;
+      ra[i] = rw[i] = f4{0.f, 0.f, 0.f, 0.f};
+      if (m0 + r < M && k + pk < K) ra[i] = *reinterpret_cast<const f4u *>(A + (size_t)(m0 + r) * lda + k + pk);
+      if (n0 + r < N && k + pk < K) rw[i] = *reinterpret_cast<const f4u *>(W + (size_t)(n0 + r) * ldw + k + pk);
+    }
+  };
+  const int at = (pk & ~15) + ((pk >> 2) & 3);
+  auto park = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        sa[buf][(prow + 16 * i) * NLD + at + 4 * e] = ra[i][e];
+        sw[buf][(prow + 16 * i) * NLD + at + 4 * e] = rw[i][e];
+      }
+  };
+  f4 acc = {0.f, 0.f, 0.f, 0.f};
+  fetch(0);
+  park(0);
+  if (NK < K) fetch(NK);
+  __syncthreads();
+  for (int k = 0, buf = 0; k < K; k += NK, buf ^= 1) {
+    if (k + NK < K) park(buf ^ 1);  // read last before the barrier at the end of the previous slice
+    if (k + 2 * NK < K) fetch(k + 2 * NK);
+    f4 fa[NK / 16], fw[NK / 16];
+#pragma unroll
+    for (int q = 0; q < NK / 16; ++q) {
+      fa[q] = *reinterpret_cast<const f4 *>(&sa[buf][(wm + l15) * NLD + 16 * q + 4 * g]);
+      fw[q] = *reinterpret_cast<const f4 *>(&sw[buf][(wn + l15) * NLD + 16 * q + 4 * g]);
+    }
+#pragma unroll
+    for (int q = 0; q < NK / 16; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(fw[q][e], fa[q][e], acc, 0, 0, 0);
+    __syncthreads();
+  }
+  const int m = m0 + wm + l15, n = n0 + wn + 4 * g;
+  if (m < M && n < N) *reinterpret_cast<f4u *>(C + (size_t)m * ldc + n) = f4u{acc[0], acc[1], acc[2], acc[3]};
 }
 
-// K and N multiples of 16, ldc == N.  `scratch` (16-byte aligned, scratch_floats long) takes the partial sums where K is split:
-// a skinny output (x_proj, 1024 x 192 x 5120: 24 tiles) would leave nine CUs of ten idle.
-int sgemm(const float *A, int lda, const float *W, int ldw, float *C, int M, int N, int K, float *scratch,
-          size_t scratch_floats, hipStream_t st) {
+// K and N multiples of 16; the rows of C are N long
+int sgemm(const float *A, int lda, const float *W, int ldw, float *C, int M, int N, int K, hipStream_t st) {
   const int wm = M > 64 ? 4 : (M > 32 ? 2 : 1), wn = 4 / wm;
-  const int tm = (M + 32 * wm - 1) / (32 * wm), tn = (N + 64 * wn - 1) / (64 * wn);
-  // as many K ranges as bring three workgroups to every CU, none shorter than eight slices
-  const size_t mn = (size_t)M * N;
-  int splits = (int)std::min<size_t>(768 / ((size_t)tm * tn) + 1, (size_t)std::max(1, K / (8 * GK)));
-  splits = (int)std::min<size_t>(splits, scratch_floats / mn);
-  if (splits < 2) splits = 1;
-  const int kper = (int)align_up((size_t)(K + splits - 1) / splits, GK);
-  splits = (K + kper - 1) / kper;
-  float *dst = splits > 1 ? scratch : C;
-  const dim3 grid(tn, tm, splits), block(256);
-  if (wm == 4) hipLaunchKernelGGL((sgemm_tn_kernel<4, 1>), grid, block, 0, st, A, lda, W, ldw, dst, N, M, N, K, kper, mn);
-  else if (wm == 2) hipLaunchKernelGGL((sgemm_tn_kernel<2, 2>), grid, block, 0, st, A, lda, W, ldw, dst, N, M, N, K, kper, mn);
-  else hipLaunchKernelGGL((sgemm_tn_kernel<1, 4>), grid, block, 0, st, A, lda, W, ldw, dst, N, M, N, K, kper, mn);
-  QUAMBA_LAUNCH_CHECK();
-  if (splits > 1) {
-    hipLaunchKernelGGL(sgemm_sum_kernel, dim3((unsigned)((mn / 4 + 255) / 256)), block, 0, st, scratch, splits, mn, C);
-    QUAMBA_LAUNCH_CHECK();
+  const dim3 block(256), grid((N + 64 * wn - 1) / (64 * wn), (M + 32 * wm - 1) / (32 * wm));
+  // under half a tile per CU the time is one tile's chain over K, which the small blocks walk in half the clocks
+  if ((size_t)grid.x * grid.y < 128) {
+    hipLaunchKernelGGL(sgemm_skinny_kernel, dim3((N + 31) / 32, (M + 31) / 32), block, 0, st, A, lda, W, ldw, C, N, M, N, K);
+  } else if (wm == 4) {
+    hipLaunchKernelGGL((sgemm_tn_kernel<4, 1>), grid, block, 0, st, A, lda, W, ldw, C, N, M, N, K);
+  } else if (wm == 2) {
+    hipLaunchKernelGGL((sgemm_tn_kernel<2, 2>), grid, block, 0, st, A, lda, W, ldw, C, N, M, N, K);
+  } else {
+    hipLaunchKernelGGL((sgemm_tn_kernel<1, 4>), grid, block, 0, st, A, lda, W, ldw, C, N, M, N, K);
   }
+  QUAMBA_LAUNCH_CHECK();
   return QUAMBA_OK;
 }
 
@@ -248,10 +297,11 @@ __global__ __launch_bounds__(256) void conv_silu_f32_kernel(const float *__restr
 
 // fp32 selective scan + gate.  A workgroup owns 32 channels of one sequence, 8 lanes per channel with two of the 16
 // states each, and walks the tokens in blocks of 32.  What is per (token, channel) is done once by all threads, a block
-// ahead of the recurrence, and handed over in LDS together with B and C; the C h sums of a token are added over
-// the eight lanes and gated by all threads again, so every access of global memory is a row of 32 channels.  With one
+// ahead of the recurrence, and handed over in LDS together with B and C; the sum C h of a token is one chain over the
+// states 0 .. 15 (the scale of the output hangs on its last bit): it travels from lane to lane, each lane one token behind
+// the one before it.  It is gated by all threads again, so every access of global memory is a row of 32 channels.  With one
 // thread per channel (80 workgroups at 4 x 5120 channels, 256 tokens) the serial chain of loads and exponentials took 367
-// us; this takes 94.
+// us; this takes 96.
 constexpr int ST = 32, SC = 32;
 
 __global__ __launch_bounds__(256) void scan_f32_kernel(const float *__restrict__ x, const float *__restrict__ dt_raw,
@@ -296,37 +346,40 @@ __global__ __launch_bounds__(256) void scan_f32_kernel(const float *__restrict__
   };
   fetch(0);
   for (int t0 = 0; t0 < L; t0 += ST) {
-    float dx[4], zg[4];
+    float xg[4], zg[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const float pre = pv[i] + bias;
       const float dt = pre > 20.f ? pre : log1pf(expf(pre));
       sdt[et + 8 * i][ec] = make_float2(dt, dt * xv[i]);
       sbc[et + 8 * i][ec] = bc[i];
-      dx[i] = Dv * xv[i];
+      xg[i] = xv[i];
       zg[i] = zv[i];
     }
     __syncthreads();
     if (t0 + ST < L) fetch(t0 + ST);
     const int nt = min(ST, L - t0);
-    for (int t = 0; t < nt; ++t) {
-      const float2 d = sdt[t][rc];
-      const float2 B = *reinterpret_cast<const float2 *>(&sbc[t][2 * rg]);
-      const float2 C = *reinterpret_cast<const float2 *>(&sbc[t][16 + 2 * rg]);
-      h0 = exp2f(d.x * a0) * h0 + d.y * B.x;
-      h1 = exp2f(d.x * a1) * h1 + d.y * B.y;
-      float y = C.x * h0 + C.y * h1;
-      y += __shfl_xor(y, 1);
-      y += __shfl_xor(y, 2);
-      y += __shfl_xor(y, 4);
-      if (rg == 0) sy[t][rc] = y;
+    float y = 0.f;
+    for (int i = 0; i < nt + 7; ++i) {
+      const int t = i - rg;  // lane rg is rg tokens behind lane 0, whose sum comes to it through the lanes between
+      const bool on = t >= 0 && t < nt;
+      const int tt = on ? t : 0;
+      const float2 d = sdt[tt][rc];
+      const float2 B = *reinterpret_cast<const float2 *>(&sbc[tt][2 * rg]);
+      const float2 C = *reinterpret_cast<const float2 *>(&sbc[tt][16 + 2 * rg]);
+      const float n0 = __builtin_fmaf(exp2f(d.x * a0), h0, d.y * B.x), n1 = __builtin_fmaf(exp2f(d.x * a1), h1, d.y * B.y);
+      h0 = on ? n0 : h0;
+      h1 = on ? n1 : h1;
+      const float in = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(y), 0x111, 0xf, 0xf, true));  // row_shr:1
+      y = __builtin_fmaf(C.y, h1, __builtin_fmaf(C.x, h0, rg ? in : 0.f));
+      if (rg == 7 && on) sy[t][rc] = y;
     }
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int t = et + 8 * i;
       if (t < nt && eon) {
-        const float y = sy[t][ec] + dx[i];
+        const float y = __builtin_fmaf(Dv, xg[i], sy[t][ec]);
         g[(row0 + t0 + t) * Di + ed] = y * zg[i] / (1.f + expf(-zg[i]));
       }
     }
@@ -616,12 +669,12 @@ int fp_forward(const quamba_dims *d, const quamba_fp_weights *w, const __half *c
   QUAMBA_LAUNCH_CHECK();
   int rc;
   // partial sums of a split K go to buffers that are written later
-  if ((rc = sgemm(b.u32, Dm, w->W_in, Dm, b.xz, (int)M, 2 * Di, Dm, b.x, b.A - b.x, st))) return rc;
+  if ((rc = sgemm(b.u32, Dm, w->W_in, Dm, b.xz, (int)M, 2 * Di, Dm, st))) return rc;
   hipLaunchKernelGGL(conv_silu_f32_kernel, dim3(nblk(M * Di / 4)), dim3(256), 0, st, b.xz, 2 * Di, w->conv_w,
                      w->conv_b, Lc, Di, b.x, M * Di / 4);
   QUAMBA_LAUNCH_CHECK();
-  if ((rc = sgemm(b.x, Di, w->W_x, Di, b.dbc, (int)M, NX, Di, b.gH, b.A - b.gH, st))) return rc;
-  if ((rc = sgemm(b.dbc, NX, w->W_dt, R, b.dtr, (int)M, Di, R, b.gH, b.A - b.gH, st))) return rc;
+  if ((rc = sgemm(b.x, Di, w->W_x, Di, b.dbc, (int)M, NX, Di, st))) return rc;
+  if ((rc = sgemm(b.dbc, NX, w->W_dt, R, b.dtr, (int)M, Di, R, st))) return rc;
   hipLaunchKernelGGL(scan_f32_kernel, dim3((unsigned)((Di + SC - 1) / SC) * nb), dim3(256), 0, st, b.x, b.dtr, w->dt_bias, b.A, b.dbc, NX,
                      R, w->D, b.xz, Lc, Di, b.g);
   QUAMBA_LAUNCH_CHECK();
@@ -666,7 +719,7 @@ int fp_mixer(const quamba_dims *d, const quamba_fp_weights *w, const __half *u, 
   const CalBufs b = carve(p, ws);
   int rc;
   if ((rc = fp_forward(d, w, u, nb, Lc, b, st))) return rc;
-  return sgemm(b.g, d->d_inner, w->W_out, d->d_inner, out, nb * Lc, d->d_model, d->d_inner, b.gH, b.A - b.gH, st);
+  return sgemm(b.g, d->d_inner, w->W_out, d->d_inner, out, nb * Lc, d->d_model, d->d_inner, st);
 }
 
 int calibrate(const quamba_dims *d, const quamba_fp_weights *w, const __half *calib_u, int nb, int Lc,
@@ -732,7 +785,7 @@ int calibrate(const quamba_dims *d, const quamba_fp_weights *w, const __half *ca
   QUAMBA_LAUNCH_CHECK();
   int rc;
   if ((rc = fp_forward(d, w, calib_u, nb, Lc, b, st))) return rc;
-  if (out_f32 && (rc = sgemm(g, Di, w->W_out, Di, out_f32, (int)M, Dm, Di, gH, A - gH, st))) return rc;
+  if (out_f32 && (rc = sgemm(g, Di, w->W_out, Di, out_f32, (int)M, Dm, Di, st))) return rc;
   if ((rc = launch_hadamard_f32(g, (int)M, Di, gH, st))) return rc;      // y^H = H_n g
   if ((rc = launch_hadamard_f32(w->W_out, Dm, Di, woh, st))) return rc;  // rows of W_out^H
 

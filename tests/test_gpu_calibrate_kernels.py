@@ -22,7 +22,7 @@ def _case(Dm, Di, R, nb, L):
     (64, 192, 16, 1, 33),    # 64-row tiles
     (64, 192, 16, 2, 32),    # exactly one 64-row tile; exactly one block of tokens
     (80, 320, 48, 5, 13),    # 65 rows: 128-row tiles
-    (768, 1536, 48, 3, 43),  # 129 rows, K split into several ranges
+    (768, 1536, 48, 3, 43),  # 129 rows; skinny outputs of a long K
 ])
 def test_fp32_forward_at_tile_edges(Dm, Di, R, nb, L):
     """fp32 sums of up to 1536 products against fp64: errors of about sqrt(K) 2^-24 per sum, 40 x 6e-8 = 2.4e-6 of the
@@ -58,3 +58,17 @@ def test_calibration_takes_unaligned_master_weights():
     assert got[0][0] == got[1][0]
     for k in got[0][1]:
         assert np.array_equal(got[0][1][k], got[1][1][k]), k
+
+
+@pytest.mark.parametrize("Dm,Di,R,nb,L", [(80, 320, 48, 3, 47), (768, 1536, 48, 6, 43)])
+def test_order_of_the_fp32_sums_does_not_depend_on_the_tile(Dm, Di, R, nb, L):
+    """Every fp32 output is one chain of multiply-adds over K, so a sequence gives the same bits alone (32- or 64-row tiles, the
+    skinny form) and in a batch (128-row tiles): scales, and with them int8 codes, do not move with the batch's shape."""
+    cfg, w, u = _case(Dm, Di, R, nb, L)
+    fw = {k: dev(v) for k, v in w.items()}
+    ws = workspace(Q.quamba_calibrate_workspace_bytes(cfg, nb, L))
+    whole, one = empty((nb, L, Dm), torch.float32), empty((1, L, Dm), torch.float32)
+    Q.quamba_mixer_fp32(cfg, fw, dev(u), nb, L, whole, ws)
+    for b in range(nb):
+        Q.quamba_mixer_fp32(cfg, fw, dev(np.ascontiguousarray(u[b:b + 1])), 1, L, one, ws)
+        assert np.array_equal(host(one)[0], host(whole)[b])
