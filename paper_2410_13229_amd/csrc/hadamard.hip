@@ -326,7 +326,7 @@ __global__ __launch_bounds__(threads_for(K << LOGM)) void hadamard_out_proj_kern
     __half *__restrict__ out, int8_t *__restrict__ codes_out) {
   constexpr int n = K << LOGM;
   constexpr int HT = threads_for(n);
-  static_assert(HT == n / 16, "one item per thread");
+  static_assert(HT >= n / 16, "one item per thread");
   extern __shared__ __attribute__((aligned(16))) float row[];
   __shared__ int red[HT / 64][OC];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -343,18 +343,22 @@ __global__ __launch_bounds__(threads_for(K << LOGM)) void hadamard_out_proj_kern
     cg = bid / M;
   }
   const int n0 = cg * OC;
+  // n / 16 need not fill the last wave (1536 = 96 items, 2560 = 160): its other threads repeat the last item with zero codes
+  const bool live = HT == n / 16 || tid < n / 16;
+  const int item = live ? tid : n / 16 - 1;
   v4i wv[OC];
 #pragma unroll
   for (int j = 0; j < OC; ++j)  // the clamp only bounds the address of a ragged last group
-    wv[j] = *reinterpret_cast<const v4i *>(W + (size_t)min(n0 + j, Dm - 1) * n + (size_t)tid * 16);
+    wv[j] = *reinterpret_cast<const v4i *>(W + (size_t)min(n0 + j, Dm - 1) * n + (size_t)item * 16);
   transform_row<K, LOGM, __half, false>(g + (size_t)r * n, row);
   float v[16];
-  last_pass(row, tid, v);
+  last_pass(row, item, v);
   v4i c;
 #pragma unroll
   for (int q = 0; q < 4; ++q)
     c[q] = static_cast<int>(pack_q8x4(v[4 * q] * inv_s, v[4 * q + 1] * inv_s, v[4 * q + 2] * inv_s, v[4 * q + 3] * inv_s));
-  if (cg == 0 && codes_out) *reinterpret_cast<v4i *>(codes_out + (size_t)r * n + (size_t)tid * 16) = c;
+  if (!live) c = v4i{0, 0, 0, 0};
+  if (cg == 0 && codes_out && live) *reinterpret_cast<v4i *>(codes_out + (size_t)r * n + (size_t)tid * 16) = c;
 #pragma unroll
   for (int j = 0; j < OC; ++j) {
     int acc = 0;
@@ -482,11 +486,12 @@ int run_out_proj(const __half *g, int M, float inv_s, const int8_t *W, int Dm, f
 }
 }  // namespace
 
-// orders for which one thread per 16 elements is a whole number of waves and the row fits 64 KB of LDS
+// orders for which one thread per 16 elements is one and a half waves or more and the row fits 64 KB of LDS
+// (1536, the 130M layer's width: with one sequence the step is bound by its launches, 22.9 -> 17.9 us with one less)
 bool hadamard_fuses_out_proj(int n, int Dm) {
   int k = 0, m = 0;
   if (Dm < 1 || !hadamard_factor(n, &k, &m)) return false;
-  return (k == 1 && m >= 10 && m <= 13) || (k == 12 && m >= 8 && m <= 10) || (k == 20 && m >= 8 && m <= 9);
+  return (k == 1 && m >= 10 && m <= 13) || (k == 12 && m >= 7 && m <= 10) || (k == 20 && m >= 7 && m <= 9);
 }
 
 // M rows (a few: with four the separate kernels are faster, and two rows per workgroup, the transforms one
@@ -500,8 +505,8 @@ int launch_hadamard_out_proj(const __half *g, int M, int n, float inv_s_y, const
 #define QUAMBA_CASE(KK, LM) \
   if (k == KK && m == LM) return run_out_proj<KK, LM>(g, M, inv_s_y, W, Dm, m_out, out, codes, st);
   QUAMBA_CASE(1, 10) QUAMBA_CASE(1, 11) QUAMBA_CASE(1, 12) QUAMBA_CASE(1, 13)
-  QUAMBA_CASE(12, 8) QUAMBA_CASE(12, 9) QUAMBA_CASE(12, 10)
-  QUAMBA_CASE(20, 8) QUAMBA_CASE(20, 9)
+  QUAMBA_CASE(12, 7) QUAMBA_CASE(12, 8) QUAMBA_CASE(12, 9) QUAMBA_CASE(12, 10)
+  QUAMBA_CASE(20, 7) QUAMBA_CASE(20, 8) QUAMBA_CASE(20, 9)
 #undef QUAMBA_CASE
   return fail(QUAMBA_EUNSUPPORTED, "hadamard + out_proj: n=%d", n);
 }
