@@ -183,7 +183,8 @@ struct DecodeInArgs {
   __half *res_out;
   const __half *norm_w;
   float eps, inv_s_u;
-  const int8_t *u_q;
+  const int8_t *u_q;   // codes of the block input, or
+  const __half *u;     // the block input itself, quantized in the kernel
   const int8_t *W_in;
   int Dm, Di, M;
   float m_in_x, m_in_z;

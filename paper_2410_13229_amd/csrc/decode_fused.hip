@@ -46,6 +46,23 @@ __global__ __launch_bounds__(256) void decode_in_kernel(DecodeInArgs p) {
         if (m < M) v = *reinterpret_cast<const v4i *>(p.u_q + (size_t)m * Dm + ch * 16);
         *reinterpret_cast<v4i *>(sA + (size_t)m * Dm + ch * 16) = v;
       }
+  } else if (p.u) {  // quantize_f16's arithmetic, M rows in every workgroup
+    for (int g = tid; g < MB * groups; g += 256) {
+      const int m = g / groups;
+      uint2 c = make_uint2(0u, 0u);
+      if (m < M) {
+        union {
+          uint4 u;
+          __half h[8];
+        } in;
+        in.u = *reinterpret_cast<const uint4 *>(p.u + (size_t)g * 8);
+        float v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = __half2float(in.h[e]) * p.inv_s_u;
+        c = make_uint2(pack_q8x4(v[0], v[1], v[2], v[3]), pack_q8x4(v[4], v[5], v[6], v[7]));
+      }
+      *reinterpret_cast<uint2 *>(sA + (size_t)g * 8) = c;
+    }
   } else {
     // One sweep: the fp16 sums s = fp16(out + res) stay in registers (8 halves per 16-byte word) between
     // the reduction and the scaling; a thread owns at most SW words per row (d_model <= 4096 with 2).
