@@ -330,8 +330,10 @@ int run_mixer(const quamba_dims *d, const quamba_qweights *qw, const quamba_scal
     } else {
       if (next_qw) {  // a stack of blocks: warm the cache with the weights that come next
         a.warm_ptr[0] = qw->W_outH; a.warm_bytes[0] = (size_t)Dm * Di;
-        a.warm_ptr[1] = next_qw->W_in; a.warm_bytes[1] = (size_t)2 * Di * Dm;
-        a.warm_ptr[2] = next_qw->W_x; a.warm_bytes[2] = (size_t)NX * Di;
+        if (next_qw != qw) {
+          a.warm_ptr[1] = next_qw->W_in; a.warm_bytes[1] = (size_t)2 * Di * Dm;
+          a.warm_ptr[2] = next_qw->W_x; a.warm_bytes[2] = (size_t)NX * Di;
+        }
       }
       QUAMBA_TRY(launch_scan_prefill(a, base + p.scan, p.total - p.scan, st));
     }
