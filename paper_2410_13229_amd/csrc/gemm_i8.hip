@@ -840,6 +840,7 @@ GemmChoice choose_gemm(int M, int N, int K, const void *ws, size_t ws_bytes, boo
   //       6.6 against 8.0; two K groups with a ring of 4: 8.8; at K = 8192 the split form stays ahead, 11.0 against 11.3);
   //       also the wide output of a step with at most 32 sequences, where one row of tiles covers them
   //       (4 to 32 x 10240 x 2560: 5.9-6.2 against 7.3-7.5 us for the 64 x 64 form)
+  //   14 = 8 with 128 x 96 tiles: one round of CUs for outputs too small for 128 x 160 tiles
   //   11 = dma 64x64, two K groups of 4 waves, 256-byte slices, ring of 3: the same job when K is a
   //       multiple of 256; half as many workgroups re-read the activation rows (64 x 10240 x 2560:
   //       7.5 against 8.0 us, 64 x 16384 x 4096: 13.6 against 14.6 us)
@@ -913,7 +914,13 @@ GemmChoice choose_gemm(int M, int N, int K, const void *ws, size_t ws_bytes, boo
   if (M > 64 && (K % 256) == 0 && K <= 8192 && (kind == 5 || kind == 9 || kind == 12) && tiles64 > 128 && tiles64 <= 256 &&
       (long)((M + 31) / 32) * ((N + 31) / 32) > (N <= 512 ? 400 : 520))
     kind = 11;
-  if ((forced_kind == 12 || forced_kind == 13) && (K % 256) == 0) kind = forced_kind;
+  // 192 to 256 tiles of 128 x 96 with two K groups of 4 waves, one round, instead of 64 x 64 tiles: half the LDS reads per
+  // product, worth it where K is deep (x 2560 x 5120: 900 rows 27.7 -> 26.4 us, 1024 28.3 -> 26.5, 1100 30.4 -> 26.7;
+  // 640 x 4096 x 8192 40.5 -> 35.6; but 256 x 10240 x 2560 14.9 -> 15.9, 1024 x 3072 x 768 7.6 -> 8.9, and with 162 tiles,
+  // 768 x 2560 x 5120, 19.4 -> 25.6)
+  const long tiles_96 = (long)((M + 127) / 128) * ((N + 95) / 96);
+  if ((K % 256) == 0 && K >= 4096 && K <= 8192 && N > 512 && (kind == 5 || kind == 9) && tiles_96 >= 192 && tiles_96 <= 256) kind = 14;
+  if (forced_kind >= 12 && forced_kind <= 14 && (K % 256) == 0) kind = forced_kind;
   if (forced_kind >= 0 && forced_kind <= 11 &&
       (forced_kind < 2 || (forced_kind == 3 && k64) || (forced_kind != 3 && k128)) &&
       ((forced_kind != 8 && forced_kind != 9 && forced_kind != 11) || (K % 256) == 0))  // their slices are 256 bytes
@@ -921,7 +928,7 @@ GemmChoice choose_gemm(int M, int N, int K, const void *ws, size_t ws_bytes, boo
 
   // split K when the output has too few tiles to fill 256 CUs and K is deep
   int splits = 1;
-  const int slice = (kind == 8 || kind == 9 || kind == 11 || kind == 12 || kind == 13) ? 256 : ((kind == 2 || kind >= 4) ? 128 : 64);
+  const int slice = (kind == 8 || kind == 9 || kind == 11 || kind >= 12) ? 256 : ((kind == 2 || kind >= 4) ? 128 : 64);
   const int nslices = (K + slice - 1) / slice;
   if ((kind == 0 || kind == 3 || kind == 5 || kind == 9) && ws != nullptr) {
     const int tiles = ((M + 63) / 64) * ((N + 63) / 64);
@@ -1008,6 +1015,7 @@ int launch_gemm_i8(const int8_t *A, int lda, const int8_t *Wt, int ldw, int M, i
       rc = conv ? run_dma<32, 32, 1, 1, 3, 256, 2, 4, false, true>(A, lda, Wt, ldw, M, N, K, epi, splits, ks, st)
                 : run_dma<32, 32, 1, 1, 3, 256, 2, 4>(A, lda, Wt, ldw, M, N, K, epi, splits, ks, st);
       break;
+    case 14: rc = run_dma<128, 96, 4, 1, 2, 256, 2, 2>(A, lda, Wt, ldw, M, N, K, epi, splits, ks, st); break;
     default: rc = run_reg<128, 128, 2, 2>(A, lda, Wt, ldw, M, N, K, epi, splits, ks, st); break;
   }
   if (rc != QUAMBA_OK || splits == 1 || epi.defer_reduce) return rc;
