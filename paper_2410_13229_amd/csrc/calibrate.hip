@@ -637,7 +637,9 @@ CalPlan cal_plan(const quamba_dims *d, int nb, int Lc) {
   p.woh = take(Dm * Di * 4);
   p.a = take(Di * d->d_state * 4);
   p.slots = take(32 * 4);
-  p.hist = take(4 * 256 * 8);
+  // four histograms of 2 KB: the last three lie in the area of the clip search, which only the other rule for x uses
+  static_assert(CLIP_WS_BYTES >= 3 * 256 * 8, "the histograms fit");
+  p.hist = take(256 * 8);
   p.clip = take(CLIP_WS_BYTES);
   p.total = off;
   return p;

@@ -1,0 +1,16 @@
+"""Sizes and kernel choices that the library decides on the host: no GPU."""
+import pytest
+
+import paper_2410_13229_amd as Q
+import workloads as W
+
+
+@pytest.mark.parametrize("Dm,Di,R,nb,L", [(16, 16, 16, 1, 1), (80, 320, 48, 3, 19), (2560, 5120, 160, 4, 256)])
+def test_calibration_takes_a_workspace_of_its_buffers_alone(Dm, Di, R, nb, L):
+    """Input, x_pre | z, x, dt_low | B | C, dt, g and H g over the batch, the folded weight, A, 32 slots, one histogram and
+    the clip search's area: a workspace that a program allocated once for a layer and batch stays large enough."""
+    cfg = W.tiny_config(name="ws", d_model=Dm, d_inner=Di, dt_rank=R, config_id=94)
+    M = nb * L
+    words = [M * Dm, M * 2 * Di, M * Di, M * (R + 32), M * Di, M * Di, M * Di, Dm * Di, Di * 16, 32]
+    want = sum((4 * n + 255) // 256 * 256 for n in words) + 256 * 8 + (Q.quamba_clip_search_workspace_bytes() + 255) // 256 * 256
+    assert Q.quamba_calibrate_workspace_bytes(cfg, nb, L) <= want
