@@ -208,14 +208,40 @@ __global__ __launch_bounds__(256) void i8_to_bf16_kernel(const int8_t *__restric
   out[i] = static_cast<uint16_t>(__float_as_uint(static_cast<float>(q[(size_t)n * K + k])) >> 16);  // |q| <= 128: exact in 8 bits
 }
 
+// row tiles per wave, workgroups of rows, K ranges and their depth, column tiles per wave
+struct XfmtPlan {
+  int rt, row_blocks, splits, kc, ntw;
+};
+
+XfmtPlan plan_xfmt(int M, int N, int K, const void *ws, size_t ws_bytes) {
+  XfmtPlan p{};
+  // K ranges: enough workgroups for the chip, ranges whole multiples of 32, at most 8 and at least 128 deep
+  // many rows: two row tiles per wave halve the weight traffic (every row block streams all of W)
+  p.rt = M >= 4096 ? 2 : 1;
+  p.row_blocks = (M + 64 * p.rt - 1) / (64 * p.rt);
+  p.splits = 1;
+  if (ws && aligned(ws, 256)) {
+    p.splits = std::min(8, std::max(1, 256 / p.row_blocks));
+    while (p.splits > 1 && ((K / 32) / p.splits < 4 || (size_t)p.splits * M * N * sizeof(float) > ws_bytes)) --p.splits;
+  }
+  p.kc = ((K / 32 + p.splits - 1) / p.splits) * 32;
+  p.splits = (K + p.kc - 1) / p.kc;
+  // Few workgroups: one column tile per wave and the column groups spread over grid.z.  From 128 to 152 workgroups (961 to 1216
+  // rows) that pays for deep K and at least three column groups, E4M3: 1024 x 192 x 5120 16.3 -> 14.5 us, 1216 rows 18.8 ->
+  // 15.6, 1216 x 288 x 8192 33.1 -> 26.2, 1216 x 192 x 4096 15.4 -> 13.9.  It loses beyond: 1280 x 288 x 5120 23.7 -> 24.0
+  // (800 workgroups, a round more), 1280 x 288 x 3072 19.1 -> 19.4, 1216 x 80 x 8192 14.4 -> 15.7, and with two row tiles per wave,
+  // whose codes every column group loads and decodes again, 20480 x 288 x 8192 240 -> 351.
+  const int wgs = p.row_blocks * p.splits;
+  const bool spread = wgs < 128 || (p.rt == 1 && wgs <= 152 && N > 128 && K >= 4096);
+  p.ntw = spread ? 1 : (N + 63) / 64;
+  return p;
+}
+
 template <int FMT, int RT>
-int run_xfmt(const uint8_t *x, const uint16_t *Wb, int M, int N, int K, int kc, int splits, float *partial,
+int run_xfmt(const uint8_t *x, const uint16_t *Wb, int M, int N, int K, const XfmtPlan &p, float *partial,
              const XfmtEpi &epi, hipStream_t st) {
-  // few workgroups: one column tile per wave and the column groups spread over grid.z (1024 rows x 192 columns: 128
-  // workgroups left half the CUs idle; with the columns spread the E4M3 prefill takes 164.3 us instead of 171.1)
-  const int row_blocks = (M + 64 * RT - 1) / (64 * RT);
-  const int ntw = (row_blocks * splits <= 160) ? 1 : (N + 63) / 64;
-  const dim3 grid((unsigned)row_blocks, (unsigned)splits, (unsigned)((N + 64 * ntw - 1) / (64 * ntw)));
+  const int kc = p.kc, ntw = p.ntw;
+  const dim3 grid((unsigned)p.row_blocks, (unsigned)p.splits, (unsigned)((N + 64 * ntw - 1) / (64 * ntw)));
   switch (ntw) {
     case 1: hipLaunchKernelGGL((xfmt_proj_kernel<FMT, 1, RT>), grid, dim3(256), 0, st, x, Wb, M, N, K, kc, partial, epi); break;
     case 2: hipLaunchKernelGGL((xfmt_proj_kernel<FMT, 2, RT>), grid, dim3(256), 0, st, x, Wb, M, N, K, kc, partial, epi); break;
@@ -238,26 +264,17 @@ int launch_xfmt_proj(int format, const uint8_t *x_code, int M, int N, int K, con
     return fail(QUAMBA_EUNSUPPORTED, "xfmt_proj: M=%d N=%d K=%d (N a multiple of 4 up to 320, K a multiple of 32)", M, N, K);
   if (!aligned(x_code, 16) || !aligned(W_bf16, 16) || !aligned(out_q, 4) || (acc_f32 && !aligned(acc_f32, 16)))
     return fail(QUAMBA_EINVAL, "xfmt_proj: pointers must be 16-byte aligned");
-  // K ranges: enough workgroups for the chip, ranges whole multiples of 32, at most 8 and at least 128 deep
-  // many rows: two row tiles per wave halve the weight traffic (every row block streams all of W)
-  const int rt = M >= 4096 ? 2 : 1;
-  const int row_blocks = (M + 64 * rt - 1) / (64 * rt);
-  int splits = 1;
-  if (ws && aligned(ws, 256)) {
-    splits = std::min(8, std::max(1, 256 / row_blocks));
-    while (splits > 1 && ((K / 32) / splits < 4 || (size_t)splits * M * N * sizeof(float) > ws_bytes)) --splits;
-  }
-  const int kc = ((K / 32 + splits - 1) / splits) * 32;
-  splits = (K + kc - 1) / kc;
+  const XfmtPlan plan = plan_xfmt(M, N, K, ws, ws_bytes);
+  const int rt = plan.rt, splits = plan.splits;
   const XfmtEpi epi{out_q, acc_f32, e0, e1, m0, m1, m2};
   float *partial = splits > 1 ? static_cast<float *>(ws) : nullptr;
   int rc;
   if (format == QUAMBA_XFMT_E4M3)
-    rc = rt == 2 ? run_xfmt<QUAMBA_XFMT_E4M3, 2>(x_code, W_bf16, M, N, K, kc, splits, partial, epi, st)
-                 : run_xfmt<QUAMBA_XFMT_E4M3, 1>(x_code, W_bf16, M, N, K, kc, splits, partial, epi, st);
+    rc = rt == 2 ? run_xfmt<QUAMBA_XFMT_E4M3, 2>(x_code, W_bf16, M, N, K, plan, partial, epi, st)
+                 : run_xfmt<QUAMBA_XFMT_E4M3, 1>(x_code, W_bf16, M, N, K, plan, partial, epi, st);
   else
-    rc = rt == 2 ? run_xfmt<QUAMBA_XFMT_LOG2, 2>(x_code, W_bf16, M, N, K, kc, splits, partial, epi, st)
-                 : run_xfmt<QUAMBA_XFMT_LOG2, 1>(x_code, W_bf16, M, N, K, kc, splits, partial, epi, st);
+    rc = rt == 2 ? run_xfmt<QUAMBA_XFMT_LOG2, 2>(x_code, W_bf16, M, N, K, plan, partial, epi, st)
+                 : run_xfmt<QUAMBA_XFMT_LOG2, 1>(x_code, W_bf16, M, N, K, plan, partial, epi, st);
   if (rc != QUAMBA_OK || splits == 1) return rc;
   const size_t groups = (size_t)M * (N / 4);
   hipLaunchKernelGGL(xfmt_reduce_kernel, dim3((unsigned)((groups + 255) / 256)), dim3(256), 0, st, partial, splits, M, N,
@@ -284,3 +301,9 @@ int launch_i8_to_bf16(const int8_t *q, int N, int K, uint16_t *out, hipStream_t 
 }
 
 }  // namespace quamba
+
+extern "C" int quamba_debug_xfmt_column_tiles(int M, int N, int K) {
+  if (M < 1 || N < 4 || N > 320 || N % 4 || K < 32 || K % 32) return 0;
+  const void *ws = reinterpret_cast<const void *>(256);  // as with a workspace of gemm_workspace_bytes
+  return quamba::plan_xfmt(M, N, K, ws, quamba::gemm_workspace_bytes(M, N)).ntw;
+}

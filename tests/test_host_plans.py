@@ -14,3 +14,13 @@ def test_calibration_takes_a_workspace_of_its_buffers_alone(Dm, Di, R, nb, L):
     words = [M * Dm, M * 2 * Di, M * Di, M * (R + 32), M * Di, M * Di, M * Di, Dm * Di, Di * 16, 32]
     want = sum((4 * n + 255) // 256 * 256 for n in words) + 256 * 8 + (Q.quamba_clip_search_workspace_bytes() + 255) // 256 * 256
     assert Q.quamba_calibrate_workspace_bytes(cfg, nb, L) <= want
+
+
+@pytest.mark.parametrize("M,N,K,tiles", [
+    (960, 288, 8192, 1), (961, 192, 4096, 1), (1216, 192, 5120, 1), (1216, 288, 8192, 1), (1217, 288, 5120, 5),
+    (1024, 128, 8192, 2), (1088, 80, 8192, 2), (1216, 288, 3072, 5),   # two column groups, shallow K
+    (16385, 192, 5120, 3), (20480, 288, 8192, 5), (16385, 80, 1536, 2),  # two row tiles per wave
+    (8128, 192, 5120, 3),
+])
+def test_column_groups_of_xfmt_proj_are_spread_where_that_was_measured_to_pay(M, N, K, tiles):
+    assert Q.quamba_debug_xfmt_column_tiles(M, N, K) == tiles
