@@ -609,6 +609,8 @@ int quamba_probe_rate(int probe, int waves_per_simd, int iters, double *instr_pe
  *                                      sequence wherever its layout rules hold, 0 = default (the cheaper of
  *                                      the two by the library's estimate for the shape)
  * Host-only queries of what is chosen for a shape with the full workspace, for tests of the rules:
+ *   quamba_debug_gemm_kind(M, N, K)    configuration of an int8 GEMM as quamba_debug_set_gemm_variant counts
+ *                                      them, before the launcher cuts rows; -1 = few-row streaming kernel, -2 = not served
  *   quamba_debug_xfmt_column_tiles(M, N, K)  x_proj of the 8-bit float formats: column tiles per wave, 1 = the
  *                                      column groups are spread over the grid; 0 = not served
  * ------------------------------------------------------------------------------------- */
@@ -618,6 +620,7 @@ void quamba_debug_set_gemv_max_rows(int v);
 void quamba_debug_set_fuse_dt(int v);
 void quamba_debug_set_fuse_decode(int v);
 void quamba_debug_set_scan_variant(int v);
+int quamba_debug_gemm_kind(int M, int N, int K);
 int quamba_debug_xfmt_column_tiles(int M, int N, int K);
 
 #ifdef __cplusplus

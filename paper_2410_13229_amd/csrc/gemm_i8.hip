@@ -914,12 +914,14 @@ GemmChoice choose_gemm(int M, int N, int K, const void *ws, size_t ws_bytes, boo
   if (M > 64 && (K % 256) == 0 && K <= 8192 && (kind == 5 || kind == 9 || kind == 12) && tiles64 > 128 && tiles64 <= 256 &&
       (long)((M + 31) / 32) * ((N + 31) / 32) > (N <= 512 ? 400 : 520))
     kind = 11;
-  // 192 to 256 tiles of 128 x 96 with two K groups of 4 waves, one round, instead of 64 x 64 tiles: half the LDS reads per
-  // product, worth it where K is deep (x 2560 x 5120: 900 rows 27.7 -> 26.4 us, 1024 28.3 -> 26.5, 1100 30.4 -> 26.7;
-  // 640 x 4096 x 8192 40.5 -> 35.6; but 256 x 10240 x 2560 14.9 -> 15.9, 1024 x 3072 x 768 7.6 -> 8.9, and with 162 tiles,
-  // 768 x 2560 x 5120, 19.4 -> 25.6)
+  // 192 to 256 tiles of 128 x 96 with two K groups of 4 waves, one round, instead of clearly more 64 x 64 tiles than one round
+  // holds (512): half the LDS reads per product, worth it where K is deep (x 2560 x 5120: 897 rows 26.4 -> 24.1 us, 1024
+  // 26.7 -> 25.0, 1152 28.6 -> 25.6; x 4096 x 8192: 513 rows 40.5 -> 32.8, 640 39.3 -> 34.5).  With fewer tiles or shallower
+  // K the 64 x 64 ones stay ahead: 192 x 9216 x 4096 (432 tiles) 15.0 against 19.2, 447 x 4672 x 5632 (511) 21.8 against 25.0,
+  // 130 x 11264 x 5376 (528) 23.6 against 24.6, 448 x 5072 x 4352 (560) 20.4 against 21.5, 1056 x 2048 x 4096 19.5 against 20.4.
   const long tiles_96 = (long)((M + 127) / 128) * ((N + 95) / 96);
-  if ((K % 256) == 0 && K >= 4096 && K <= 8192 && N > 512 && (kind == 5 || kind == 9) && tiles_96 >= 192 && tiles_96 <= 256) kind = 14;
+  if ((K % 256) == 0 && K >= 5120 && K <= 8192 && N > 512 && (kind == 5 || kind == 9) && tiles64 > 560 && tiles_96 >= 192 && tiles_96 <= 256)
+    kind = 14;
   if (forced_kind >= 12 && forced_kind <= 14 && (K % 256) == 0) kind = forced_kind;
   if (forced_kind >= 0 && forced_kind <= 11 &&
       (forced_kind < 2 || (forced_kind == 3 && k64) || (forced_kind != 3 && k128)) &&
@@ -1035,3 +1037,9 @@ int launch_gemm_i8(const int8_t *A, int lda, const int8_t *Wt, int ldw, int M, i
 extern "C" void quamba_debug_set_gemm_variant(int v) { quamba::g_gemm_variant.store(v); }
 extern "C" void quamba_debug_set_gemm_split(int v) { quamba::g_gemm_split.store(v); }
 extern "C" void quamba_debug_set_gemv_max_rows(int v) { quamba::g_gemv_max_rows.store(v < 0 ? 2 : (v < 4 ? v : 4)); }
+extern "C" int quamba_debug_gemm_kind(int M, int N, int K) {
+  if (M < 1 || N < 4 || N % 4 || K < 16 || K % 16) return -2;
+  const void *ws = reinterpret_cast<const void *>(256);  // as with a workspace of gemm_workspace_bytes
+  const quamba::GemmPlan p = quamba::choose_gemm(M, N, K, ws, quamba::gemm_workspace_bytes(M, N));
+  return p.gemv ? -1 : p.kind;
+}

@@ -24,3 +24,14 @@ def test_calibration_takes_a_workspace_of_its_buffers_alone(Dm, Di, R, nb, L):
 ])
 def test_column_groups_of_xfmt_proj_are_spread_where_that_was_measured_to_pay(M, N, K, tiles):
     assert Q.quamba_debug_xfmt_column_tiles(M, N, K) == tiles
+
+
+@pytest.mark.parametrize("M,N,K,taken", [
+    (896, 2560, 5120, False), (897, 2560, 5120, True), (1152, 2560, 5120, True), (1153, 2560, 5120, False),
+    (512, 4096, 8192, False), (513, 4096, 8192, True), (640, 4096, 8192, True), (641, 4096, 8192, False),
+    (1408, 1712, 5632, True), (576, 4096, 4864, False), (1056, 2048, 4096, False), (1088, 2048, 4096, False), (1024, 3072, 768, False),
+    (129, 9216, 4096, False), (160, 9376, 4608, False), (447, 4672, 5632, False), (319, 6416, 7168, False),  # one round of 64 x 64
+    (130, 11264, 5376, False), (448, 5072, 4352, False), (288, 6608, 5120, False),  # little more than one
+])
+def test_128_by_96_tiles_are_taken_where_that_was_measured_to_pay(M, N, K, taken):
+    assert (Q.quamba_debug_gemm_kind(M, N, K) == 14) == taken
