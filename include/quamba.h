@@ -613,6 +613,8 @@ int quamba_probe_rate(int probe, int waves_per_simd, int iters, double *instr_pe
  *                                      them, before the launcher cuts rows; -1 = few-row streaming kernel, -2 = not served
  *   quamba_debug_xfmt_column_tiles(M, N, K)  x_proj of the 8-bit float formats: column tiles per wave, 1 = the
  *                                      column groups are spread over the grid; 0 = not served
+ *   quamba_debug_last_block_reads_ahead(batch, L, d_model, d_inner)  1 = the scan of a stack's last block reads
+ *                                      that block's out_proj weights ahead in a prefill
  * ------------------------------------------------------------------------------------- */
 void quamba_debug_set_gemm_variant(int v);
 void quamba_debug_set_gemm_split(int v);
@@ -622,6 +624,7 @@ void quamba_debug_set_fuse_decode(int v);
 void quamba_debug_set_scan_variant(int v);
 int quamba_debug_gemm_kind(int M, int N, int K);
 int quamba_debug_xfmt_column_tiles(int M, int N, int K);
+int quamba_debug_last_block_reads_ahead(int batch, int L, int d_model, int d_inner);
 
 #ifdef __cplusplus
 }

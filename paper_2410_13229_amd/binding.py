@@ -29,7 +29,7 @@ __all__ = [
     "quamba_xdyn_workspace_bytes", "quamba_mixer_prefill_xdyn", "quamba_mixer_decode_xdyn",
     "quamba_debug_set_gemm_variant", "quamba_debug_set_gemm_split", "quamba_debug_set_gemv_max_rows",
     "quamba_debug_set_fuse_dt", "quamba_debug_set_fuse_decode", "quamba_debug_set_scan_variant",
-    "quamba_debug_gemm_kind", "quamba_debug_xfmt_column_tiles",
+    "quamba_debug_gemm_kind", "quamba_debug_xfmt_column_tiles", "quamba_debug_last_block_reads_ahead",
     "PROBE_FMA_F32", "PROBE_EXP_F32", "PROBE_SCAN_MIX", "PROBE_MFMA_I8", "PROBE_MFMA_I8_RANDOM",
     "PROBE_MUL_F32", "PROBE_FMA_EXP_INDEP", "PROBE_MIX_NOEXP", "PROBE_MIX_GROUPED",
     "quamba_probe_workspace_bytes", "quamba_probe_rate",
@@ -355,6 +355,8 @@ def lib():
     for name in ("quamba_debug_gemm_kind", "quamba_debug_xfmt_column_tiles"):
         getattr(L, name).argtypes = [i, i, i]
         getattr(L, name).restype = i
+    L.quamba_debug_last_block_reads_ahead.argtypes = [i, i, i, i]
+    L.quamba_debug_last_block_reads_ahead.restype = i
     L.quamba_probe_workspace_bytes.restype = sz
     L.quamba_probe_workspace_bytes.argtypes = [i]
     L.quamba_probe_rate.restype = C.c_int
@@ -715,6 +717,10 @@ def quamba_debug_gemm_kind(M, N, K) -> int:
 
 def quamba_debug_xfmt_column_tiles(M, N, K) -> int:
     return int(lib().quamba_debug_xfmt_column_tiles(int(M), int(N), int(K)))
+
+
+def quamba_debug_last_block_reads_ahead(batch, L, d_model, d_inner) -> bool:
+    return bool(lib().quamba_debug_last_block_reads_ahead(int(batch), int(L), int(d_model), int(d_inner)))
 
 
 # ---- diagnostics: instruction-rate probes

@@ -11,8 +11,6 @@
 // is a skinny product that streams E once: an fp16 MFMA kernel with fp32 accumulation.
 // Generation keeps the current token, the step counter and the token log on the device, so one
 // step is a fixed sequence of launches that can be replayed from a HIP graph.
-#include <algorithm>
-
 #include "common.h"
 #include "device_util.h"
 
@@ -393,7 +391,7 @@ int run_model(const quamba_model *m, const int32_t *tokens, int Bt, int L, bool 
       if (rc != QUAMBA_OK) return rc;
       prev = OutPartial{decode && l + 1 < m->n_layers, 1, nullptr, 0.f};
       rc = mixer_run_q(&m->dims, &ly.q, &ly.s, u_q, Bt, L, decode, out, ssm, cs, base + c.mixer, c.mixer_bytes, st,
-                       &prev, decode ? nullptr : &m->layers[std::min(l + 1, m->n_layers - 1)].q);
+                       &prev, (!decode && l + 1 < m->n_layers) ? &m->layers[l + 1].q : nullptr, !decode && l + 1 == m->n_layers);
     }
     if (rc != QUAMBA_OK) return rc;
   }

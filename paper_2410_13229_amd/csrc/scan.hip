@@ -1046,19 +1046,33 @@ bool sweep_layout_ok(const ScanArgs &a) {
 //            SIMD is busy, 40 ns per token and wave
 //   chunked  30 + L * (W / 256) * 52 ns: three launches and the carry, every exponential taken twice
 // so the sweep takes the short sequences and the batches, the chunked form a long single sequence.
-bool sweep_is_cheaper(const ScanArgs &a) {
-  const double W = (double)a.Bt * (a.Di / SW_CH);
-  const int k = (int)std::ceil(W / 256.0);
-  const double s = k <= 1 ? 0.0645 : (k == 2 ? 0.098 : 0.040 * k);
-  const double sweep = 3.6 + a.L * s;
-  const double chunked = 30.0 + (double)a.L * (W / 256.0) * 0.052;
-  return sweep < chunked;
+double sweep_us(int Bt, int L, int Di) {
+  const int k = (int)std::ceil((double)Bt * (Di / SW_CH) / 256.0);
+  return 3.6 + L * (k <= 1 ? 0.0645 : (k == 2 ? 0.098 : 0.040 * k));
+}
+
+bool sweep_is_cheaper(int Bt, int L, int Di) {
+  const double W = (double)Bt * (Di / SW_CH);
+  return sweep_us(Bt, L, Di) < 30.0 + (double)L * (W / 256.0) * 0.052;
+}
+
+int sweep_warm_blocks(int Bt) { return std::max(1, 96 / Bt); }  // per sequence: about 96 workgroups in all
+
+// Does the sweep leave CUs idle for workgroups that read `bytes` ahead for one projection of a last block?  They must fit the last
+// round of at most three per CU (where they do not, they cost the scan a round: d_inner 4096, 2 x 512 tokens, 150 -> 165 us for
+// one block; d_inner 1536, 4 x 1024, 150 -> 180) and be done before the scan is, at 3 TB/s (d_inner 8192, 16 tokens:
+// 142 -> 147); and the cold read must be a visible part of that projection: from 12 MB (2.8B layer 13 MB, 512 tokens
+// 166.2 -> 162.0 us, 2 x 256 158.1 -> 154.2; 8 MB with d_inner 4096: no gain) and up to 2048 tokens (4 x 1024: no gain).
+bool sweep_idle_for_read_ahead(int Bt, int L, int Di, size_t bytes) {
+  const long wgs = (long)Bt * (Di / SW_CH), rest = wgs % 256;
+  return wgs <= 768 && rest > 0 && rest + (long)sweep_warm_blocks(Bt) * Bt <= 256 && bytes >= 12000000 && (long)Bt * L <= 2048 &&
+         (double)bytes / 3e6 <= sweep_us(Bt, L, Di);
 }
 
 template <int NK, int XM, bool LAT>
 int run_sweep(const Dev &p, const ScanArgs &a, hipStream_t st) {
   Dev q = p;
-  if (q.warm.n16[0] || q.warm.n16[1] || q.warm.n16[2]) q.warm.blocks = std::max(1, 96 / a.Bt);  // about 96 workgroups in all
+  if (q.warm.n16[0] || q.warm.n16[1] || q.warm.n16[2]) q.warm.blocks = sweep_warm_blocks(a.Bt);
   hipLaunchKernelGGL((scan_sweep_kernel<NK, XM, LAT>), dim3(a.Di / SW_CH + q.warm.blocks, a.Bt), dim3(SW_THREADS), 0, st, q,
                      a.ssm_state);
   QUAMBA_LAUNCH_CHECK();
@@ -1089,7 +1103,9 @@ int launch_scan_prefill(const ScanArgs &a, void *ws, size_t ws_bytes, hipStream_
     return fail(QUAMBA_EWORKSPACE, "scan: workspace %zu < %zu", ws_bytes, scan_workspace_bytes(a.Bt, a.L, a.Di));
   Dev p = make_dev(a);
   const int variant = g_scan_variant_hook.load(std::memory_order_relaxed);
-  if (variant != 1 && sweep_layout_ok(a) && (variant == 2 || sweep_is_cheaper(a))) {
+  const bool sweep = variant != 1 && sweep_layout_ok(a) && (variant == 2 || sweep_is_cheaper(a.Bt, a.L, a.Di));
+  if (a.warm_if_idle && !(sweep && sweep_idle_for_read_ahead(a.Bt, a.L, a.Di, a.warm_bytes[0]))) p.warm = WarmRanges{};
+  if (sweep) {
     switch (scan_x_mode(a)) {
       case X_E4M3: return dispatch_sweep<X_E4M3>(p, a, st);
       case X_LOG2: return dispatch_sweep<X_LOG2>(p, a, st);
@@ -1206,3 +1222,8 @@ int launch_scan_step(const ScanArgs &a, hipStream_t st) {
 }  // namespace quamba
 
 extern "C" void quamba_debug_set_scan_variant(int v) { quamba::g_scan_variant_hook.store(v); }
+extern "C" int quamba_debug_last_block_reads_ahead(int batch, int L, int d_model, int d_inner) {
+  if (batch < 1 || L < 1 || d_model < 16 || d_inner < 16 || d_inner % quamba::SW_CH) return 0;
+  return quamba::sweep_is_cheaper(batch, L, d_inner) &&
+         quamba::sweep_idle_for_read_ahead(batch, L, d_inner, (size_t)d_model * d_inner);
+}

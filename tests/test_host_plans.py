@@ -35,3 +35,14 @@ def test_column_groups_of_xfmt_proj_are_spread_where_that_was_measured_to_pay(M,
 ])
 def test_128_by_96_tiles_are_taken_where_that_was_measured_to_pay(M, N, K, taken):
     assert (Q.quamba_debug_gemm_kind(M, N, K) == 14) == taken
+
+
+@pytest.mark.parametrize("batch,L,Dm,Di,ahead", [
+    (1, 512, 2560, 5120, True), (2, 256, 2560, 5120, True), (4, 512, 2560, 5120, True), (1, 256, 6144, 4096, True),
+    (3, 512, 2560, 5120, False), (2, 512, 6144, 4096, False), (1, 256, 4096, 8192, False),  # no idle CUs in the last round
+    (4, 1024, 768, 1536, False), (2, 512, 2048, 4096, False),                               # weights of 1 and 8 MB
+    (1, 1, 2560, 5120, False), (1, 16, 6144, 4096, False),                                  # scans shorter than the read
+    (1, 4096, 2560, 5120, False), (4, 1024, 2560, 5120, False), (12, 64, 2560, 5120, False),
+])
+def test_last_block_reads_ahead_only_beside_a_scan_that_leaves_cus_idle(batch, L, Dm, Di, ahead):
+    assert Q.quamba_debug_last_block_reads_ahead(batch, L, Dm, Di) == ahead
