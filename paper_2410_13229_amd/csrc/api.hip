@@ -218,7 +218,7 @@ int run_mixer(const quamba_dims *d, const quamba_qweights *qw, const quamba_scal
       a.out_prev = norm->out_prev; a.res_in = norm->res_in; a.res_out = norm->res_out; a.norm_w = norm->norm_w;
       a.eps = norm->eps; a.inv_s_u = sc->inv_s_u;
     } else if (quant_in) {
-      a.u = u; a.inv_s_u = sc->inv_s_u;
+      a.out_prev = u; a.inv_s_u = sc->inv_s_u;
     } else {
       a.u_q = uq;
     }

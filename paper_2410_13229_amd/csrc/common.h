@@ -177,15 +177,15 @@ int launch_hadamard_out_proj(const __half *g, int M, int n, float inv_s_y, const
 int launch_hadamard_inverse(const int8_t *xH_q, int M, int n, float scale, __half *x_hat, hipStream_t st);
 
 // generation with M <= 4 rows: [add + RMSNorm + quant] -> in_proj -> conv step in one kernel.
-// Either u_q (already quantized input [M, Dm]) or out_prev / res_in / res_out / norm_w (res_out must
-// not alias res_in: every workgroup reads res_in while workgroup 0 writes res_out).
+// One of u_q (already quantized input [M, Dm]), out_prev / res_in / res_out / norm_w (res_out must not alias
+// res_in: every workgroup reads res_in while workgroup 0 writes res_out), or out_prev alone (no u_q, no
+// res_in): the block input in half precision, quantized as it is.
 struct DecodeInArgs {
   const __half *out_prev, *res_in;
   __half *res_out;
   const __half *norm_w;
   float eps, inv_s_u;
-  const int8_t *u_q;   // codes of the block input, or
-  const __half *u;     // the block input itself, quantized in the kernel
+  const int8_t *u_q;
   const int8_t *W_in;
   int Dm, Di, M;
   float m_in_x, m_in_z;

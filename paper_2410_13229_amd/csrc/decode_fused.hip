@@ -4,8 +4,12 @@
 // handful of rows every one of these is a few microseconds of launch latency and almost no work,
 // and each output column of in_proj needs only its own conv window, so the three chain inside
 // one workgroup:
-//   s = fp16(out_prev + res_in)            (workgroup 0 stores it as the new residual)
-//   u_q = q(RMSNorm(s) * w, 1/s_u)         (recomputed by every workgroup into LDS: M rows only)
+//   the codes of the block input into LDS, by every workgroup again (M rows only), from one of
+//     the codes themselves (p.u_q)
+//     the residual stream: s = fp16(out_prev + res_in) (workgroup 0 stores it as the new residual),
+//       u_q = q(RMSNorm(s) * w, 1/s_u)
+//     the block input in half precision (F16): u_q = q(u, 1/s_u), a kernel of its own: as a third branch
+//       chosen at run time it cost the 64-block step with one sequence 1657 -> 1662 us
 //   acc[m, n] = sum_k u_q[m, k] W_in[n, k]  for the workgroup's 16 columns n (4 per wave)
 //   n <  Di: xpre_q = q(acc m_in_x) -> conv step on that channel's window -> x_q[m, n]
 //   n >= Di: z_q[m, n - Di] = q(acc m_in_z)
@@ -16,7 +20,7 @@
 namespace quamba {
 namespace {
 
-template <int MB>
+template <int MB, bool F16>
 __global__ __launch_bounds__(256) void decode_in_kernel(DecodeInArgs p) {
   extern __shared__ __attribute__((aligned(16))) int8_t sA[];  // [MB][Dm] int8 codes of u, rows past M zero
   __shared__ float part[4][MB];
@@ -38,15 +42,7 @@ __global__ __launch_bounds__(256) void decode_in_kernel(DecodeInArgs p) {
       wpre[r][j] = *reinterpret_cast<const v4i *>(p.W_in + (size_t)min(n0 + j, N - 1) * Dm + ch * 16);
     }
 
-  if (p.u_q) {  // already quantized input
-#pragma unroll
-    for (int m = 0; m < MB; ++m)
-      for (int ch = tid; ch < Dm / 16; ch += 256) {
-        v4i v = {0, 0, 0, 0};
-        if (m < M) v = *reinterpret_cast<const v4i *>(p.u_q + (size_t)m * Dm + ch * 16);
-        *reinterpret_cast<v4i *>(sA + (size_t)m * Dm + ch * 16) = v;
-      }
-  } else if (p.u) {  // quantize_f16's arithmetic, M rows in every workgroup
+  if constexpr (F16) {  // quantize_f16's arithmetic
     for (int g = tid; g < MB * groups; g += 256) {
       const int m = g / groups;
       uint2 c = make_uint2(0u, 0u);
@@ -55,7 +51,7 @@ __global__ __launch_bounds__(256) void decode_in_kernel(DecodeInArgs p) {
           uint4 u;
           __half h[8];
         } in;
-        in.u = *reinterpret_cast<const uint4 *>(p.u + (size_t)g * 8);
+        in.u = *reinterpret_cast<const uint4 *>(p.out_prev + (size_t)g * 8);
         float v[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[e] = __half2float(in.h[e]) * p.inv_s_u;
@@ -63,6 +59,14 @@ __global__ __launch_bounds__(256) void decode_in_kernel(DecodeInArgs p) {
       }
       *reinterpret_cast<uint2 *>(sA + (size_t)g * 8) = c;
     }
+  } else if (p.u_q) {  // already quantized input
+#pragma unroll
+    for (int m = 0; m < MB; ++m)
+      for (int ch = tid; ch < Dm / 16; ch += 256) {
+        v4i v = {0, 0, 0, 0};
+        if (m < M) v = *reinterpret_cast<const v4i *>(p.u_q + (size_t)m * Dm + ch * 16);
+        *reinterpret_cast<v4i *>(sA + (size_t)m * Dm + ch * 16) = v;
+      }
   } else {
     // One sweep: the fp16 sums s = fp16(out + res) stay in registers (8 halves per 16-byte word) between
     // the reduction and the scaling; a thread owns at most SW words per row (d_model <= 4096 with 2).
@@ -251,10 +255,20 @@ int launch_decode_in(const DecodeInArgs &a, hipStream_t st) {
   const int mb = a.M <= 1 ? 1 : (a.M <= 2 ? 2 : 4);
   const size_t lds = (size_t)mb * a.Dm;
   const dim3 grid((2 * a.Di + 15) / 16), block(256);
+  const bool f16 = !a.u_q && !a.res_in;
   switch (mb) {
-    case 1: hipLaunchKernelGGL(decode_in_kernel<1>, grid, block, lds, st, a); break;
-    case 2: hipLaunchKernelGGL(decode_in_kernel<2>, grid, block, lds, st, a); break;
-    default: hipLaunchKernelGGL(decode_in_kernel<4>, grid, block, lds, st, a); break;
+    case 1:
+      if (f16) hipLaunchKernelGGL((decode_in_kernel<1, true>), grid, block, lds, st, a);
+      else hipLaunchKernelGGL((decode_in_kernel<1, false>), grid, block, lds, st, a);
+      break;
+    case 2:
+      if (f16) hipLaunchKernelGGL((decode_in_kernel<2, true>), grid, block, lds, st, a);
+      else hipLaunchKernelGGL((decode_in_kernel<2, false>), grid, block, lds, st, a);
+      break;
+    default:
+      if (f16) hipLaunchKernelGGL((decode_in_kernel<4, true>), grid, block, lds, st, a);
+      else hipLaunchKernelGGL((decode_in_kernel<4, false>), grid, block, lds, st, a);
+      break;
   }
   QUAMBA_LAUNCH_CHECK();
   return QUAMBA_OK;
