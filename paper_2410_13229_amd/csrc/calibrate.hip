@@ -33,10 +33,11 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // lane ends with four consecutive columns of one row.  A slice is 32 of K, register-prefetched into one padded LDS
 // buffer; a lane reads four consecutive k of every eight as 16 bytes, and two swaps between the halves of the wave make of
 // the four registers the operands of four products in the order of k (stored in that order instead, as pairs, the
-// products took 600 us at the size below), so LDS gives 0.75 reads per four products and the matrix pipe is what bounds it.
-// Small tiles on purpose: 1024 x 10240 is 1280 workgroups of 128 x 64, five on every CU, whose waves cover each other's barriers.
-// WM x WN waves: 128 x 64, 64 x 128, 32 x 256 outputs per workgroup.  1024 x 10240 x 2560: 553 us = 97 TFLOP/s of the
-// 157 that fp32 matrix products reach at most (a 64 x 64 tile on the vector units: 935 us).
+// products took 600 us at the size below), so a wave reads 16 bytes per lane three times for eight products.
+// Small tiles, so that several workgroups cover each other's barriers: 74 vector and 32 accumulation registers leave room for
+// four on a CU.  The 1280 of 1024 x 10240 are a full round of them and a quarter of one, in which a workgroup has its CU to
+// itself: 553 us = 97 TFLOP/s of the 157 that fp32 matrix products reach at most (a 64 x 64 tile on the vector units: 935 us).
+// WM x WN waves: 128 x 64, 64 x 128, 32 x 256 outputs per workgroup.
 constexpr int GK = 32, GLD = GK + 4;
 
 template <int WM, int WN>
@@ -262,7 +263,7 @@ int absmax(const Obs *obs, int count, unsigned *slots, hipStream_t st) {
     int lt = 2;
     while (lt < 8 && (4 << lt) < w) ++lt;
     s.lt[i] = lt;
-    // at least 8192 values per workgroup, at most 512 workgroups
+    // a workgroup for every 8192 values begun, at most 512
     s.end[i] = end += (unsigned)std::min<size_t>((total + 8191) / 8192, 512);
   }
   hipLaunchKernelGGL(absmax_kernel, dim3(end), dim3(256), 0, st, s, slots);
@@ -670,7 +671,6 @@ int fp_forward(const quamba_dims *d, const quamba_fp_weights *w, const __half *c
   hipLaunchKernelGGL(neg_exp_kernel, dim3(nblk((size_t)Di * N)), dim3(256), 0, st, w->A_log, b.A, (size_t)Di * N);
   QUAMBA_LAUNCH_CHECK();
   int rc;
-  // partial sums of a split K go to buffers that are written later
   if ((rc = sgemm(b.u32, Dm, w->W_in, Dm, b.xz, (int)M, 2 * Di, Dm, st))) return rc;
   hipLaunchKernelGGL(conv_silu_f32_kernel, dim3(nblk(M * Di / 4)), dim3(256), 0, st, b.xz, 2 * Di, w->conv_w,
                      w->conv_b, Lc, Di, b.x, M * Di / 4);

@@ -6,7 +6,7 @@
 //   acc[m, n] = sum_k W_q[n, k] value(x_code[m, k]);   out = clamp(rne(acc * mult)) int8
 // The output is skinny (N = dt_rank + 2 d_state <= 320) and K deep, so K is cut over grid.y into
 // equal ranges whose fp32 partial sums a second kernel adds in ascending order (a fixed order:
-// the result does not depend on scheduling).  A workgroup is 64 (or 128) rows x all columns: wave w
+// the result does not depend on scheduling).  A workgroup is 64 (or 128) rows x all columns (64 in small launches): wave w
 // takes row tile(s) w % 2 and the column tiles w / 2, w / 2 + 2, ...; operands come straight from global
 // memory and the codes are decoded in registers.  So that those loads are whole cache lines, the
 // bf16 weight is stored in the order the matrix unit consumes it (the calibration writes it):

@@ -313,8 +313,8 @@ __global__ __launch_bounds__(threads_for(K << LOGM)) void hadamard_quant_kernel(
 
 // Generation with up to three sequences: Hadamard + quantization + out_proj in one launch.  Two launches
 // of a few microseconds each, almost all of it latency, become one: every workgroup owns one row and OC
-// output columns, asks for its pieces of their weight rows first (one 16-byte piece per thread and column:
-// n / 16 threads), transforms its row itself while they arrive (redundantly: the row is 10 KB
+// output columns, asks for its pieces of their weight rows first (one 16-byte piece per thread and column, n / 16
+// threads rounded up to whole waves), transforms its row itself while they arrive (redundantly: the row is 10 KB
 // and stays in the cache), and multiplies the 16 codes each thread ends up holding with exactly the
 // weight pieces it asked for.  The codes are the stand-alone kernel's bit for bit (same passes, same
 // order); the workgroups of column group 0 also store them.  out[r, n] = fp16(acc[r, n] * m_out).
@@ -486,8 +486,10 @@ int run_out_proj(const __half *g, int M, float inv_s, const int8_t *W, int Dm, f
 }
 }  // namespace
 
-// orders for which one thread per 16 elements is one and a half waves or more and the row fits 64 KB of LDS
-// (1536, the 130M layer's width: with one sequence the step is bound by its launches, 22.9 -> 17.9 us with one less)
+// orders for which one thread per 16 elements is a whole wave or more and the row fits 64 KB of LDS: 1024 to 8192, 1536 to 12288
+// and 2560 to 10240, each by powers of two.  The step of a narrow layer is bound by its launches: with three sequences (20 launches
+// in a graph, us each) 1536 wide 19.9 -> 17.5, 2560 wide 21.8 -> 18.6; with one or two, quantization in in_proj's launch
+// included, 16.2 -> 14.0 and 18.5 -> 15.0, 16.2 -> 13.9 and 18.8 -> 15.2
 bool hadamard_fuses_out_proj(int n, int Dm) {
   int k = 0, m = 0;
   if (Dm < 1 || !hadamard_factor(n, &k, &m)) return false;

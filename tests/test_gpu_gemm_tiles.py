@@ -1,4 +1,4 @@
-"""The 128 x 96 tiles of the int8 GEMM: ragged edges against the oracle, and the sizes at which the planner takes them."""
+"""The 128 x 96 tiles of the int8 GEMM: ragged edges against the oracle, and the sums where the planner takes them."""
 import numpy as np
 import pytest
 
@@ -28,9 +28,11 @@ def test_tiles_of_128_by_96_forced_onto_ragged_shapes(M, N, K):
     assert np.array_equal(host(outh).view(np.uint16), (acc_ref.astype(np.float32) * mult[0]).astype(np.float16).view(np.uint16))
 
 
-@pytest.mark.parametrize("M,N,K", [(896, 2560, 5120), (897, 2560, 5120), (1152, 2560, 5120), (1153, 2560, 5120), (520, 4096, 8192)])
-def test_planned_tiles_give_the_sums_of_the_64_by_64_ones(M, N, K):
+@pytest.mark.parametrize("M,N,K,taken", [(896, 2560, 5120, False), (897, 2560, 5120, True), (1152, 2560, 5120, True),
+                                         (1153, 2560, 5120, False), (520, 4096, 8192, True)])
+def test_planned_tiles_give_the_sums_of_the_64_by_64_ones(M, N, K, taken):
     """Either side of the row counts at which the planner changes over (189 and 270 tiles are outside its range)."""
+    assert (Q.quamba_debug_gemm_kind(M, N, K) == 14) == taken
     g = torch.Generator(device="cuda:0").manual_seed(M)
     A, Wt = (torch.randint(-128, 128, s, dtype=torch.int8, device="cuda:0", generator=g) for s in ((M, K), (N, K)))
     mult, ws, got = np.array([1e-5] * 3, dtype=np.float32), workspace(Q.quamba_gemm_workspace_bytes(M, N, K)), []

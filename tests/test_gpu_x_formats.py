@@ -65,7 +65,8 @@ def test_encoder_bit_exact(fmt):
 
 @pytest.mark.parametrize("fmt", XF.FORMATS)
 @pytest.mark.parametrize("M,N,K", [(1, 48, 64), (37, 80, 192), (64, 192, 5120), (200, 192, 5120), (2048, 192, 5120),
-                                   (4100, 192, 1024), (70, 288, 1024), (5, 320, 32), (33, 192, 352)])
+                                   (4100, 192, 1024), (70, 288, 1024), (5, 320, 32), (33, 192, 352),
+                                   (961, 132, 4096), (1216, 288, 4096), (1217, 288, 4096)])
 def test_xfmt_proj_against_the_float64_product(fmt, M, N, K):
     rng = np.random.default_rng(M + N + K)
     t = (rng.standard_normal((M, K)) * np.exp(rng.standard_normal((M, K)))).astype(np.float32)
