@@ -331,7 +331,7 @@ int run_mixer(const quamba_dims *d, const quamba_qweights *qw, const quamba_scal
     } else {
       if (next_qw || last_block) {  // a stack of blocks: warm the cache with the weights that come next
         a.warm_ptr[0] = qw->W_outH; a.warm_bytes[0] = (size_t)Dm * Di;
-        a.warm_if_idle = !next_qw;
+        a.warm_if_it_pays = !next_qw;
       }
       if (next_qw) {
         a.warm_ptr[1] = next_qw->W_in; a.warm_bytes[1] = (size_t)2 * Di * Dm;

@@ -161,7 +161,7 @@ struct ScanArgs {
   // these ranges (16-byte aligned) and thereby bring them into the last-level cache; nothing is written
   const void *warm_ptr[3];
   size_t warm_bytes[3];
-  bool warm_if_idle;  // only where the launch leaves CUs idle for it (the last block of a stack, whose gain is one cold read)
+  bool warm_if_it_pays;  // the last block of a stack, whose gain is one cold read: only where that outweighs the cost to the scan
 };
 
 size_t scan_workspace_bytes(int Bt, int L, int Di);
@@ -218,8 +218,8 @@ int mixer_run_q(const quamba_dims *d, const quamba_qweights *qw, const quamba_sc
                 bool last_block = false);
 // next_qw (prefill, optional): the weights of the block that runs after this one; its in_proj and x_proj weights
 // and this block's out_proj weights are read into the last-level cache under the scan (ScanArgs::warm_ptr).
-// last_block (prefill): no block follows in the stack; this block's out_proj weights alone, where the scan leaves CUs
-// idle (2.8B layer, 512 tokens: that projection 25.4 -> 18 us)
+// last_block (prefill): no block follows in the stack; this block's out_proj weights alone, where that pays (2.8B
+// layer, 512 tokens: that projection 25.4 -> 18 us)
 int check_model_dims(const quamba_dims *d);
 
 // generation with at most 4 sequences: the block's own residual add + RMSNorm + quantization runs

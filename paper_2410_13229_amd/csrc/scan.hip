@@ -1058,15 +1058,22 @@ bool sweep_is_cheaper(int Bt, int L, int Di) {
 
 int sweep_warm_blocks(int Bt) { return std::max(1, 96 / Bt); }  // per sequence: about 96 workgroups in all
 
-// Does the sweep leave CUs idle for workgroups that read `bytes` ahead for one projection of a last block?  They must fit the last
-// round of at most three per CU (where they do not, they cost the scan a round: d_inner 4096, 2 x 512 tokens, 150 -> 165 us for
-// one block; d_inner 1536, 4 x 1024, 150 -> 180) and be done before the scan is, at 3 TB/s (d_inner 8192, 16 tokens:
-// 142 -> 147); and the cold read must be a visible part of that projection: from 12 MB (2.8B layer 13 MB, 512 tokens
-// 166.2 -> 162.0 us, 2 x 256 158.1 -> 154.2; 8 MB with d_inner 4096: no gain) and up to 2048 tokens (4 x 1024: no gain).
-bool sweep_idle_for_read_ahead(int Bt, int L, int Di, size_t bytes) {
-  const long wgs = (long)Bt * (Di / SW_CH), rest = wgs % 256;
-  return wgs <= 768 && rest > 0 && rest + (long)sweep_warm_blocks(Bt) * Bt <= 256 && bytes >= 12000000 && (long)Bt * L <= 2048 &&
-         (double)bytes / 3e6 <= sweep_us(Bt, L, Di);
+// Does reading `bytes` ahead for one projection (the last block of a stack) pay?  It must be a visible part of that projection
+// (from 12 MB: with the 8 MB of width 4096 no gain, with the 1 MB of width 1536 a loss) and the reading workgroups must not
+// lengthen the scan.  One block, us without -> with:
+//   up to three sweep workgroups per CU, all resident: they have to fit CUs that the last of these leaves idle, be done before the
+//     scan is at 3.5 TB/s, up to 2048 tokens (2.8B layer, 512 tokens 166.2 -> 162.0, 4 x 256 196.1 -> 192.5; full CUs: 3 x 512
+//     237 -> 247; width 4096, d_model 6144, 2 x 512 342 -> 359; Jamba's layer, 16 tokens 142 -> 147)
+//   more of them, or the chunked form: the launch has a tail anyway, so beside a full last round too, for scans that outlast
+//     the read at 2 TB/s and small projections, 1680 tokens of the 2.8B layer (16 x 32 156.7 -> 152.3, 1 x 1152 248.9 -> 241.1,
+//     9 x 179 238.5 -> 233.3, 64 x 1 164.6 -> 166.2; 8 x 512 414 -> 427, 1 x 4096 464 -> 472), up to 20 MB (Jamba's layer, 33 MB:
+//     27 x 21 312 -> 304, but 52 x 9 329 -> 341)
+bool read_ahead_pays(int Bt, int L, int Di, size_t bytes, bool sweep) {
+  const long wgs = (long)Bt * (Di / SW_CH), rest = wgs % 256, tokens = (long)Bt * L;
+  const bool fits = rest + (long)sweep_warm_blocks(Bt) * Bt <= 256;
+  if (bytes < 12000000) return false;
+  if (sweep && wgs <= 768) return fits && rest > 0 && tokens <= 2048 && (double)bytes / 3.5e6 <= sweep_us(Bt, L, Di);
+  return bytes < 20000000 && (double)tokens * (double)bytes <= 2.2e10 && (!sweep || (fits && (double)bytes / 2e6 <= sweep_us(Bt, L, Di)));
 }
 
 template <int NK, int XM, bool LAT>
@@ -1104,7 +1111,7 @@ int launch_scan_prefill(const ScanArgs &a, void *ws, size_t ws_bytes, hipStream_
   Dev p = make_dev(a);
   const int variant = g_scan_variant_hook.load(std::memory_order_relaxed);
   const bool sweep = variant != 1 && sweep_layout_ok(a) && (variant == 2 || sweep_is_cheaper(a.Bt, a.L, a.Di));
-  if (a.warm_if_idle && !(sweep && sweep_idle_for_read_ahead(a.Bt, a.L, a.Di, a.warm_bytes[0]))) p.warm = WarmRanges{};
+  if (a.warm_if_it_pays && !read_ahead_pays(a.Bt, a.L, a.Di, a.warm_bytes[0], sweep)) p.warm = WarmRanges{};
   if (sweep) {
     switch (scan_x_mode(a)) {
       case X_E4M3: return dispatch_sweep<X_E4M3>(p, a, st);
@@ -1224,6 +1231,5 @@ int launch_scan_step(const ScanArgs &a, hipStream_t st) {
 extern "C" void quamba_debug_set_scan_variant(int v) { quamba::g_scan_variant_hook.store(v); }
 extern "C" int quamba_debug_last_block_reads_ahead(int batch, int L, int d_model, int d_inner) {
   if (batch < 1 || L < 1 || d_model < 16 || d_inner < 16 || d_inner % quamba::SW_CH) return 0;
-  return quamba::sweep_is_cheaper(batch, L, d_inner) &&
-         quamba::sweep_idle_for_read_ahead(batch, L, d_inner, (size_t)d_model * d_inner);
+  return quamba::read_ahead_pays(batch, L, d_inner, (size_t)d_model * d_inner, quamba::sweep_is_cheaper(batch, L, d_inner));
 }

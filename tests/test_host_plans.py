@@ -41,8 +41,10 @@ def test_128_by_96_tiles_are_taken_where_that_was_measured_to_pay(M, N, K, taken
     (1, 512, 2560, 5120, True), (2, 256, 2560, 5120, True), (4, 512, 2560, 5120, True), (1, 256, 6144, 4096, True),
     (3, 512, 2560, 5120, False), (2, 512, 6144, 4096, False), (1, 256, 4096, 8192, False),  # no idle CUs in the last round
     (4, 1024, 768, 1536, False), (2, 512, 2048, 4096, False),                               # weights of 1 and 8 MB
-    (1, 1, 2560, 5120, False), (1, 16, 6144, 4096, False),                                  # scans shorter than the read
-    (1, 4096, 2560, 5120, False), (4, 1024, 2560, 5120, False), (12, 64, 2560, 5120, False),
+    (1, 4, 2560, 5120, True), (1, 1, 2560, 5120, False), (1, 16, 6144, 4096, False),        # scans shorter than the read
+    (1, 1456, 2560, 5120, True), (1, 4096, 2560, 5120, False), (1, 1024, 6144, 4096, False),  # chunked scans
+    (16, 32, 2560, 5120, True), (64, 16, 2560, 5120, True), (64, 1, 2560, 5120, False), (6, 96, 2560, 5120, False),
+    (8, 512, 2560, 5120, False), (52, 9, 4096, 8192, False),                                # sweeps of many rounds
 ])
-def test_last_block_reads_ahead_only_beside_a_scan_that_leaves_cus_idle(batch, L, Dm, Di, ahead):
+def test_last_block_reads_ahead_only_where_that_was_measured_to_pay(batch, L, Dm, Di, ahead):
     assert Q.quamba_debug_last_block_reads_ahead(batch, L, Dm, Di) == ahead
