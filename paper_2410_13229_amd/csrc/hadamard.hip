@@ -316,7 +316,7 @@ __global__ __launch_bounds__(threads_for(K << LOGM)) void hadamard_quant_kernel(
 // output columns, asks for its pieces of their weight rows first (one 16-byte piece per thread and column, n / 16
 // threads rounded up to whole waves), transforms its row itself while they arrive (redundantly: the row is 10 KB
 // and stays in the cache), and multiplies the 16 codes each thread ends up holding with exactly the
-// weight pieces it asked for.  The codes are the stand-alone kernel's bit for bit (same passes, same
+// weight pieces it asked for.  The codes and sums are the stand-alone kernels' bit for bit (same passes, same
 // order); the workgroups of column group 0 also store them.  out[r, n] = fp16(acc[r, n] * m_out).
 constexpr int OC = 16;  // output columns per workgroup (8: +2 %, 4: +3 %, 32: +12 % on the 64-block step)
 
@@ -372,7 +372,12 @@ __global__ __launch_bounds__(threads_for(K << LOGM)) void hadamard_out_proj_kern
     int a = 0;
 #pragma unroll
     for (int w = 0; w < HT / 64; ++w) a += red[w][tid];
-    out[(size_t)r * Dm + n0 + tid] = __float2half_rn(static_cast<float>(a) * m_out);
+    float y = static_cast<float>(a) * m_out;
+    // Left alone, the compiler folds product and conversion into one instruction with one rounding (v_fma_mixlo_f16), which
+    // differs from the separate kernels' fp32 product where that lands halfway between two halves (one output in 10^4).
+    // 1536 and 2560 keep those kernels' bits; the other orders have been rounded once for as long as this launch serves them.
+    if constexpr (HT != n / 16) asm volatile("" : "+v"(y));
+    out[(size_t)r * Dm + n0 + tid] = __float2half_rn(y);
   }
 }
 
