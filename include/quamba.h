@@ -608,6 +608,9 @@ int quamba_probe_rate(int probe, int waves_per_simd, int iters, double *instr_pe
  *   quamba_debug_set_scan_variant(v)   prefill scan: 1 = always the three-pass chunked form, 2 = one sweep per
  *                                      sequence wherever its layout rules hold, 0 = default (the cheaper of
  *                                      the two by the library's estimate for the shape)
+ *   quamba_debug_set_decode_stack(v)   generation of a stack with one or two sequences: 1 = four launches a block,
+ *                                      2 = all blocks in one launch, its work items taken from a counter as when
+ *                                      the GPU is shared; 0 = default (all blocks in one launch where served)
  * Host-only queries of what is chosen for a shape with the full workspace, for tests of the rules:
  *   quamba_debug_gemm_kind(M, N, K)    configuration of an int8 GEMM as quamba_debug_set_gemm_variant counts
  *                                      them, before the launcher cuts rows; -1 = few-row streaming kernel, -2 = not served
@@ -622,6 +625,7 @@ void quamba_debug_set_gemv_max_rows(int v);
 void quamba_debug_set_fuse_dt(int v);
 void quamba_debug_set_fuse_decode(int v);
 void quamba_debug_set_scan_variant(int v);
+void quamba_debug_set_decode_stack(int v);
 int quamba_debug_gemm_kind(int M, int N, int K);
 int quamba_debug_xfmt_column_tiles(int M, int N, int K);
 int quamba_debug_last_block_reads_ahead(int batch, int L, int d_model, int d_inner);

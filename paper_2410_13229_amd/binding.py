@@ -29,7 +29,7 @@ __all__ = [
     "quamba_xdyn_workspace_bytes", "quamba_mixer_prefill_xdyn", "quamba_mixer_decode_xdyn",
     "quamba_debug_set_gemm_variant", "quamba_debug_set_gemm_split", "quamba_debug_set_gemv_max_rows",
     "quamba_debug_set_fuse_dt", "quamba_debug_set_fuse_decode", "quamba_debug_set_scan_variant",
-    "quamba_debug_gemm_kind", "quamba_debug_xfmt_column_tiles", "quamba_debug_last_block_reads_ahead",
+    "quamba_debug_set_decode_stack", "quamba_debug_gemm_kind", "quamba_debug_xfmt_column_tiles", "quamba_debug_last_block_reads_ahead",
     "PROBE_FMA_F32", "PROBE_EXP_F32", "PROBE_SCAN_MIX", "PROBE_MFMA_I8", "PROBE_MFMA_I8_RANDOM",
     "PROBE_MUL_F32", "PROBE_FMA_EXP_INDEP", "PROBE_MIX_NOEXP", "PROBE_MIX_GROUPED",
     "quamba_probe_workspace_bytes", "quamba_probe_rate",
@@ -349,7 +349,8 @@ def lib():
                  "quamba_scan_prefill_dtproj", "quamba_hadamard_quant"):
         getattr(L, name).restype = C.c_int
     for name in ("quamba_debug_set_gemm_variant", "quamba_debug_set_gemm_split", "quamba_debug_set_gemv_max_rows",
-                 "quamba_debug_set_fuse_dt", "quamba_debug_set_fuse_decode", "quamba_debug_set_scan_variant"):
+                 "quamba_debug_set_fuse_dt", "quamba_debug_set_fuse_decode", "quamba_debug_set_scan_variant",
+                 "quamba_debug_set_decode_stack"):
         getattr(L, name).argtypes = [i]
         getattr(L, name).restype = None
     for name in ("quamba_debug_gemm_kind", "quamba_debug_xfmt_column_tiles"):
@@ -709,6 +710,10 @@ def quamba_debug_set_fuse_decode(v):
 
 def quamba_debug_set_scan_variant(v):
     lib().quamba_debug_set_scan_variant(int(v))
+
+
+def quamba_debug_set_decode_stack(v):
+    lib().quamba_debug_set_decode_stack(int(v))
 
 
 def quamba_debug_gemm_kind(M, N, K) -> int:

@@ -408,6 +408,10 @@ bool mixer_decode_norm_available(const quamba_dims *d, int Bt) {
   return g_fuse_decode_hook.load(std::memory_order_relaxed) && Bt <= gemv_max_rows() && d->d_model <= 8192;
 }
 
+bool mixer_decode_fuses_dt() { return g_fuse_dt_hook.load(std::memory_order_relaxed) != 0; }
+
+int check_model_layer(const quamba_qweights *qw, const quamba_scales *sc) { return check_q(qw, sc); }
+
 int check_model_dims(const quamba_dims *d) { return check_dims(d); }
 
 }  // namespace quamba

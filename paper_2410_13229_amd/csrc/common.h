@@ -231,8 +231,15 @@ struct NormIn {
   float eps;
 };
 bool mixer_decode_norm_available(const quamba_dims *d, int Bt);
+bool mixer_decode_fuses_dt();
 int mixer_decode_norm(const quamba_dims *d, const quamba_qweights *qw, const quamba_scales *sc, const NormIn &norm,
                       int Bt, __half *out, float *ssm_state, __half *conv_state, void *ws, size_t ws_bytes,
                       hipStream_t st);
+
+// one layer's weights and scales as run_mixer checks them
+int check_model_layer(const quamba_qweights *qw, const quamba_scales *sc);
+// generation with one or two sequences: all blocks of the stack in one launch, where the shape and the device allow (*served)
+int launch_decode_stack(const quamba_model *m, const int32_t *tokens, int Bt, float *ssm, __half *conv, __half *out, __half *res,
+                        void *ws, size_t ws_bytes, hipStream_t st, bool *served);
 
 }  // namespace quamba

@@ -1,0 +1,878 @@
+// Generation with one or two sequences: the whole stack of blocks in one launch.
+//
+// A block of such a step is a chain of four small products (A in_proj + conv step, B x_proj, C scan step with dt_proj, D Hadamard +
+// out_proj), each of which needs all of the one before.  As four launches a block, the 64-block step of the 2.8B model
+// spends most of its time on launch boundaries and on the first reads of cold weights behind them.  Here one workgroup per CU
+// stays for all blocks; eight of its waves have role A (40 columns of in_proj), five role D (10 columns of out_proj), three B or C,
+// and each role walks the blocks at its own pace.  A wave asks for its weights of the next block as soon as it is done with the last
+// (8 x 15 and 5 x 10 rows of 1 KB, all in registers) and then waits for its input, so the 40 MB of a block stream in
+// under the other roles, and a hand-over costs one trip through the memory side (1.2 to 2 us among 256 workgroups) instead of
+// a launch boundary plus the first cold read.  64 blocks of the 2.8B layer: one sequence 1637 -> 1049 us a step, two 1936 -> 1610.  Bound by the
+// chain: of 16.5 us a block about 7 are hand-overs, 4 the Hadamard transform with its products, 3 in_proj (its weights
+// arrive 9 us early).
+//
+// Hand-over: every 4 bytes of payload (four codes, or two halves) travel in one 8-byte word with a tag, the number of the block
+// plus one, written and read by relaxed 64-bit atomics at device scope.  A reader that sees its tag has the payload, so no
+// fence (which would write back or drop a whole L2) and no flag is needed.  One buffer per kind of value serves all blocks: a word is
+// overwritten for block l + 1 only by a workgroup whose input needs, through the chain, every reader of block l's word to be done.
+// How the words lie and are polled decides the speed (the same step 1750 us with every wave polling all its words in lines shared by neighbours): a
+// workgroup's words fill lines of their own, readers take whole lines through LDS, and until the first word is there one wave per role
+// watches it alone.
+//
+// Progress does not depend on how many workgroups run at once.  At its start every workgroup signs in; if all of them
+// do so within a bounded time they are all resident, and each keeps its own items (the walk above).  If not (another
+// kernel holds part of the GPU), the ones that run take the items from a counter, in an order in which an item only waits for
+// items with lower numbers, which somebody already holds: any number of workgroups gets through (all resident, that form
+// takes 1195 us).  Every wait is bounded (WAIT_TRIES polls, far beyond any wait that can occur); a workgroup that gives up marks the
+// step, whose output is then NaN.
+//
+// Arithmetic, operand order and rounding are those of the separate kernels (decode_in_kernel, gemv_i8_kernel, scan_step_kernel,
+// hadamard_out_proj_kernel): same bits.
+#include <algorithm>
+#include <atomic>
+
+#include "common.h"
+#include "hadamard_row.h"
+
+namespace quamba {
+
+// 0: on where it is served, 1: off, 2: on, with the work items taken from the counter
+std::atomic<int> g_decode_stack_hook{0};
+
+namespace {
+
+typedef unsigned long long u64;
+constexpr float LOG2E = 1.44269504088896340736f;
+constexpr float LN2 = 0.69314718055994530942f;
+constexpr int NS = 16;
+constexpr int AC = 5;          // in_proj columns per wave
+constexpr int PF = 3;          // rounds of 64 16-byte pieces that cover d_model
+// Measured at 64 blocks of the 2.8B layer, one sequence: 3 weight loads in flight per wave 1049 us, 2 1065, 5 1090, all at once 1105; a
+// pause of 4 in front of a repeated poll 1049, 1 1056, none 1062 (units of 64 clocks)
+constexpr int LOADS_IN_FLIGHT = 3, FRONT_PACE = 20, PACE = 4, RETRY_PACE = 2;
+constexpr int WAIT_TRIES = 1 << 18;
+constexpr int SIGN_IN_TRIES = 64;
+
+// A workgroup is one per CU, 16 waves: 8 for role A, 5 for D, 3 for B or C (the first workgroups B, the others C).
+constexpr int A_WAVES = 8, D_WAVES = 5, BC_WAVES = 3;
+constexpr int STACK_THREADS = 64 * (A_WAVES + D_WAVES + BC_WAVES);
+constexpr int A_COLS = A_WAVES * AC;  // in_proj columns per workgroup: whole groups of four
+constexpr int D_COLS = 10;            // out_proj columns per workgroup
+constexpr int D_THREADS = 64 * D_WAVES, BC_THREADS = 64 * BC_WAVES;
+static_assert(A_COLS % 4 == 0 && D_COLS % 2 == 0 && A_COLS / 4 <= 16 && D_COLS <= 16 && BC_THREADS / 4 <= 64, "codes leave in fours, halves in pairs");
+
+// What the kernel needs of one block; written to device memory by stack_begin_kernel.
+struct StackLayer {
+  const int8_t *W_in, *conv_w, *W_x, *W_dt, *A, *D, *W_outH;
+  const float *conv_b, *dt_bias;
+  const __half *norm_w;
+  float inv_s_u, m_in_x, m_in_z, s_cw, s_xpre, inv_s_x, m_x_dt, m_x_B, m_x_C, m_dt;
+  float s_x, s_dt, s_z, s_B, s_C, s_A, s_D, inv_s_y, m_out, pad;
+};
+constexpr int CHUNK_LAYERS = 22;  // descriptors handed over by value in one launch: 3.5 KB of kernel arguments
+struct LayerChunk {
+  StackLayer layer[CHUNK_LAYERS];
+};
+
+struct Words {  // tagged words, [M] rows each: residual stream, x codes, z codes, x_proj codes, gated scan output
+  u64 *s, *x, *z, *dbc, *g;
+  unsigned *ctrl;  // control words, one per 256 bytes
+};
+constexpr int CTRL_STRIDE = 64, CTRL_WORDS = 12;
+enum { C_SUB = 0 /* 8 sign-in counters */, C_TOP = 8, C_MODE = 9, C_TICKET = 10, C_DEAD = 11 };
+
+struct StackArgs {
+  const StackLayer *layers;
+  int n_layers, Dm, Di, R;
+  float eps;
+  float *ssm;
+  __half *conv;
+  Words w;
+  __half *out, *res;  // of the last block, for the final norm
+  int nA, nB, nC, nD;
+  int x_row, g_row;  // words of one row of x or z, of the gated output
+  int from_counter;
+};
+
+__device__ __forceinline__ u64 word_load(const u64 *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void word_store(u64 *p, unsigned payload, unsigned tag) {
+  __hip_atomic_store(p, (static_cast<u64>(tag) << 32) | payload, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ unsigned ctrl_load(const unsigned *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// A block's descriptor through scalar loads, its pointers as global ones (as generic ones every weight load would also count
+// as an LDS access).
+typedef __attribute__((address_space(4))) const StackLayer *LayerRef;
+__device__ __forceinline__ LayerRef layer_ref(const StackLayer *layers, int l) { return (LayerRef)(layers + l); }
+template <typename T>
+__device__ __forceinline__ T gload(const void *p) {
+  return *(__attribute__((address_space(1))) const T *)p;
+}
+typedef unsigned v2u __attribute__((ext_vector_type(2)));
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+// Where a word lies.  What one workgroup hands over is in 128-byte lines of its own: a line is written at one moment, so readers that have
+// polled it do not have to fetch it again for every neighbour's store.
+constexpr int LINE = 16;  // words
+__device__ __host__ __forceinline__ int quad_at(int quad) { return quad / (A_COLS / 4) * LINE + quad % (A_COLS / 4); }  // codes of x or z: four columns
+__device__ __host__ __forceinline__ int pair_at(int row, int pair) {  // residual stream: two columns
+  return pair / (D_COLS / 2) * LINE + row * (D_COLS / 2) + pair % (D_COLS / 2);
+}
+__device__ __host__ __forceinline__ int gate_at(int d) {  // gated output: channels d, d + 1
+  return d / (BC_THREADS / 4) * (2 * LINE) + d % (BC_THREADS / 4) / 2;
+}
+
+// Polls base[idx[j]] until all N words carry `tag`; the payloads are left in v.
+template <int N>
+__device__ __forceinline__ void wait_words(const u64 *base, const int (&idx)[N], unsigned tag, unsigned (&v)[N], unsigned *ctrl,
+                                           bool &dead) {
+  for (int tries = 0;; ++tries) {
+    u64 t[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) t[j] = word_load(base + idx[j]);
+    bool ok = true;
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      ok &= static_cast<unsigned>(t[j] >> 32) == tag;
+      v[j] = static_cast<unsigned>(t[j]);
+    }
+    if (ok) break;
+    if (dead || tries >= WAIT_TRIES) {
+      if (!dead) __hip_atomic_store(ctrl + C_DEAD * CTRL_STRIDE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      dead = true;
+      break;
+    }
+    __builtin_amdgcn_s_sleep(RETRY_PACE);
+  }
+}
+
+// What one wave of a role does for all of them before wait_words reads every word: it watches one of the awaited words, and before that,
+// at a slow pace, one word of the role in front.  All words of all waiting workgroups polled all the time keep the memory
+// side so busy that the stores they wait for hardly get through.
+__device__ __forceinline__ void wait_ahead(const u64 *front, unsigned front_tag, const u64 *word, unsigned tag, bool dead) {
+  int tries = 0;
+  if (front)
+    for (; static_cast<unsigned>(word_load(front) >> 32) != front_tag && !dead && tries < WAIT_TRIES; ++tries) __builtin_amdgcn_s_sleep(FRONT_PACE);
+  for (; static_cast<unsigned>(word_load(word) >> 32) != tag && !dead && tries < WAIT_TRIES; ++tries) __builtin_amdgcn_s_sleep(PACE);
+}
+
+// A scale read now: left to the compiler, the scalar load of a descriptor field lands where the value is needed, behind the waits.
+__device__ __forceinline__ float now(float f) {
+  asm volatile("" : "+s"(f));
+  return f;
+}
+
+// Barrier among the waves of one role: each adds one to an LDS counter that is never reset and waits for its target.
+struct RoleBarrier {
+  unsigned *count;
+  unsigned waves;
+  mutable unsigned target;
+  __device__ __forceinline__ void operator()() const {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    target += waves;
+    if ((threadIdx.x & 63) == 0) __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    while (static_cast<int>(__hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) - target) < 0) {
+    }
+    asm volatile("" ::: "memory");
+  }
+};
+
+// Weight loads are kept a few in flight per wave: all at once they queue in front of the hand-overs.
+__device__ __forceinline__ void throttle(int issued) {
+  if (issued % LOADS_IN_FLIGHT == LOADS_IN_FLIGHT - 1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
+// The thread and item index as values of this block only: hoisted out of the walk over the blocks, their addresses
+// would take more registers than the weights.
+__device__ __forceinline__ int fresh_tid(int first) {
+  int t = static_cast<int>(threadIdx.x) - first;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+__device__ __forceinline__ int fresh(int i) {
+  asm volatile("" : "+s"(i));
+  return i;
+}
+
+// Sum over the wave in the order of the shuffles lane ^ 32, ^ 16, ^ 8, ^ 4, ^ 2, ^ 1, without a trip through LDS for each.  After the first
+// three steps lanes that agree modulo 8 hold the same value, so a rotation by 4 inside a row is lane ^ 4.
+__device__ __forceinline__ float butterfly_sum(float v) {
+  auto both = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(both[0]) + __uint_as_float(both[1]);
+  both = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(both[0]) + __uint_as_float(both[1]);
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xf, 0xf, true));  // row_ror 8
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x124, 0xf, 0xf, true));  // row_ror 4
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xf, 0xf, true));   // quad_perm [2, 3, 0, 1]
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xf, 0xf, true));   // quad_perm [1, 0, 3, 2]
+  return v;
+}
+
+// Sums of N values per lane over the wave: lane j < N returns the sum of value j.
+template <int N>
+__device__ __forceinline__ int wave_sums(const int (&v)[N], int lane) {
+  int t[N];
+#pragma unroll
+  for (int j = 0; j < N; ++j) t[j] = v[j] + __builtin_amdgcn_update_dpp(0, v[j], 0xB1, 0xf, 0xf, true);  // quad_perm [1, 0, 3, 2]
+#pragma unroll
+  for (int j = 0; j < N; ++j) t[j] += __builtin_amdgcn_update_dpp(0, t[j], 0x4E, 0xf, 0xf, true);  // quad_perm [2, 3, 0, 1]
+#pragma unroll
+  for (int j = 0; j < N; ++j) t[j] += __builtin_amdgcn_update_dpp(0, t[j], 0x141, 0xf, 0xf, true);  // row_half_mirror
+#pragma unroll
+  for (int j = 0; j < N; ++j) t[j] += __builtin_amdgcn_update_dpp(0, t[j], 0x140, 0xf, 0xf, true);  // row_mirror
+  int mine = t[0];  // every lane of a row of 16 holds the row's sums
+#pragma unroll
+  for (int j = 1; j < N; ++j) mine = (lane & 15) == j ? t[j] : mine;
+  auto both = __builtin_amdgcn_permlane16_swap(static_cast<unsigned>(mine), static_cast<unsigned>(mine), false, false);
+  mine = static_cast<int>(both[0] + both[1]);
+  both = __builtin_amdgcn_permlane32_swap(static_cast<unsigned>(mine), static_cast<unsigned>(mine), false, false);
+  return static_cast<int>(both[0] + both[1]);
+}
+
+template <int MB>
+struct InShared {
+  __attribute__((aligned(16))) unsigned s[MB * PF * 512];
+  float part[4][MB];
+  int sums[MB][A_COLS];
+};
+
+// ---- role A: residual stream -> norm -> codes -> in_proj for A_COLS columns -> conv step on those of x
+template <int MB>
+__device__ __forceinline__ void role_in(const StackArgs &p, int l, int idx, int8_t *sA, InShared<MB> &sh, const RoleBarrier &sync,
+                                        bool &dead) {
+  const LayerRef q = layer_ref(p.layers, l);
+  idx = fresh(idx);
+  const int tid = fresh_tid(0), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int Dm = p.Dm, Di = p.Di, N = 2 * Di, nch = Dm / 16, groups = Dm / 8;
+  const int n0 = idx * A_COLS + wave * AC;
+  v4i w[PF][AC];
+#pragma unroll
+  for (int j = 0; j < AC; ++j)
+#pragma unroll
+    for (int r = 0; r < PF; ++r) {
+      w[r][j] = gload<v4i>(q->W_in + (size_t)min(n0 + j, N - 1) * Dm + min(lane + 64 * r, nch - 1) * 16);
+      throttle(j * PF + r);
+    }
+  // thread t of the first wave finishes columns 4 (t % quads) .. of row t / quads
+  constexpr int quads = A_COLS / 4;
+  const int fm = tid / quads, nq = idx * A_COLS + 4 * (tid % quads);
+  const bool fin = tid < MB * quads && nq < N, fin_x = fin && nq < Di;
+  v4u cw = {0u, 0u, 0u, 0u};
+  v4f cb = {0.f, 0.f, 0.f, 0.f};
+  ConvWindow4 win;
+  win.u[0] = win.u[1] = win.u[2] = make_uint2(0u, 0u);
+  uint2 *cs = reinterpret_cast<uint2 *>(p.conv + (((size_t)l * MB + (fin_x ? fm : 0)) * Di + (fin_x ? nq : 0)) * 3);
+  if (fin_x) {
+    cw = gload<v4u>(q->conv_w + (size_t)nq * 4);
+    cb = gload<v4f>(q->conv_b + nq);
+    win.u[0] = cs[0];
+    win.u[1] = cs[1];
+    win.u[2] = cs[2];
+  }
+  v4u nw[2] = {};
+  if (wave < 4) {
+#pragma unroll
+    for (int it = 0; it < 2; ++it) nw[it] = gload<v4u>(q->norm_w + (size_t)min(tid + it * 256, groups - 1) * 8);
+  }
+  const float inv_s_u = now(q->inv_s_u), m_in_x = now(q->m_in_x), m_in_z = now(q->m_in_z), s_cw = now(q->s_cw), s_xpre = now(q->s_xpre),
+              inv_s_x = now(q->inv_s_x);
+  if (wave == 0) wait_ahead(l ? p.w.g + idx % p.nC * (2 * LINE) : nullptr, l, p.w.s + idx * 37 % p.nD * LINE, l + 1, dead);
+  sync();
+  {  // the rows, as whole lines, into LDS
+    constexpr int NWORD = (MB * PF * 512 + 64 * A_WAVES - 1) / (64 * A_WAVES);
+    const int per_row = Dm / 2, words = MB * per_row;
+    int at[NWORD];
+    unsigned v[NWORD];
+#pragma unroll
+    for (int k = 0; k < NWORD; ++k) {
+      const int i = min(tid + 64 * A_WAVES * k, words - 1);
+      at[k] = pair_at(MB == 1 ? 0 : i / per_row, MB == 1 ? i : i % per_row);
+    }
+    wait_words(p.w.s, at, l + 1, v, p.w.ctrl, dead);
+#pragma unroll
+    for (int k = 0; k < NWORD; ++k)
+      if (tid + 64 * A_WAVES * k < words) sh.s[tid + 64 * A_WAVES * k] = v[k];
+  }
+  sync();
+  // the first four waves own groups of 8 halves (tid, tid + 256) of every row (a scalar branch: each wave passes one of the barriers)
+  if (wave < 4) {
+    uint4 keep[MB][2];
+    float ss[MB];
+#pragma unroll
+    for (int m = 0; m < MB; ++m) {
+      ss[m] = 0.f;
+#pragma unroll
+      for (int it = 0; it < 2; ++it) {
+        if (tid + it * 256 < groups) {
+          union {
+            uint4 u;
+            __half h[8];
+          } r;
+          r.u = *reinterpret_cast<const uint4 *>(sh.s + m * (Dm / 2) + (tid + it * 256) * 4);
+          keep[m][it] = r.u;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const float f = __half2float(r.h[e]);
+            ss[m] += f * f;
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int m = 0; m < MB; ++m) {
+      const float t = butterfly_sum(ss[m]);
+      if (lane == 0) sh.part[wave][m] = t;
+    }
+    sync();
+    float rinv[MB];
+#pragma unroll
+    for (int m = 0; m < MB; ++m)
+      rinv[m] = 1.f / sqrtf((sh.part[0][m] + sh.part[1][m] + sh.part[2][m] + sh.part[3][m]) / static_cast<float>(Dm) + p.eps);
+#pragma unroll
+    for (int it = 0; it < 2; ++it) {
+      const int g = tid + it * 256;
+      if (g < groups) {
+#pragma unroll
+        for (int m = 0; m < MB; ++m) {
+          union {
+            uint4 u;
+            __half h[8];
+          } r, wv;
+          r.u = keep[m][it];
+          wv.u = make_uint4(nw[it][0], nw[it][1], nw[it][2], nw[it][3]);
+          float v[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) v[e] = __half2float(r.h[e]) * rinv[m] * __half2float(wv.h[e]) * inv_s_u;
+          *reinterpret_cast<uint2 *>(sA + (size_t)m * Dm + (size_t)g * 8) =
+              make_uint2(pack_q8x4(v[0], v[1], v[2], v[3]), pack_q8x4(v[4], v[5], v[6], v[7]));
+        }
+      }
+    }
+  } else {
+    sync();
+  }
+  sync();
+  int acc[MB][AC];
+#pragma unroll
+  for (int m = 0; m < MB; ++m)
+#pragma unroll
+    for (int j = 0; j < AC; ++j) acc[m][j] = 0;
+#pragma unroll
+  for (int r = 0; r < PF; ++r)
+    if (lane + 64 * r < nch) {
+#pragma unroll
+      for (int m = 0; m < MB; ++m) {
+        const v4i a = *reinterpret_cast<const v4i *>(sA + (size_t)m * Dm + (lane + 64 * r) * 16);
+#pragma unroll
+        for (int j = 0; j < AC; ++j)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[m][j] = __builtin_amdgcn_sdot4(a[e], w[r][j][e], acc[m][j], false);
+      }
+    }
+#pragma unroll
+  for (int m = 0; m < MB; ++m) {
+    const int mine = wave_sums<AC>(acc[m], lane);
+    if (lane < AC) sh.sums[m][wave * AC + lane] = mine;
+  }
+  sync();
+  if (fin) {
+    int a4[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) a4[j] = sh.sums[fm][4 * (tid % quads) + j];
+    if (fin_x) {
+      const unsigned xpre = requant_pack4(a4, m_in_x);
+      float sv[4];
+      conv_step4_core(xpre, make_uint4(cw[0], cw[1], cw[2], cw[3]), make_float4(cb[0], cb[1], cb[2], cb[3]), win, s_cw, s_xpre, sv);
+      word_store(p.w.x + fm * p.x_row + quad_at(nq / 4),
+                 pack_q8x4(sv[0] * inv_s_x, sv[1] * inv_s_x, sv[2] * inv_s_x, sv[3] * inv_s_x), l + 1);
+      cs[0] = win.u[0];
+      cs[1] = win.u[1];
+      cs[2] = win.u[2];
+    } else {
+      word_store(p.w.z + fm * p.x_row + quad_at((nq - Di) / 4), requant_pack4(a4, m_in_z), l + 1);
+    }
+  }
+}
+
+// ---- role B: x_proj for four columns; the threads split K in 16-byte pieces
+template <int n, int MB>
+__device__ __forceinline__ void role_x(const StackArgs &p, int l, int idx, int8_t *sx, int (*red)[MB * 4], const RoleBarrier &sync, bool &dead) {
+  const LayerRef q = layer_ref(p.layers, l);
+  idx = fresh(idx);
+  const int tid = fresh_tid(64 * (A_WAVES + D_WAVES)), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  constexpr int nch = n / 16, ROUNDS = (nch + BC_THREADS - 1) / BC_THREADS;
+  const int n0 = idx * 4;
+  v4i w[ROUNDS][4];
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) w[r][j] = gload<v4i>(q->W_x + (size_t)(n0 + j) * n + min(tid + BC_THREADS * r, nch - 1) * 16);
+  const float m_x = now(n0 < p.R ? q->m_x_dt : (n0 < p.R + NS ? q->m_x_B : q->m_x_C));
+  if (wave == 0) wait_ahead(p.w.s + idx * LINE, l + 1, p.w.x + quad_at(idx * 37 % (n / 4)), l + 1, dead);
+  sync();
+  constexpr int NWORD = (n / 4 + BC_THREADS - 1) / BC_THREADS;
+#pragma unroll
+  for (int m = 0; m < MB; ++m) {
+    int at[NWORD];
+    unsigned v[NWORD];
+#pragma unroll
+    for (int k = 0; k < NWORD; ++k) at[k] = m * p.x_row + quad_at(min(tid + BC_THREADS * k, n / 4 - 1));
+    wait_words(p.w.x, at, l + 1, v, p.w.ctrl, dead);
+#pragma unroll
+    for (int k = 0; k < NWORD; ++k)
+      if (tid + BC_THREADS * k < n / 4) reinterpret_cast<unsigned *>(sx)[m * (n / 4) + tid + BC_THREADS * k] = v[k];
+  }
+  sync();
+#pragma unroll
+  for (int m = 0; m < MB; ++m) {
+    v4i a[ROUNDS];
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) a[r] = *reinterpret_cast<const v4i *>(sx + m * n + min(tid + BC_THREADS * r, nch - 1) * 16);
+    int dots[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      dots[j] = 0;
+#pragma unroll
+      for (int r = 0; r < ROUNDS; ++r)
+        if (tid + BC_THREADS * r < nch) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) dots[j] = __builtin_amdgcn_sdot4(a[r][e], w[r][j][e], dots[j], false);
+        }
+    }
+    const int mine = wave_sums<4>(dots, lane);
+    if (lane < 4) red[wave][m * 4 + lane] = mine;
+  }
+  sync();
+  if (tid < MB) {
+    int a[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int wv = 0; wv < BC_WAVES; ++wv)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) a[j] += red[wv][tid * 4 + j];
+    word_store(p.w.dbc + idx * LINE + tid, requant_pack4(a, m_x), l + 1);
+  }
+}
+
+// softplus and gate as the scan kernels form them
+__device__ __forceinline__ float softplus_f(float v) {
+  const float e = __builtin_amdgcn_exp2f(-fabsf(v) * LOG2E);
+  const float w = 1.f + e;
+  const float c = (w - 1.f) - e;
+  return fmaxf(v, 0.f) + __builtin_fmaf(__builtin_amdgcn_logf(w), LN2, -c);
+}
+__device__ __forceinline__ float silu_gate(float y, float z) {
+  return y * z * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-z * LOG2E));
+}
+
+// ---- role C: one step of the scan with dt_proj inside, four lanes per channel, which walk the sequences
+template <int Di, int MB>
+__device__ __forceinline__ void role_scan(const StackArgs &p, int l, int idx, int8_t *sdbc, const RoleBarrier &sync, bool &dead) {
+  const LayerRef q = layer_ref(p.layers, l);
+  idx = fresh(idx);
+  const int tid = fresh_tid(64 * (A_WAVES + D_WAVES));
+  const int R = p.R, NX = R + 2 * NS;
+  const int gid = idx * BC_THREADS + tid;
+  const bool live = gid < Di * 4;
+  const int id = live ? gid : Di * 4 - 1;
+  const int quad = id & 3, d = id >> 2;
+  float *hp = p.ssm + (size_t)l * MB * Di * NS + (size_t)id * 4;
+  float4 hv[MB];
+#pragma unroll
+  for (int m = 0; m < MB; ++m) hv[m] = *reinterpret_cast<const float4 *>(hp + (size_t)m * Di * NS);
+  const unsigned aw = gload<unsigned>(q->A + (size_t)d * NS + 4 * quad);
+  const float bias = gload<float>(q->dt_bias + d);
+  const float Dq = static_cast<float>(gload<signed char>(q->D + d));
+  v4i w[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int kc = 16 * quad + 64 * j;
+    w[j] = v4i{0, 0, 0, 0};
+    if (kc < R) w[j] = gload<v4i>(q->W_dt + (size_t)d * R + kc);
+  }
+  const float m_dt = now(q->m_dt), s_x = now(q->s_x), s_dt = now(q->s_dt), s_z = now(q->s_z), s_B = now(q->s_B), s_C = now(q->s_C),
+              s_A = now(q->s_A), s_D = now(q->s_D);
+  if (tid < 64) wait_ahead(p.w.x + quad_at(idx), l + 1, p.w.dbc + idx % p.nB * LINE, l + 1, dead);
+  sync();
+  unsigned xw[MB], zw[MB];
+  {
+    int at[MB];
+#pragma unroll
+    for (int m = 0; m < MB; ++m) at[m] = m * p.x_row + quad_at(d / 4);
+    wait_words(p.w.x, at, l + 1, xw, p.w.ctrl, dead);
+    wait_words(p.w.z, at, l + 1, zw, p.w.ctrl, dead);
+  }
+  for (int i = tid; i < MB * (NX / 4); i += BC_THREADS) {
+    const int at[1] = {i % (NX / 4) * LINE + i / (NX / 4)};
+    unsigned dw[1];
+    wait_words(p.w.dbc, at, l + 1, dw, p.w.ctrl, dead);
+    reinterpret_cast<unsigned *>(sdbc)[i] = dw[0];
+  }
+  sync();
+  const int sh = 8 * (d & 3);
+#pragma unroll
+  for (int m = 0; m < MB; ++m) {
+    const int8_t *row = sdbc + m * NX;
+    int acc = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int kc = 16 * quad + 64 * j;
+      if (kc < R) {
+        const v4i a = *reinterpret_cast<const v4i *>(row + kc);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_sdot4(a[e], w[j][e], acc, false);
+      }
+    }
+    const unsigned bw = *reinterpret_cast<const unsigned *>(row + R + 4 * quad);
+    const unsigned cw = *reinterpret_cast<const unsigned *>(row + R + NS + 4 * quad);
+    acc += __builtin_amdgcn_update_dpp(0, acc, 0xB1, 0xf, 0xf, true);  // quad_perm [1, 0, 3, 2]
+    acc += __builtin_amdgcn_update_dpp(0, acc, 0x4E, 0xf, 0xf, true);  // quad_perm [2, 3, 0, 1]
+    const int dtq = static_cast<int>(__builtin_rintf(__builtin_amdgcn_fmed3f(static_cast<float>(acc) * m_dt, -128.f, 127.f)));
+    const float xv = __builtin_fmaf(s_x, static_cast<float>(static_cast<int8_t>(xw[m] >> sh)), -0.f);
+    const float dt = softplus_f(s_dt * static_cast<float>(dtq) + bias);
+    const float zv = s_z * static_cast<float>(static_cast<int8_t>(zw[m] >> sh));
+    const float u = dt * xv;
+    float h[4] = {hv[m].x, hv[m].y, hv[m].z, hv[m].w};
+    float y = 0.f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float a2 = static_cast<float>(static_cast<int8_t>(aw >> (8 * j))) * (s_A * LOG2E);
+      const float Bv = s_B * static_cast<float>(static_cast<int8_t>(bw >> (8 * j)));
+      const float Cv = s_C * static_cast<float>(static_cast<int8_t>(cw >> (8 * j)));
+      h[j] = __builtin_fmaf(__builtin_amdgcn_exp2f(dt * a2), h[j], u * Bv);
+      y = __builtin_fmaf(Cv, h[j], y);
+    }
+    y += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(y), 0xB1, 0xf, 0xf, true));
+    y += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(y), 0x4E, 0xf, 0xf, true));
+    y = __builtin_fmaf(s_D * Dq, xv, y);
+    const unsigned g = __half_as_ushort(__float2half_rn(silu_gate(y, zv)));
+    // the neighbouring channel's (lane ^ 4, at lanes that are multiples of 8: four lanes up the row)
+    const unsigned g1 = static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(g), 0x104, 0xf, 0xf, true));  // row_shl 4
+    if (live) {
+      if ((tid & 7) == 0) word_store(p.w.g + m * p.g_row + gate_at(d), g | (g1 << 16), l + 1);
+      *reinterpret_cast<float4 *>(hp + (size_t)m * Di * NS) = make_float4(h[0], h[1], h[2], h[3]);
+    }
+  }
+}
+
+// ---- role D: Hadamard + quantization of every row (each workgroup for itself), out_proj for D_COLS columns, residual add
+template <int K, int LOGM, int MB>
+__device__ __forceinline__ void role_out(const StackArgs &p, int l, int idx, float *row, int (*red)[MB * D_COLS],
+                                         const RoleBarrier &sync, bool &dead) {
+  const LayerRef q = layer_ref(p.layers, l);
+  idx = fresh(idx);
+  const int tid = fresh_tid(64 * A_WAVES), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  constexpr int n = K << LOGM, NT = D_THREADS;
+  const int Dm = p.Dm, n0 = idx * D_COLS;
+  const bool item_live = n / 16 == NT || tid < n / 16;
+  const int item = item_live ? tid : n / 16 - 1;
+  v4i wv[D_COLS];
+#pragma unroll
+  for (int j = 0; j < D_COLS; ++j) {
+    wv[j] = gload<v4i>(q->W_outH + (size_t)min(n0 + j, Dm - 1) * n + (size_t)item * 16);
+    throttle(j);
+  }
+  OrderK hk;
+  if constexpr (K > 1) {
+    hk = order_k_operands<K, false>(lane);
+    asm volatile("" : "+v"(hk.f[0]), "+v"(hk.f[1]));  // (read now, not behind the wait)
+  }
+  const float inv_s_y = now(q->inv_s_y), m_out = now(q->m_out);
+  // thread t finishes output n0 + t % D_COLS of row t / D_COLS (Dm and D_COLS are even: a pair of outputs is all in or all out)
+  const int fr = tid / D_COLS, fc = n0 + tid % D_COLS;
+  const bool fin = tid < MB * D_COLS && fc < Dm;
+  const int s_at[1] = {pair_at(fr, fc / 2)};
+  unsigned res[1] = {0};
+  if (fin) wait_words(p.w.s, s_at, l + 1, res, p.w.ctrl, dead);
+  // where this thread's words lie and go: formed now, not behind the wait
+  int at[(n / 2 + NT - 1) / NT], to[(n / 2 + NT - 1) / NT];
+#pragma unroll
+  for (int k = 0; k < (n / 2 + NT - 1) / NT; ++k) {
+    const int i = 2 * min(tid + NT * k, n / 2 - 1);
+    at[k] = gate_at(i);
+    if constexpr (K > 1) to[k] = static_cast<int>(reinterpret_cast<char *>(half_slot<K, LOGM>(row, i)) - reinterpret_cast<char *>(row));
+    else to[k] = pad(i) * 4;
+    asm volatile("" : "+v"(at[k]), "+v"(to[k]));
+  }
+  if (wave == 0) wait_ahead(p.w.dbc + idx % p.nB * LINE, l + 1, p.w.g + idx * 37 % p.nC * (2 * LINE), l + 1, dead);
+  sync();
+#pragma unroll
+  for (int r = 0; r < MB; ++r) {
+    if (r > 0) sync();  // the row in front has been read
+    constexpr int NWORD = (n / 2 + NT - 1) / NT;
+    unsigned g[NWORD];
+#pragma unroll
+    for (int k = 0; k < NWORD; ++k) at[k] += r ? p.g_row : 0;
+    wait_words(p.w.g, at, l + 1, g, p.w.ctrl, dead);
+#pragma unroll
+    for (int k = 0; k < NWORD; ++k)
+      if (tid + NT * k < n / 2) {
+        if constexpr (K > 1) {
+          *reinterpret_cast<unsigned *>(reinterpret_cast<char *>(row) + to[k]) = g[k];
+        } else {
+          float *dst = reinterpret_cast<float *>(reinterpret_cast<char *>(row) + to[k]);
+          dst[0] = __half2float(__ushort_as_half(static_cast<unsigned short>(g[k] & 0xffffu)));
+          dst[1] = __half2float(__ushort_as_half(static_cast<unsigned short>(g[k] >> 16)));
+        }
+      }
+    if constexpr (K > 1) order_k_mfma<K, LOGM, NT>(row, tid, hk, sync);
+    else sync();
+    high_passes<K, LOGM, NT>(row, tid, sync);
+    float v[16];
+    last_pass(row, item, v);
+    v4i c;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      c[k] = static_cast<int>(pack_q8x4(v[4 * k] * inv_s_y, v[4 * k + 1] * inv_s_y, v[4 * k + 2] * inv_s_y, v[4 * k + 3] * inv_s_y));
+    if (!item_live) c = v4i{0, 0, 0, 0};
+    int dots[D_COLS];
+#pragma unroll
+    for (int j = 0; j < D_COLS; ++j) {
+      dots[j] = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) dots[j] = __builtin_amdgcn_sdot4(c[e], wv[j][e], dots[j], false);
+    }
+    const int mine = wave_sums<D_COLS>(dots, lane);
+    if (lane < D_COLS) red[wave][r * D_COLS + lane] = mine;
+  }
+  sync();
+  if (fin) {
+    int a = 0;
+#pragma unroll
+    for (int w = 0; w < D_WAVES; ++w) a += red[w][tid];
+    float y = static_cast<float>(a) * m_out;
+    // one rounding from product to half for the orders whose items fill whole waves, two for the others, as
+    // hadamard_out_proj_kernel has it
+    if constexpr (threads_for(n) != n / 16) asm volatile("" : "+v"(y));
+    __half o = __float2half_rn(y);
+    const __half rh = __ushort_as_half(static_cast<unsigned short>((fc & 1) ? res[0] >> 16 : res[0] & 0xffffu));
+    if (l + 1 == p.n_layers) {
+      if (dead || ctrl_load(p.w.ctrl + C_DEAD * CTRL_STRIDE)) o = __ushort_as_half(static_cast<unsigned short>(0x7e00));
+      p.out[(size_t)fr * Dm + fc] = o;
+      p.res[(size_t)fr * Dm + fc] = rh;
+    } else {
+      const unsigned t = __half_as_ushort(__float2half_rn(__half2float(o) + __half2float(rh)));
+      const unsigned t1 = __shfl_down(t, 1);
+      if ((fc & 1) == 0) word_store(p.w.s + s_at[0], t | (t1 << 16), l + 2);
+    }
+  }
+}
+
+template <int K, int LOGM, int MB>
+__global__ __launch_bounds__(STACK_THREADS) void decode_stack_kernel(StackArgs p) {
+  constexpr int n = K << LOGM;
+  extern __shared__ __attribute__((aligned(16))) float row[];          // role D's row
+  __shared__ __attribute__((aligned(16))) int8_t sA[MB * PF * 1024];    // role A's codes
+  __shared__ InShared<MB> sIn;
+  __shared__ __attribute__((aligned(16))) int8_t sx[MB * n];            // role B's codes
+  __shared__ __attribute__((aligned(16))) int8_t sdbc[MB * (256 + 2 * NS)];
+  __shared__ int red_x[BC_WAVES][MB * 4], red_out[D_WAVES][MB * D_COLS];
+  __shared__ unsigned count[3];
+  __shared__ int s_word;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int G = gridDim.x;
+  unsigned *ctrl = p.w.ctrl;
+  bool dead = false;
+  if (tid < 3) count[tid] = 0;
+  if (tid == 0) {
+    unsigned mode = 2;
+    if (!p.from_counter) {
+      // sign in: eight counters by workgroup index, their last arrivals in a ninth
+      const int sub = blockIdx.x & 7, members = (G - sub + 7) / 8, subs = min(G, 8);
+      if (__hip_atomic_fetch_add(ctrl + (C_SUB + sub) * CTRL_STRIDE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == (unsigned)members &&
+          __hip_atomic_fetch_add(ctrl + C_TOP * CTRL_STRIDE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == (unsigned)subs)
+        atomicCAS(ctrl + C_MODE * CTRL_STRIDE, 0u, 1u);
+      for (int tries = 0; (mode = ctrl_load(ctrl + C_MODE * CTRL_STRIDE)) == 0; ++tries)
+        if (tries >= SIGN_IN_TRIES) {
+          const unsigned was = atomicCAS(ctrl + C_MODE * CTRL_STRIDE, 0u, 2u);
+          mode = was == 0 ? 2u : was;
+          break;
+        }
+    }
+    s_word = (int)mode;
+  }
+  __syncthreads();
+  const bool resident = s_word == 1;
+  const int role = wave < A_WAVES ? 0 : (wave < A_WAVES + D_WAVES ? 1 : 2);
+  const RoleBarrier sync{&count[role], static_cast<unsigned>(role == 0 ? A_WAVES : (role == 1 ? D_WAVES : BC_WAVES)), 0u};
+  const int per_block = p.nA + p.nB + p.nC + p.nD;
+  // resident: this workgroup's item of each role for every block, each role's waves at their own pace
+  const int blk = blockIdx.x;
+  int l = 0, item_a = blk < p.nA ? blk : -1, item_d = blk < p.nD ? blk : -1, item_x = blk < p.nB ? blk : -1,
+      item_c = blk >= p.nB && blk < p.nB + p.nC ? blk - p.nB : -1;
+  for (;; ++l) {
+    if (!resident) {  // one item of one role at a time
+      __syncthreads();
+      if (tid == 0) s_word = (int)__hip_atomic_fetch_add(ctrl + C_TICKET * CTRL_STRIDE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __syncthreads();
+      const int ticket = __builtin_amdgcn_readfirstlane(s_word);
+      l = ticket / per_block;
+      int r = ticket % per_block;
+      item_a = r < p.nA ? r : -1;
+      r -= p.nA;
+      item_x = r >= 0 && r < p.nB ? r : -1;
+      r -= p.nB;
+      item_c = r >= 0 && r < p.nC ? r : -1;
+      r -= p.nC;
+      item_d = r;
+    }
+    if (l >= p.n_layers) break;
+    if (role == 0) {
+      if (item_a >= 0) role_in<MB>(p, l, item_a, sA, sIn, sync, dead);
+    } else if (role == 1) {
+      if (item_d >= 0) role_out<K, LOGM, MB>(p, l, item_d, row, red_out, sync, dead);
+    } else if (item_x >= 0) {
+      role_x<n, MB>(p, l, item_x, sx, red_x, sync, dead);
+    } else if (item_c >= 0) {
+      role_scan<n, MB>(p, l, item_c, sdbc, sync, dead);
+    }
+  }
+}
+
+// Descriptors of up to CHUNK_LAYERS blocks; the first launch also sets up the words: the residual stream of block 0 is the embedding
+// of the token (plus zero, as the first add of the separate kernels has it), all other words and the control words zero.
+__global__ __launch_bounds__(256) void stack_begin_kernel(LayerChunk chunk, StackLayer *dst, int count, const __half *E,
+                                                          const int32_t *tokens, int M, int Dm, int vocab, Words w, u64 *clear,
+                                                          unsigned n_clear) {
+  if (blockIdx.x == 0) {
+    // (read through the argument segment: indexing the by-value struct would copy it to scratch first)
+    typedef __attribute__((address_space(4))) const unsigned *args_t;
+    const args_t src = (args_t)__builtin_amdgcn_kernarg_segment_ptr();
+    for (int i = threadIdx.x; i < count * (int)(sizeof(StackLayer) / 4); i += 256) reinterpret_cast<unsigned *>(dst)[i] = src[i];
+  }
+  if (!E) return;
+  const unsigned i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n_clear) clear[i] = 0;
+  const unsigned per = Dm / 2;
+  if (i < M * per) {
+    const int m = i / per, c = i % per;
+    const int tok = min(max(tokens[m], 0), vocab - 1);
+    const __half2 e = reinterpret_cast<const __half2 *>(E + (size_t)tok * Dm)[c];
+    const unsigned lo = __half_as_ushort(__float2half_rn(0.f + __half2float(__low2half(e))));
+    const unsigned hi = __half_as_ushort(__float2half_rn(0.f + __half2float(__high2half(e))));
+    w.s[pair_at(m, c)] = (1ull << 32) | lo | (hi << 16);
+  }
+}
+
+struct StackCarve {
+  size_t layers, s, x, z, dbc, g, ctrl, total;
+};
+int stack_x_row(int Di) { return ((Di / 4 + A_COLS / 4 - 1) / (A_COLS / 4)) * LINE; }
+int stack_g_row(int Di) { return (Di + BC_THREADS / 4 - 1) / (BC_THREADS / 4) * 2 * LINE; }
+StackCarve stack_carve(int n_layers, int M, int Dm, int Di, int R) {
+  StackCarve c{};
+  size_t off = 0;
+  auto take = [&](size_t bytes) {
+    const size_t at = off;
+    off += align_up(bytes, 256);
+    return at;
+  };
+  c.layers = take((size_t)n_layers * sizeof(StackLayer));
+  c.s = take((size_t)((Dm + D_COLS - 1) / D_COLS) * LINE * 8);
+  c.x = take((size_t)M * stack_x_row(Di) * 8);  // from here on cleared
+  c.z = take((size_t)M * stack_x_row(Di) * 8);
+  c.dbc = take((size_t)(R + 2 * NS) / 4 * LINE * 8);
+  c.g = take((size_t)M * stack_g_row(Di) * 8);
+  c.ctrl = take((size_t)CTRL_WORDS * CTRL_STRIDE * 4);
+  c.total = off;
+  return c;
+}
+
+// Does the current device hold `groups` workgroups of this kernel at once (as far as the runtime can tell)?
+template <int K, int LOGM, int MB>
+bool fits(int groups, size_t lds) {
+  static std::atomic<int> known[64];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return false;
+  std::atomic<int> &slot = known[dev & 63];
+  int v = slot.load(std::memory_order_relaxed);
+  if (v == 0) {
+    int per_cu = 0, cus = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_stack_kernel<K, LOGM, MB>, STACK_THREADS, lds) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+      return false;
+    v = per_cu * cus;
+    slot.store(v, std::memory_order_relaxed);
+  }
+  return groups <= v;
+}
+
+template <int K, int LOGM, int MB, typename Begin>
+int run_stack(const StackArgs &args, const Begin &begin, bool *served, hipStream_t st) {
+  constexpr int n = K << LOGM;
+  StackArgs p = args;
+  p.nA = (2 * p.Di + A_COLS - 1) / A_COLS;
+  p.nB = (p.R + 2 * NS) / 4;
+  p.nC = (p.Di * 4 + BC_THREADS - 1) / BC_THREADS;
+  p.nD = (p.Dm + D_COLS - 1) / D_COLS;
+  p.x_row = stack_x_row(n);
+  p.g_row = stack_g_row(n);
+  const int G = std::max(std::max(p.nA, p.nD), p.nB + p.nC);
+  const size_t lds = (size_t)(n + n / 4) * sizeof(float);
+  *served = fits<K, LOGM, MB>(G, lds);
+  if (!*served) return QUAMBA_OK;
+  const int rc = begin();
+  if (rc != QUAMBA_OK) return rc;
+  hipLaunchKernelGGL((decode_stack_kernel<K, LOGM, MB>), dim3(G), dim3(STACK_THREADS), lds, st, p);
+  QUAMBA_LAUNCH_CHECK();
+  return QUAMBA_OK;
+}
+
+}  // namespace
+
+// All blocks of a generation step from tokens [Bt]; leaves the last block's output and the residual stream before its add in `out`
+// and `res`, the states advanced.  *served = false (and nothing launched): the general path has to run.
+int launch_decode_stack(const quamba_model *m, const int32_t *tokens, int Bt, float *ssm, __half *conv, __half *out, __half *res,
+                        void *ws, size_t ws_bytes, hipStream_t st, bool *served) {
+  *served = false;
+  const int hook = g_decode_stack_hook.load(std::memory_order_relaxed);
+  const int Dm = m->dims.d_model, Di = m->dims.d_inner, R = m->dims.dt_rank;
+  // (one block alone: no weights to read ahead)
+  if (hook == 1 || Bt < 1 || Bt > 2 || m->n_layers < 2 || Dm > PF * 1024 || R > 256) return QUAMBA_OK;
+  int k = 0, lm = 0;
+  if (!hadamard_factor(Di, &k, &lm)) return QUAMBA_OK;
+  const StackCarve c = stack_carve(m->n_layers, Bt, Dm, Di, R);
+  if (c.total > ws_bytes || (long long)m->n_layers * 4096 > 0x7fffffffLL) return QUAMBA_OK;
+  char *base = static_cast<char *>(ws);
+  StackArgs a{};
+  a.layers = reinterpret_cast<const StackLayer *>(base + c.layers);
+  a.n_layers = m->n_layers; a.Dm = Dm; a.Di = Di; a.R = R; a.eps = m->eps;
+  a.ssm = ssm; a.conv = conv; a.out = out; a.res = res;
+  auto words = [&](size_t at) { return reinterpret_cast<u64 *>(base + at); };
+  a.w = Words{words(c.s), words(c.x), words(c.z), words(c.dbc), words(c.g), reinterpret_cast<unsigned *>(base + c.ctrl)};
+  a.from_counter = hook == 2;
+  auto begin = [&]() -> int {
+    for (int l0 = 0; l0 < m->n_layers; l0 += CHUNK_LAYERS) {
+      LayerChunk chunk{};
+      const int count = m->n_layers - l0 < CHUNK_LAYERS ? m->n_layers - l0 : CHUNK_LAYERS;
+      for (int i = 0; i < count; ++i) {
+        const quamba_layer &ly = m->layers[l0 + i];
+        const quamba_scales &s = ly.s;
+        chunk.layer[i] = StackLayer{ly.q.W_in, ly.q.conv_w, ly.q.W_x, ly.q.W_dt, ly.q.A, ly.q.D, ly.q.W_outH, ly.q.conv_b, ly.q.dt_bias,
+                                    reinterpret_cast<const __half *>(ly.norm_w), s.inv_s_u, s.m_in_x, s.m_in_z, s.s_cw, s.s_xpre,
+                                    s.inv_s_x, s.m_x_dt, s.m_x_B, s.m_x_C, s.m_dt, s.s_x, s.s_dt, s.s_z, s.s_B, s.s_C, s.s_A, s.s_D,
+                                    s.inv_s_y, s.m_out, 0.f};
+      }
+      const unsigned n_clear = l0 ? 0u : (unsigned)((c.total - c.x) / 8);
+      const unsigned n = l0 ? 1u : std::max<unsigned>(n_clear, (unsigned)(Bt * Dm / 2));
+      hipLaunchKernelGGL(stack_begin_kernel, dim3((n + 255) / 256), dim3(256), 0, st, chunk,
+                         const_cast<StackLayer *>(a.layers) + l0, count,
+                         l0 ? nullptr : reinterpret_cast<const __half *>(m->embedding), tokens, Bt, Dm, m->vocab, a.w, words(c.x), n_clear);
+      QUAMBA_LAUNCH_CHECK();
+    }
+    return QUAMBA_OK;
+  };
+#define QUAMBA_CASE(KK, LM)                                                                         \
+  if (k == KK && lm == LM) return Bt == 1 ? run_stack<KK, LM, 1>(a, begin, served, st) : run_stack<KK, LM, 2>(a, begin, served, st);
+  QUAMBA_CASE(12, 7) QUAMBA_CASE(1, 11) QUAMBA_CASE(20, 7) QUAMBA_CASE(12, 8) QUAMBA_CASE(1, 12) QUAMBA_CASE(20, 8)
+#undef QUAMBA_CASE
+  return QUAMBA_OK;
+}
+
+}  // namespace quamba
+
+extern "C" void quamba_debug_set_decode_stack(int v) { quamba::g_decode_stack_hook.store(v); }

@@ -357,19 +357,31 @@ int run_model(const quamba_model *m, const int32_t *tokens, int Bt, int L, bool 
   int32_t *pidx = next ? reinterpret_cast<int32_t *>(base + c.pidx) : nullptr;
   int32_t *step = reinterpret_cast<int32_t *>(base + c.step);
 
-  const size_t pieces = (size_t)M * (Dm / 8);
-  hipLaunchKernelGGL(embed_kernel, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, st,
-                     reinterpret_cast<const __half *>(m->embedding), tokens, M,
-                     Dm, m->vocab, res, out);
-  QUAMBA_LAUNCH_CHECK();
+  // generation with one or two sequences: all blocks in one launch
+  const bool fused = decode && mixer_decode_norm_available(&m->dims, Bt);
+  bool stacked = false;
+  if (fused && mixer_decode_fuses_dt()) {
+    for (int l = 0; l < m->n_layers; ++l) {
+      const int rc = check_model_layer(&m->layers[l].q, &m->layers[l].s);
+      if (rc != QUAMBA_OK) return rc;
+    }
+    const int rc = launch_decode_stack(m, tokens, Bt, ssm_states, conv_states, out, res, base + c.mixer, c.mixer_bytes, st, &stacked);
+    if (rc != QUAMBA_OK) return rc;
+  }
+  if (!stacked) {
+    const size_t pieces = (size_t)M * (Dm / 8);
+    hipLaunchKernelGGL(embed_kernel, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, st,
+                       reinterpret_cast<const __half *>(m->embedding), tokens, M,
+                       Dm, m->vocab, res, out);
+    QUAMBA_LAUNCH_CHECK();
+  }
   // generation with at most 4 sequences: the add + norm + quantization runs inside each block's first
   // kernel, which reads one residual buffer and writes the other
-  const bool fused = decode && mixer_decode_norm_available(&m->dims, Bt);
   __half *res_other = reinterpret_cast<__half *>(base + c.res2);
   // generation with more sequences: where out_proj splits K over the grid, the next block's add + norm +
   // quantization adds up the partial sums (the last block's output is stored as usual for the final norm)
   OutPartial prev{false, 1, nullptr, 0.f};
-  for (int l = 0; l < m->n_layers; ++l) {
+  for (int l = 0; !stacked && l < m->n_layers; ++l) {
     const quamba_layer &ly = m->layers[l];
     float *ssm = ssm_states + (size_t)l * Bt * Di * N;
     __half *cs = conv_states + (size_t)l * Bt * Di * 3;

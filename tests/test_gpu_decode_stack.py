@@ -1,0 +1,129 @@
+"""Generation of a stack in one launch: the bits of the launch-by-launch form, at the edges of its column groups and widths, with its
+work items kept or taken from the counter, replayed from a graph, and with two steps in flight at once."""
+import pytest
+import torch
+
+import paper_2410_13229_amd as Q
+import workloads as W
+from gpu_util import empty, workspace
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+VOCAB = 97
+
+
+def _model(Dm, Di, R, n_layers, seed):
+    """A calibrated stack with random weights, everything on the GPU."""
+    d = W.tiny_config(name="stack", d_model=Dm, d_inner=Di, dt_rank=R, batch=1, seqlen=1, config_id=97)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+
+    def normal(*shape):
+        return torch.randn(shape, generator=g, device=DEV)
+
+    E, norms = (normal(VOCAB, Dm) * 0.5).half(), (1 + 0.1 * normal(n_layers + 1, Dm)).half()
+    nb, Lc, layers = 1, 24, []
+    res = E[torch.randint(0, VOCAB, (nb * Lc,), generator=g, device=DEV)].float()
+    out, ws = torch.zeros_like(res), workspace(Q.quamba_calibrate_workspace_bytes(d, nb, Lc))
+    for i in range(n_layers):
+        fw = {"W_in": normal(2 * Di, Dm) * Dm ** -0.5, "conv_w": normal(Di, 4) * 0.5, "conv_b": normal(Di) * 0.1,
+              "W_x": normal(R + 32, Di) * Di ** -0.5, "W_dt": normal(Di, R) * R ** -0.5, "dt_bias": normal(Di) - 3.0,
+              "A_log": torch.log(torch.arange(1, 17, device=DEV, dtype=torch.float32)).repeat(Di, 1), "D": normal(Di),
+              "W_out": normal(Dm, Di) * Di ** -0.5}
+        q = {k: torch.empty(s, dtype=torch.int8, device=DEV)
+             for k, s in {"W_in": (2 * Di, Dm), "conv_w": (Di, 4), "W_x": (R + 32, Di), "W_dt": (Di, R), "A": (Di, 16), "D": (Di,),
+                          "W_outH": (Dm, Di)}.items()}
+        q["conv_b"], q["dt_bias"] = empty((Di,), torch.float32), empty((Di,), torch.float32)
+        sc = Q.quamba_calibrate_block(d, fw, norms[i], 1e-5, res, out, nb, Lc, 99.999, q, ws)
+        layers.append((q, sc, norms[i]))
+    return d, Q.make_model(d, E, norms[n_layers], layers, 1e-5), (E, norms, layers)
+
+
+def _states(d, n_layers, Bt, seed):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    return (torch.randn((n_layers, Bt, d.d_inner, 16), generator=g, device=DEV) * 0.1,
+            (torch.randn((n_layers, Bt, d.d_inner, 3), generator=g, device=DEV) * 0.5).half())
+
+
+def _steps(d, m, n_layers, Bt, hook, steps=2, fill=0):
+    ssm, conv = _states(d, n_layers, Bt, 5)
+    ws = workspace(Q.quamba_model_workspace_bytes(m, Bt, 1))
+    ws.fill_(fill)  # words of an earlier step, or anything else
+    tok = torch.arange(Bt, dtype=torch.int32, device=DEV) * 40 + 3
+    logits, got = empty((Bt, VOCAB), torch.float32), []
+    Q.quamba_debug_set_decode_stack(hook)
+    try:
+        for _ in range(steps):
+            Q.quamba_model_decode(m, tok, Bt, logits, tok, ssm, conv, ws)
+            got += [logits.clone(), tok.clone()]
+    finally:
+        Q.quamba_debug_set_decode_stack(0)
+    return got + [ssm, conv]
+
+
+@pytest.mark.parametrize("Dm,Di,R,n_layers,Bt", [
+    (80, 1536, 16, 3, 1),     # fewer columns than workgroups, Hadamard items that leave a wave half empty
+    (208, 1536, 48, 2, 2),    # a ragged last group of out_proj columns
+    (768, 1536, 48, 23, 1),   # more blocks than descriptors in one launch
+    (1024, 2048, 64, 2, 2),   # an order that is a power of two
+    (1280, 2560, 256, 2, 1),  # the widest dt_rank
+    (1536, 3072, 96, 2, 2),
+    (2048, 4096, 128, 2, 1),
+    (2560, 5120, 160, 2, 1),  # every CU
+    (2560, 5120, 160, 2, 2),
+    (3072, 1536, 16, 2, 2),   # the widest d_model; more out_proj columns than 256 workgroups take: launch by launch
+])
+def test_one_launch_gives_the_bits_of_separate_launches(Dm, Di, R, n_layers, Bt):
+    """Integer sums and the same fp32 operations in the same order: equal, not close."""
+    d, m, keep = _model(Dm, Di, R, n_layers, Dm + Di + Bt)
+    want = _steps(d, m, n_layers, Bt, 1)
+    assert torch.isfinite(want[0]).all() and want[0].std() > 0
+    for hook, fill in ((0, 0), (0, 255), (2, 1)):
+        print("decode stack", Dm, Di, Bt, "hook", hook, flush=True)
+        for a, b in zip(_steps(d, m, n_layers, Bt, hook, fill=fill), want):
+            assert torch.equal(a, b)
+    del keep
+
+
+def test_generation_from_a_graph():
+    d, m, keep = _model(768, 1536, 48, 4, 11)
+    outs = []
+    for hook, graph in ((1, 0), (0, 0), (0, 1), (0, 1)):
+        ssm, conv = _states(d, 4, 1, 5)
+        ws, toks = workspace(Q.quamba_model_workspace_bytes(m, 1, 1)), empty((9, 1), torch.int32)
+        stream = torch.cuda.Stream()
+        stream.wait_stream(torch.cuda.current_stream())
+        Q.quamba_debug_set_decode_stack(hook)
+        try:
+            Q.quamba_model_generate(m, torch.tensor([3], dtype=torch.int32, device=DEV), 1, 9, toks, ssm, conv, ws, graph,
+                                    stream.cuda_stream)
+            torch.cuda.synchronize()
+        finally:
+            Q.quamba_debug_set_decode_stack(0)
+        outs.append((toks.clone(), ssm.clone(), conv.clone()))
+    for o in outs[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(o, outs[0]))
+    del keep
+
+
+def test_two_steps_in_flight():
+    """Two streams, states and workspaces of their own, their launches interleaved: neither step waits for the other's workgroups."""
+    d, m, keep = _model(2560, 5120, 160, 2, 12)
+    want = _steps(d, m, 2, 1, 1, steps=6)
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    runs = []
+    for s in streams:
+        ssm, conv = _states(d, 2, 1, 5)
+        runs.append((torch.full((1,), 3, dtype=torch.int32, device=DEV), empty((1, VOCAB), torch.float32), ssm, conv,
+                     workspace(Q.quamba_model_workspace_bytes(m, 1, 1))))
+    torch.cuda.synchronize()
+    for _ in range(6):
+        for s, (tok, logits, ssm, conv, ws) in zip(streams, runs):
+            Q.quamba_model_decode(m, tok, 1, logits, tok, ssm, conv, ws, s.cuda_stream)
+    torch.cuda.synchronize()
+    for tok, logits, ssm, conv, _ in runs:
+        assert torch.equal(logits, want[-4]) and torch.equal(tok, want[-3])
+        assert torch.equal(ssm, want[-2]) and torch.equal(conv, want[-1])
+    del keep
