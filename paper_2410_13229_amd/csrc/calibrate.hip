@@ -3,6 +3,7 @@
 // for the scan input x, the Hadamard-space scale of the scan output and the folding of H_n
 // into W_out, followed by the per-tensor symmetric quantization of every weight (Eq. 2).
 // This runs once per layer.  4 x 256 tokens of the 2.8B layer: 54 GFLOP of fp32 input projection are the floor.
+#include <atomic>
 #include <cmath>
 #include <cstring>
 #include <vector>
@@ -21,6 +22,7 @@ constexpr float LOG2E = 1.44269504088896340736f;
 // Pieces of four values of master weights and outputs, which promise no more than their own alignment.
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 // ---------------------------------------------------------------- fp32 GEMM, C = A W^T
@@ -35,8 +37,8 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // the four registers the operands of four products in the order of k (stored in that order instead, as pairs, the
 // products took 600 us at the size below), so a wave reads 16 bytes per lane three times for eight products.
 // Small tiles, so that several workgroups cover each other's barriers: 74 vector and 32 accumulation registers leave room for
-// four on a CU.  The 1280 of 1024 x 10240 are a full round of them and a quarter of one, in which a workgroup has its CU to
-// itself: 553 us = 97 TFLOP/s of the 157 that fp32 matrix products reach at most (a 64 x 64 tile on the vector units: 935 us).
+// four on a CU.  Where the last round of them is nearly empty (the 1280 of 1024 x 10240 are a full round and a quarter of one: 479 us, 112
+// TFLOP/s of the 157 that fp32 matrix products reach at most) the wide tiles below take over (a 64 x 64 tile on the vector units: 935 us).
 // WM x WN waves: 128 x 64, 64 x 128, 32 x 256 outputs per workgroup.
 constexpr int GK = 32, GLD = GK + 4;
 
@@ -110,6 +112,84 @@ __global__ __launch_bounds__(256) void sgemm_tn_kernel(const float *__restrict__
     }
 }
 
+// Large outputs whose tiles come out even over the CUs: 128 x 32 TN outputs per workgroup, a wave 32 rows x 32 TN columns (TN = 3 to 5; 80
+// accumulators at 5), at most two workgroups per CU.  A wave reads TN + 1 operand pieces for 4 TN products; slices of 32 in two unpadded LDS
+// buffers (the pieces of a row exchanged by the row's low bits), so one barrier per slice, and the slice after next is on its way meanwhile.
+// Bound by the matrix unit: 1024 x 10240 x 2560 431 us = 125 TFLOP/s, 479 in tiles of 128 x 64 (467 with these tiles and the swaps above:
+// here the even k of every eight are stored in one piece and the odd ones in the next, which costs a second store per piece).
+template <int TN>
+__global__ __launch_bounds__(256, 2) void sgemm_wide_kernel(const float *__restrict__ A, int lda, const float *__restrict__ W,
+                                                            int ldw, float *__restrict__ C, int ldc, int M, int N, int K) {
+  constexpr int BM = 128, BN = 32 * TN, ROWS = BM + BN, PIECES = ROWS / 32;
+  extern __shared__ __attribute__((aligned(16))) float tile[];  // [2][ROWS][GK]
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l31 = lane & 31, h = lane >> 5;
+  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
+  const int prow = tid >> 3, piece = tid & 7;
+  // row r of the tile: rows of A, then rows of W; past the end: read again, never stored
+  const float *src[PIECES];
+#pragma unroll
+  for (int i = 0; i < PIECES; ++i) {
+    const int r = prow + 32 * i;
+    src[i] = (r < BM ? A + (size_t)min(m0 + r, M - 1) * lda : W + (size_t)min(n0 + r - BM, N - 1) * ldw) + piece * 4;
+  }
+  f4 reg[PIECES];
+  auto fetch = [&](int k) {  // K is a multiple of 16: a piece is in range or out of it
+#pragma unroll
+    for (int i = 0; i < PIECES; ++i) {
+      reg[i] = f4{0.f, 0.f, 0.f, 0.f};
+      if (k + piece * 4 < K) reg[i] = *reinterpret_cast<const f4u *>(src[i] + k);
+    }
+  };
+  // of every eight k, the even ones go to one 16-byte piece and the odd ones to the next (rows 32 apart share their low bits)
+  const int to0 = prow * GK + ((((piece & ~1) + 0) ^ (prow & 7)) * 4) + 2 * (piece & 1);
+  const int to1 = prow * GK + ((((piece & ~1) + 1) ^ (prow & 7)) * 4) + 2 * (piece & 1);
+  auto park = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < PIECES; ++i) {
+      float *row = tile + buf * (ROWS * GK) + 32 * i * GK;
+      *reinterpret_cast<f2 *>(row + to0) = f2{reg[i][0], reg[i][2]};
+      *reinterpret_cast<f2 *>(row + to1) = f2{reg[i][1], reg[i][3]};
+    }
+  };
+  f32x16 acc[TN];
+#pragma unroll
+  for (int j = 0; j < TN; ++j)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
+  fetch(0);
+  park(0);
+  if (GK < K) fetch(GK);
+  __syncthreads();
+  for (int k = 0, buf = 0; k < K; k += GK, buf ^= 1) {
+    if (k + GK < K) park(buf ^ 1);  // read last before the barrier at the end of the previous slice
+    if (k + 2 * GK < K) fetch(k + 2 * GK);
+    const float *a = tile + buf * (ROWS * GK) + (wave * 32 + l31) * GK, *w = tile + buf * (ROWS * GK) + (BM + l31) * GK;
+#pragma unroll
+    for (int kk = 0; kk < GK / 8; ++kk) {
+      const int at = ((2 * kk + h) ^ (l31 & 7)) * 4;
+      const f4 fa = *reinterpret_cast<const f4 *>(a + at);
+      f4 fw[TN];
+#pragma unroll
+      for (int j = 0; j < TN; ++j) fw[j] = *reinterpret_cast<const f4 *>(w + j * 32 * GK + at);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fw[j][e], fa[e], acc[j], 0, 0, 0);
+    }
+    __syncthreads();
+  }
+  const int m = m0 + wave * 32 + l31;
+  if (m >= M) return;
+  float *row = C + (size_t)m * ldc;
+#pragma unroll
+  for (int j = 0; j < TN; ++j)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int n = n0 + j * 32 + 8 * q + 4 * h;  // N is a multiple of 16
+      if (n < N) *reinterpret_cast<f4u *>(row + n) = f4u{acc[j][4 * q], acc[j][4 * q + 1], acc[j][4 * q + 2], acc[j][4 * q + 3]};
+    }
+}
+
 // Skinny outputs (x_proj: 1024 x 192 x 5120, 24 tiles of the form above): the chain over K is what takes the time, so the
 // output is cut as small as the matrix unit allows, one 16 x 16 block (v_mfma_f32_16x16x4_f32, 32 clocks per four of K)
 // for each of the four waves of a 32 x 32 tile; slices of 64 in two buffers, the one after
@@ -169,6 +249,45 @@ __global__ __launch_bounds__(256) void sgemm_skinny_kernel(const float *__restri
   if (m < M && n < N) *reinterpret_cast<f4u *>(C + (size_t)m * ldc + n) = f4u{acc[0], acc[1], acc[2], acc[3]};
 }
 
+template <int TN>
+int run_wide(const float *A, int lda, const float *W, int ldw, float *C, int M, int N, int K, hipStream_t st) {
+  constexpr size_t lds = 2 * (128 + 32 * TN) * GK * sizeof(float);
+  if (lds > 64 * 1024) {  // the attribute is per device: one bit per device index
+    static std::atomic<unsigned long long> attr_set{0};
+    int dev = 0;
+    QUAMBA_HIP(hipGetDevice(&dev));
+    const unsigned long long bit = 1ull << (dev & 63);
+    if (!(attr_set.load(std::memory_order_acquire) & bit)) {
+      QUAMBA_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&sgemm_wide_kernel<TN>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+      attr_set.fetch_or(bit, std::memory_order_release);
+    }
+  }
+  hipLaunchKernelGGL(sgemm_wide_kernel<TN>, dim3((N + 32 * TN - 1) / (32 * TN), (M + 127) / 128), dim3(256), lds, st, A, lda, W, ldw, C, N,
+                     M, N, K);
+  QUAMBA_LAUNCH_CHECK();
+  return QUAMBA_OK;
+}
+
+// Width of the wide tiles in blocks of 32 columns, 0: the 128 x 64 tiles.  Prices are us at K = 2560 (1024, 768, 512, 256 rows x 10240
+// columns, and 3072, 8192 and 16384 columns at other K in proportion): 50 and 85 for every 256 of the 128 x 64 tiles begun; the wide ones
+// up to one and up to two per CU.  Beyond two per CU, and within 7 %, the 128 x 64 tiles stay (measured there: 0.85 to 1.02 of the wide).
+int wide_tiles(int M, int N) {
+  const long rows = (M + 127) / 128;
+  auto tiles = [&](int cols) { return rows * ((N + cols - 1) / cols); };
+  double best = 0.93 * (50.0 + 85.0 * (double)((tiles(64) + 255) / 256));
+  int tn = 0;
+  constexpr double one[3] = {180, 218, 260}, two[3] = {280, 353, 428};
+  for (int t = 3; t <= 5; ++t) {
+    const long n = tiles(32 * t);
+    const double price = n <= 256 ? one[t - 3] : two[t - 3];
+    if (n <= 512 && price < best) {
+      best = price;
+      tn = t;
+    }
+  }
+  return tn;
+}
+
 // K and N multiples of 16; the rows of C are N long
 int sgemm(const float *A, int lda, const float *W, int ldw, float *C, int M, int N, int K, hipStream_t st) {
   const int wm = M > 64 ? 4 : (M > 32 ? 2 : 1), wn = 4 / wm;
@@ -177,6 +296,12 @@ int sgemm(const float *A, int lda, const float *W, int ldw, float *C, int M, int
   if ((size_t)grid.x * grid.y < 128) {
     hipLaunchKernelGGL(sgemm_skinny_kernel, dim3((N + 31) / 32, (M + 31) / 32), block, 0, st, A, lda, W, ldw, C, N, M, N, K);
   } else if (wm == 4) {
+    switch (wide_tiles(M, N)) {
+      case 3: return run_wide<3>(A, lda, W, ldw, C, M, N, K, st);
+      case 4: return run_wide<4>(A, lda, W, ldw, C, M, N, K, st);
+      case 5: return run_wide<5>(A, lda, W, ldw, C, M, N, K, st);
+      default: break;
+    }
     hipLaunchKernelGGL((sgemm_tn_kernel<4, 1>), grid, block, 0, st, A, lda, W, ldw, C, N, M, N, K);
   } else if (wm == 2) {
     hipLaunchKernelGGL((sgemm_tn_kernel<2, 2>), grid, block, 0, st, A, lda, W, ldw, C, N, M, N, K);
@@ -418,6 +543,11 @@ __device__ unsigned select_prefix(const unsigned long long *hist, int passes, un
   return prefix;
 }
 
+// One workgroup per CU: in the first two passes all of them add to the same few bins, and additions to one word in memory come 14 ns
+// apart (1024 workgroups: 18 and 26 us for these passes of 4 x 256 tokens of the 2.8B layer, the calibration 886 us against 870; 128: 888;
+// copies of the bins in LDS change nothing).
+constexpr int HIST_WGS = 256;
+
 __global__ __launch_bounds__(256) void select_hist_kernel(const float *__restrict__ x, size_t n, int pass,
                                                           unsigned long long rank, unsigned long long *hist) {
   __shared__ unsigned long long sum[256];
@@ -427,6 +557,7 @@ __global__ __launch_bounds__(256) void select_hist_kernel(const float *__restric
   const unsigned mask = pass ? ~0u << (32 - 8 * pass) : 0u;
   const int shift = 24 - 8 * pass;
   __syncthreads();
+#pragma unroll 4
   for (size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4; i < n; i += (size_t)gridDim.x * 1024) {  // n: a multiple of 16
     const f4 v = *reinterpret_cast<const f4 *>(x + i);
 #pragma unroll
@@ -536,12 +667,16 @@ constexpr size_t CLIP_WS_BYTES = 256 + CLIP_BLOCKS * sizeof(ClipPart);
 
 // Eq. 2 for several tensors in one launch: q = clamp(rne(x * inv_s)), four values per thread and step; every tensor is a
 // multiple of four long.  A segment marked `copy` is copied as fp32 instead.
+// The scale of a tensor with this largest magnitude (1 if it is zero) and its reciprocal, each rounded once from 64 bits.
+__host__ __device__ inline float scale_of(float m) { return m > 0.f ? (float)((double)m / 127.0) : 1.0f; }
+__host__ __device__ inline float inverse_scale(float m) { return (float)(1.0 / (double)scale_of(m)); }
+
 typedef unsigned u1u __attribute__((aligned(1)));
 struct QuantSegs {
   const float *x[MAX_SEGS];
   void *q[MAX_SEGS];
   size_t n[MAX_SEGS];
-  float inv_s[MAX_SEGS];
+  const unsigned *max_bits[MAX_SEGS];  // largest magnitude: 1 / scale is formed here, by the operations the host takes
   int copy[MAX_SEGS];
   unsigned end[MAX_SEGS];
 };
@@ -552,8 +687,9 @@ __global__ __launch_bounds__(256) void quantize_f32_kernel(QuantSegs s) {
   while (blockIdx.x >= s.end[i]) ++i;
   const size_t at = (size_t)(blockIdx.x - (i ? s.end[i - 1] : 0u)) * Q_PER_WG;
   const size_t stop = min(s.n[i], at + Q_PER_WG);
-  const float *x = s.x[i], inv_s = s.inv_s[i];
+  const float *x = s.x[i];
   const bool copy = s.copy[i];
+  const float inv_s = copy ? 0.f : inverse_scale(__uint_as_float(*s.max_bits[i]));
 #pragma unroll 4
   for (size_t k = at + threadIdx.x * 4; k < stop; k += 1024) {
     const f4 v = *reinterpret_cast<const f4u *>(x + k);
@@ -575,7 +711,7 @@ struct Quant {
   const float *x;
   void *q;
   size_t n;
-  float inv_s;
+  const unsigned *max_bits;
   int copy;
 };
 
@@ -583,7 +719,7 @@ int quantize_f32(const Quant *qs, int count, hipStream_t st) {
   QuantSegs s{};
   unsigned end = 0;
   for (int i = 0; i < count; ++i) {
-    s.x[i] = qs[i].x; s.q[i] = qs[i].q; s.n[i] = qs[i].n; s.inv_s[i] = qs[i].inv_s; s.copy[i] = qs[i].copy;
+    s.x[i] = qs[i].x; s.q[i] = qs[i].q; s.n[i] = qs[i].n; s.max_bits[i] = qs[i].max_bits; s.copy[i] = qs[i].copy;
     s.end[i] = end += (unsigned)((qs[i].n + Q_PER_WG - 1) / Q_PER_WG);
   }
   hipLaunchKernelGGL(quantize_f32_kernel, dim3(end), dim3(256), 0, st, s);
@@ -808,10 +944,17 @@ int calibrate(const quamba_dims *d, const quamba_fp_weights *w, const __half *ca
     if (rank < 1) rank = 1;
     if (rank > nx) rank = nx;
     for (int pass = 0; pass < 4; ++pass)
-      hipLaunchKernelGGL(select_hist_kernel, dim3(1024), dim3(256), 0, st, x, nx, pass, (unsigned long long)rank, hist);
+      hipLaunchKernelGGL(select_hist_kernel, dim3(HIST_WGS), dim3(256), 0, st, x, nx, pass, (unsigned long long)rank, hist);
     hipLaunchKernelGGL(select_finish_kernel, dim3(1), dim3(256), 0, st, hist, (unsigned long long)rank, slots + S_COUNT);
     QUAMBA_LAUNCH_CHECK();
   }
+  // quantize the weights (Eq. 2) and copy the two fp32 bias vectors; with the scales formed on the device, so that the host is waited for once
+  const Quant qws[] = {{w->W_in, oq->W_in, (size_t)2 * Di * Dm, slots + S_WIN, 0}, {w->conv_w, oq->conv_w, (size_t)Di * 4, slots + S_CW, 0},
+                       {w->W_x, oq->W_x, (size_t)NX * Di, slots + S_WX, 0},        {w->W_dt, oq->W_dt, (size_t)Di * R, slots + S_WDT, 0},
+                       {A, oq->A, (size_t)Di * N, slots + S_A, 0},                 {w->D, oq->D, (size_t)Di, slots + S_D, 0},
+                       {woh, oq->W_outH, (size_t)Dm * Di, slots + S_WOH, 0},     {w->conv_b, oq->conv_b, (size_t)Di, nullptr, 1},
+                       {w->dt_bias, oq->dt_bias, (size_t)Di, nullptr, 1}};
+  if ((rc = quantize_f32(qws, sizeof(qws) / sizeof(qws[0]), st))) return rc;
   float mx[S_COUNT + 1];
   QUAMBA_HIP(hipMemcpyAsync(mx, slots, sizeof(mx), hipMemcpyDeviceToHost, st));
   QUAMBA_HIP(hipStreamSynchronize(st));
@@ -823,7 +966,7 @@ int calibrate(const quamba_dims *d, const quamba_fp_weights *w, const __half *ca
   }
 
   if (x_clip_out) *x_clip_out = xp;  // the clipping value of x before it becomes a scale
-  auto sc_of = [](float m) { return m > 0.f ? (float)((double)m / 127.0) : 1.0f; };
+  auto sc_of = scale_of;
   quamba_scales s{};
   s.s_u = sc_of(mx[S_U]); s.s_xpre = sc_of(mx[S_XPRE]); s.s_z = sc_of(mx[S_Z]); s.s_x = sc_of(xp);
   s.s_dtl = sc_of(mx[S_DTL]); s.s_B = sc_of(mx[S_B]); s.s_C = sc_of(mx[S_C]); s.s_dt = sc_of(mx[S_DT]);
@@ -844,16 +987,6 @@ int calibrate(const quamba_dims *d, const quamba_fp_weights *w, const __half *ca
   s.inv_s_y = (float)(1.0 / dy);
   s.m_out = (float)(dy * dWoh / (double)Di);
   *os = s;
-
-  // quantize the weights (Eq. 2) and copy the two fp32 bias vectors
-  auto inv = [](float sc) { return (float)(1.0 / (double)sc); };
-  const Quant qws[] = {{w->W_in, oq->W_in, (size_t)2 * Di * Dm, inv(s.s_Win), 0}, {w->conv_w, oq->conv_w, (size_t)Di * 4, inv(s.s_cw), 0},
-                       {w->W_x, oq->W_x, (size_t)NX * Di, inv(s.s_Wx), 0},        {w->W_dt, oq->W_dt, (size_t)Di * R, inv(s.s_Wdt), 0},
-                       {A, oq->A, (size_t)Di * N, inv(s.s_A), 0},                 {w->D, oq->D, (size_t)Di, inv(s.s_D), 0},
-                       {woh, oq->W_outH, (size_t)Dm * Di, inv(s.s_WoutH), 0},     {w->conv_b, oq->conv_b, (size_t)Di, 0.f, 1},
-                       {w->dt_bias, oq->dt_bias, (size_t)Di, 0.f, 1}};
-  if ((rc = quantize_f32(qws, sizeof(qws) / sizeof(qws[0]), st))) return rc;
-  QUAMBA_HIP(hipStreamSynchronize(st));
   return QUAMBA_OK;
 }
 
@@ -881,7 +1014,7 @@ int calibrate_hadx(const quamba_dims *d, const quamba_fp_weights *w, const __hal
   float mx[2];
   QUAMBA_HIP(hipMemcpyAsync(mx, b.slots, sizeof(mx), hipMemcpyDeviceToHost, st));
   QUAMBA_HIP(hipStreamSynchronize(st));
-  auto sc_of = [](float m) { return m > 0.f ? (float)((double)m / 127.0) : 1.0f; };
+  auto sc_of = scale_of;
   oh->s_xH = sc_of(mx[0]);
   oh->s_WxH = sc_of(mx[1]);
   const double a = oh->s_xH, c = oh->s_WxH;
@@ -891,7 +1024,7 @@ int calibrate_hadx(const quamba_dims *d, const quamba_fp_weights *w, const __hal
   oh->m_xh_C = (float)(a * c / ((double)Di * (double)os->s_C));
   oh->xhat_scale = (float)(a / (double)Di);
   const size_t nw = (size_t)NX * Di;
-  const Quant qw{b.woh, oh->W_xH, nw, (float)(1.0 / c), 0};
+  const Quant qw{b.woh, oh->W_xH, nw, b.slots + 1, 0};
   if ((rc = quantize_f32(&qw, 1, st))) return rc;
   QUAMBA_HIP(hipStreamSynchronize(st));
   return QUAMBA_OK;

@@ -17,7 +17,7 @@ def _case(Dm, Di, R, nb, L):
 
 
 # Products of fewer than 128 tiles run in 32 x 32 blocks, others in tiles of 128 x 64 (more than 64 rows), 64 x 128 (33 to
-# 64) or 32 x 256 (up to 32).
+# 64) or 32 x 256 (up to 32); above 64 rows tiles of 128 x 96, 128 x 128 or 128 x 160 where they come out even over the CUs.
 @pytest.mark.parametrize("Dm,Di,R,nb,L", [
     # 32 x 32 blocks throughout
     (48, 16, 16, 1, 1),        # half a block of channels, one token, K = 16 and 48: a part of a slice
@@ -30,6 +30,13 @@ def _case(Dm, Di, R, nb, L):
     (768, 1536, 48, 3, 100),   # in_proj: 48 x 3 tiles, 300 rows
     (48, 1536, 48, 5, 130),    # in_proj and dt_proj: 650 rows, K = 48: a slice and a half
     (1040, 192, 16, 7, 131),   # out_proj: 917 rows, 1040 columns (a quarter of the last tile)
+    # 128 x 96, 128 x 128 and 128 x 160 tiles
+    (48, 5120, 16, 1, 129),    # in_proj: 107 x 2 of 96 columns, 64 in the last, one row in the second row block
+    (80, 5120, 16, 2, 128),    # whole row blocks
+    (10256, 16, 16, 5, 130),   # out_proj: 650 rows, 81 x 6 of 128 columns, 16 in the last
+    (48, 5120, 16, 5, 151),    # in_proj: 755 rows, 128 columns
+    (80, 5120, 16, 3, 131),    # in_proj: 393 rows, 64 x 4 of 160 columns
+    (10192, 16, 16, 7, 130),   # out_proj: 910 rows, 64 x 8 of 160 columns, 112 in the last
     # 64 x 128 tiles: in_proj to 16384 columns
     (48, 8192, 16, 1, 33),
     (80, 8192, 16, 3, 21),     # 63 rows
@@ -119,7 +126,8 @@ def _chain(a, w):
     return acc
 
 
-@pytest.mark.parametrize("Dm,Di,R,nb,L", [(80, 320, 48, 1, 31), (48, 1536, 48, 5, 130), (80, 8192, 16, 2, 32), (80, 16384, 16, 1, 20)])
+@pytest.mark.parametrize("Dm,Di,R,nb,L", [(80, 320, 48, 1, 31), (48, 1536, 48, 5, 130), (80, 8192, 16, 2, 32), (80, 16384, 16, 1, 20),
+                                             (48, 5120, 16, 1, 130), (80, 5120, 16, 5, 130), (48, 5120, 16, 7, 141)])
 def test_fp32_sums_run_over_k_in_order(Dm, Di, R, nb, L):
     """Each projection of the forward against the chain on the host, bit for bit, at rows and columns of every part of a tile."""
     cfg, w, u = _case(Dm, Di, R, nb, L)
