@@ -112,7 +112,64 @@ __device__ __forceinline__ void store_tiles(const v16i (&acc)[TN][TM], int m_bas
 // wave-level store covers whole runs of a row instead of 8-byte pieces of 32 different rows.
 // Needs N, ldo and the output base aligned to 16 bytes; `scratch` is this wave's region of
 // TM*32 * (TN*32 * sizeof(element) + 16) bytes, free of other use (callers barrier before).
-template <int TM, int TN, bool CONV = false>
+// The conv step's operands for the groups of four channels that one wave takes of a block of TM x TN tiles: of the block's groups in row-major
+// order lane + 64 (part * IT + it), part being the wave's among the PARTS that share the block.  Consecutive lanes take consecutive
+// groups of one row, so the 24-byte windows they touch are adjacent.
+template <int TM, int TN, int PARTS>
+struct ConvBlock {
+  static constexpr int GPR = TN * 8;                    // groups per block row (int8 output)
+  static constexpr int IT = TM * 32 * GPR / 64 / PARTS;  // groups per lane
+  ConvWindow4 win[IT];
+  v4i wv[IT], bv[IT];
+
+  // where group `it` lies; false: outside the conv's columns (an address that may be read, never written)
+  __device__ __forceinline__ bool at(int it, int part, int lane, int m_base, int n_base, int M, int N, int e0, int *q, int *cm, int *cn) const {
+    *q = lane + 64 * (part * IT + it);
+    const int gm = m_base + *q / GPR, gn = n_base + *q % GPR * 4;
+    const bool on = gm < M && gn < N && gn < e0;
+    *cm = on ? gm : 0;
+    *cn = on ? gn : 0;
+    return on;
+  }
+  __device__ __forceinline__ void load(const GemmEpilogue &epi, int part, int lane, int m_base, int n_base, int M, int N) {
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      int q, cm, cn;
+      at(it, part, lane, m_base, n_base, M, N, epi.e0, &q, &cm, &cn);
+      const uint2 *cs = reinterpret_cast<const uint2 *>(epi.conv.state + ((size_t)cm * epi.e0 + cn) * 3);
+      win[it].u[0] = cs[0];
+      win[it].u[1] = cs[1];
+      win[it].u[2] = cs[2];
+      wv[it] = *reinterpret_cast<const v4i *>(epi.conv.w_q + (size_t)cn * 4);
+      bv[it] = *reinterpret_cast<const v4i *>(epi.conv.bias + cn);
+    }
+  }
+  // from the block's codes staged in `scratch` (rows `pitch` bytes apart)
+  __device__ __forceinline__ void step(const GemmEpilogue &epi, int part, int lane, int m_base, int n_base, int M, int N, const int8_t *scratch,
+                                       int pitch) {
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      int q, cm, cn;
+      const bool on = at(it, part, lane, m_base, n_base, M, N, epi.e0, &q, &cm, &cn);
+      const size_t to = (size_t)cm * epi.e0 + cn;
+      const uint4 w4 = make_uint4(wv[it][0], wv[it][1], wv[it][2], wv[it][3]);
+      const float4 b4 = make_float4(__int_as_float(bv[it][0]), __int_as_float(bv[it][1]), __int_as_float(bv[it][2]), __int_as_float(bv[it][3]));
+      float sv[4];
+      conv_step4_core(*reinterpret_cast<const unsigned *>(scratch + q / GPR * pitch + q % GPR * 4), w4, b4, win[it], epi.conv.s_cw,
+                      epi.conv.s_xpre, sv);
+      if (on) {
+        uint2 *cs = reinterpret_cast<uint2 *>(epi.conv.state + to * 3);
+        cs[0] = win[it].u[0];
+        cs[1] = win[it].u[1];
+        cs[2] = win[it].u[2];
+        *reinterpret_cast<unsigned *>(epi.conv.x_q + to) =
+            pack_q8x4(sv[0] * epi.conv.inv_s_x, sv[1] * epi.conv.inv_s_x, sv[2] * epi.conv.inv_s_x, sv[3] * epi.conv.inv_s_x);
+      }
+    }
+  }
+};
+
+template <int TM, int TN>
 __device__ __forceinline__ void store_tiles_rows(const v16i (&acc)[TN][TM], int m_base, int n_base, int lane,
                                                  int M, int N, const GemmEpilogue &epi, int8_t *scratch) {
   const bool f16 = epi.out_f16 != nullptr;
@@ -162,64 +219,25 @@ __device__ __forceinline__ void store_tiles_rows(const v16i (&acc)[TN][TM], int 
       }
     }
   }
-  if constexpr (CONV) {
-    // conv step on the x_pre columns, from the staged codes: consecutive lanes take consecutive
-    // groups of four channels of one row, so the 24-byte windows they touch are adjacent.  All
-    // windows, weights and biases of the wave's block are requested before the first is used.
-    constexpr int GPR = TN * 8;            // groups per block row (int8 output)
-    constexpr int IT = TM * 32 * GPR / 64;  // groups per lane
-    ConvWindow4 win[IT];
-    uint4 wv[IT];
-    float4 bv[IT];
-    bool on[IT];
-    size_t at[IT];
-#pragma unroll
-    for (int it = 0; it < IT; ++it) {
-      const int q = lane + 64 * it;
-      const int row = q / GPR, cg = q % GPR;
-      const int gm = m_base + row, gn = n_base + cg * 4;
-      on[it] = gm < M && gn < N && gn < epi.e0;
-      const int cm = on[it] ? gm : 0, cn = on[it] ? gn : 0;  // off: a valid address, loaded, never stored
-      at[it] = (size_t)cm * epi.e0 + cn;
-      const uint2 *cs = reinterpret_cast<const uint2 *>(epi.conv.state + at[it] * 3);
-      win[it].u[0] = cs[0];
-      win[it].u[1] = cs[1];
-      win[it].u[2] = cs[2];
-      wv[it] = *reinterpret_cast<const uint4 *>(epi.conv.w_q + (size_t)cn * 4);
-      bv[it] = *reinterpret_cast<const float4 *>(epi.conv.bias + cn);
-    }
-#pragma unroll
-    for (int it = 0; it < IT; ++it) {
-      const int q = lane + 64 * it;
-      const int row = q / GPR, cg = q % GPR;
-      float sv[4];
-      conv_step4_core(*reinterpret_cast<const unsigned *>(scratch + row * pitch + cg * 4), wv[it], bv[it], win[it],
-                      epi.conv.s_cw, epi.conv.s_xpre, sv);
-      if (on[it]) {
-        uint2 *cs = reinterpret_cast<uint2 *>(epi.conv.state + at[it] * 3);
-        cs[0] = win[it].u[0];
-        cs[1] = win[it].u[1];
-        cs[2] = win[it].u[2];
-        *reinterpret_cast<unsigned *>(epi.conv.x_q + at[it]) =
-            pack_q8x4(sv[0] * epi.conv.inv_s_x, sv[1] * epi.conv.inv_s_x, sv[2] * epi.conv.inv_s_x, sv[3] * epi.conv.inv_s_x);
-      }
-    }
-  }
+}
+
+// Can a wave's block leave through LDS as whole rows (store_tiles_rows)?  The same for all waves of a launch.
+template <int TM, int TN>
+__device__ __forceinline__ bool rows_ok(int N, const GemmEpilogue &epi, const int32_t *partial, int scratch_bytes) {
+  const bool f16 = epi.out_f16 != nullptr;
+  const int per = f16 ? 8 : 16;  // elements per 16-byte store
+  const int region = TM * 32 * (TN * 32 * (f16 ? 2 : 1) + 16);  // bytes one wave stages (padded rows)
+  const uintptr_t base = reinterpret_cast<uintptr_t>(f16 ? (const void *)epi.out_f16 : (const void *)epi.out_i8);
+  return !partial && !epi.acc && base != 0 && (N % per) == 0 && (epi.ldo % per) == 0 && (base % 16) == 0 && region <= scratch_bytes;
 }
 
 template <int TM, int TN, bool BARRIER, bool CONV = false>
 __device__ __forceinline__ void finish(const v16i (&acc)[TN][TM], int m_base, int n_base, int lane,
                                        int M, int N, const GemmEpilogue &epi, int32_t *partial,
                                        int8_t *scratch, int scratch_bytes) {
-  const bool f16 = epi.out_f16 != nullptr;
-  const int per = f16 ? 8 : 16;  // elements per 16-byte store
-  const int region = TM * 32 * (TN * 32 * (f16 ? 2 : 1) + 16);  // bytes one wave stages (padded rows)
-  const uintptr_t base = reinterpret_cast<uintptr_t>(f16 ? (const void *)epi.out_f16 : (const void *)epi.out_i8);
-  const bool rows_ok = !partial && !epi.acc && base != 0 && (N % per) == 0 && (epi.ldo % per) == 0 &&
-                       (base % 16) == 0 && region <= scratch_bytes;
-  if (rows_ok) {
+  if (rows_ok<TM, TN>(N, epi, partial, scratch_bytes)) {
     if (BARRIER) __syncthreads();
-    store_tiles_rows<TM, TN, CONV>(acc, m_base, n_base, lane, M, N, epi, scratch);
+    store_tiles_rows<TM, TN>(acc, m_base, n_base, lane, M, N, epi, scratch);
   } else {
     store_tiles<TM, TN, CONV>(acc, m_base, n_base, lane, M, N, epi, partial);
   }
@@ -377,6 +395,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC) void gemm_i8_dma_kernel(c
                                                                int tiles_m, int tiles_n, KSplit ks) {
   // KG wave groups share one output tile: group g multiplies the 32-byte sub-slices s with
   // s % KG == g, and the groups' sums are added through LDS before the epilogue.
+  static_assert(!CONV || (KG > 1 && S > 2), "the conv step rides in the K-group epilogue of the deeper rings");
   constexpr int NW = WGM * WGN * KG;  // waves per workgroup
   static_assert(NW == 2 || NW == 4 || NW == 8, "two, four or eight waves per workgroup");
   static_assert(BKB == 64 || BKB == 128 || BKB == 256, "slice width");
@@ -583,7 +602,12 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC) void gemm_i8_dma_kernel(c
     constexpr int PART = TM * TN * 16 * 64 * 4;
     constexpr int TILES = WGM * WGN;
     static_assert(S * STAGE >= (KG - 1) * TILES * PART, "K-group sums fit in the ring");
+    // The conv step's groups are spread over all K groups of waves, their operands asked for in front of the exchange of sums (one wave per tile
+    // behind it: generation step of the 2.8B layer, 32 sequences 36.2 -> 35.1 us, 16 31.8 -> 31.2; in front of the products the reads
+    // hold up the ring's first slices: 40.7 against 39.9 us at 64)
     __syncthreads();  // operand tiles are dead
+    ConvBlock<TM, TN, CONV ? KG : 1> conv;
+    if constexpr (CONV) conv.load(epi, kg, lane, m0 + wm * WM, n0 + wn * WN, M, N);
     if (kg >= 1) {
       v4i *part = reinterpret_cast<v4i *>(ring + ((kg - 1) * TILES + wtile) * PART);
 #pragma unroll
@@ -596,7 +620,9 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC) void gemm_i8_dma_kernel(c
                 v4i{acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
     }
     __syncthreads();
-    if (kg >= 1) return;
+    if constexpr (!CONV)
+      if (kg >= 1) return;
+    if (!CONV || kg == 0) {
 #pragma unroll
     for (int o = 0; o < KG - 1; ++o) {
       const v4i *part = reinterpret_cast<const v4i *>(ring + (o * TILES + wtile) * PART);
@@ -613,6 +639,12 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC) void gemm_i8_dma_kernel(c
     }
     finish<TM, TN, false, CONV>(acc, m0 + wm * WM, n0 + wn * WN, lane, M, N, epi,
                                 ks.partial ? ks.partial + (size_t)blockIdx.y * M * N : nullptr, ring + wtile * PART, PART);
+    }
+    if constexpr (CONV)
+      if (rows_ok<TM, TN>(N, epi, ks.partial, PART)) {  // otherwise every group was stepped as it was stored
+        __syncthreads();  // the codes of the tile are staged
+        conv.step(epi, kg, lane, m0 + wm * WM, n0 + wn * WN, M, N, ring + wtile * PART, TN * 32 + 16);
+      }
   } else {
     constexpr int REGION = S * STAGE / NW / 16 * 16;
     finish<TM, TN, true, CONV>(acc, m0 + wm * WM, n0 + wn * WN, lane, M, N, epi,
