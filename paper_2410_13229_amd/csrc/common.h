@@ -119,11 +119,17 @@ int launch_requant_dyn(const int32_t *acc, int8_t *out, int M, int N, int e0, in
                        float so0, float so1, float so2, hipStream_t st);
 int launch_dyn_export(const unsigned *slot, float *out, hipStream_t st);
 
+// memory that the launches after this one will read (weights of a stack too large for the last-level cache): extra workgroups
+// of a launch that leaves most CUs idle read it, so that it waits in the cache
+struct ReadAhead {
+  const void *ptr = nullptr;
+  size_t bytes = 0;
+};
 int launch_add_rmsnorm_quant(const __half *x_out, __half *res, const __half *weight, float eps,
-                             float inv_s, int8_t *u_q, int M, int Dm, hipStream_t st);
+                             float inv_s, int8_t *u_q, int M, int Dm, hipStream_t st, ReadAhead ahead = {});
 // the same with x_out given as `splits` (<= 8) int32 partial sums [splits][M][Dm]: x_out = fp16(m_out * their sum)
 int launch_add_rmsnorm_quant_partial(const int32_t *partial, int splits, float m_out, __half *res, const __half *weight,
-                                     float eps, float inv_s, int8_t *u_q, int M, int Dm, hipStream_t st);
+                                     float eps, float inv_s, int8_t *u_q, int M, int Dm, hipStream_t st, ReadAhead ahead = {});
 
 struct ScanArgs {
   const int8_t *x_q, *dt_q, *z_q, *B_q, *C_q, *A_q, *D_q;
@@ -169,7 +175,7 @@ int launch_scan_prefill(const ScanArgs &a, void *ws, size_t ws_bytes, hipStream_
 int launch_scan_step(const ScanArgs &a, hipStream_t st);
 
 int launch_hadamard_quant(const __half *g, int M, int n, float inv_s_y, int8_t *yH_q, float *yH_f32,
-                          hipStream_t st);
+                          hipStream_t st, ReadAhead ahead = {});
 // x_hat = fp16(scale * H_n^T xH_q): the backward transform of the Appendix H comparison variant
 bool hadamard_fuses_out_proj(int n, int Dm);
 int launch_hadamard_out_proj(const __half *g, int M, int n, float inv_s_y, const int8_t *W, int Dm, float m_out,
@@ -208,6 +214,7 @@ size_t mixer_workspace_bytes(const quamba_dims *d, int Bt, int L);
 // the mixer's workspace: valid until the next mixer call on it) and the multiplier of the sums.
 struct OutPartial {
   bool want;
+  bool cold;  // set by the caller: the stack's weights exceed the last-level cache, read this block's out_proj weights ahead
   int splits;
   const int32_t *partial;
   float m_out;

@@ -230,4 +230,32 @@ __device__ __forceinline__ void warm_read(const WarmRanges &w, int part, int npa
   asm volatile("" ::"v"(acc));
 }
 
+// The same for one range beside a launch of few workgroups and a few microseconds, where the reading must not outlast the launch: one word per
+// 64 bytes brings the line in, and up to 16 of them per thread leave at once.
+struct WarmLines {
+  const char *ptr;
+  unsigned lines;  // of 64 bytes
+  int blocks;      // workgroups of the launch that do this (0: none)
+};
+__device__ __forceinline__ void warm_lines(const WarmLines &w, int part) {
+  unsigned acc = 0;
+  const unsigned step = w.blocks * blockDim.x;
+  for (unsigned i0 = part * blockDim.x + threadIdx.x; i0 < w.lines; i0 += 16 * step) {
+    unsigned v[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      v[j] = 0;
+      if (i0 + j * step < w.lines) v[j] = *reinterpret_cast<const unsigned *>(w.ptr + (size_t)(i0 + j * step) * 64);
+    }
+#pragma unroll
+    for (int j = 0; j < 16; ++j) acc ^= v[j];
+  }
+  asm volatile("" ::"v"(acc));
+}
+// Workgroups that read ahead: 128 (2.8B layers, 16 of them, 64 sequences: none 887 us a step, 64 863, 96 847, 128 849, 192 857, 256 871).
+inline WarmLines warm_lines_of(const void *p, size_t bytes) {
+  const bool on = p && bytes >= 64;
+  return WarmLines{static_cast<const char *>(p), on ? static_cast<unsigned>(bytes / 64) : 0u, on ? 128 : 0};
+}
+
 }  // namespace quamba

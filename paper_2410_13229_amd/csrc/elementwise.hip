@@ -186,7 +186,11 @@ __global__ __launch_bounds__(256) void add_rmsnorm_quant_kernel(const __half *__
                                                                 float eps, float inv_s,
                                                                 int8_t *__restrict__ u_q, int Dm,
                                                                 const int32_t *__restrict__ partial, int splits,
-                                                                float m_out) {
+                                                                float m_out, int M, WarmLines warm) {
+  if ((int)blockIdx.x >= M) {  // appended workgroups only read ahead
+    warm_lines(warm, blockIdx.x - M);
+    return;
+  }
   const size_t row = blockIdx.x;
   const int ngroups = Dm / 8;
   float vals[RMS_MAX_PER_THREAD][8];
@@ -200,7 +204,7 @@ __global__ __launch_bounds__(256) void add_rmsnorm_quant_kernel(const __half *__
         __half h[8];
       } a, r;
       if constexpr (PART) {
-        const size_t rows = gridDim.x;
+        const size_t rows = M;
         v4i v[8][2];
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
@@ -442,25 +446,27 @@ int launch_conv_step(const int8_t *xpre_q, int ldx, const int8_t *w_q, const flo
 }
 
 int launch_add_rmsnorm_quant(const __half *x_out, __half *res, const __half *weight, float eps,
-                             float inv_s, int8_t *u_q, int M, int Dm, hipStream_t st) {
+                             float inv_s, int8_t *u_q, int M, int Dm, hipStream_t st, ReadAhead ahead) {
   if (Dm % 8 != 0 || Dm > 8 * 256 * RMS_MAX_PER_THREAD)
     return fail(QUAMBA_EUNSUPPORTED, "add_rmsnorm_quant: d_model=%d must be a multiple of 8 and <= %d", Dm,
                 8 * 256 * RMS_MAX_PER_THREAD);
-  hipLaunchKernelGGL(add_rmsnorm_quant_kernel<false>, dim3(M), dim3(256), 0, st, x_out, res, weight, eps, inv_s,
-                     u_q, Dm, nullptr, 0, 0.f);
+  const WarmLines warm = warm_lines_of(ahead.ptr, ahead.bytes);
+  hipLaunchKernelGGL(add_rmsnorm_quant_kernel<false>, dim3(M + warm.blocks), dim3(256), 0, st, x_out, res, weight, eps, inv_s,
+                     u_q, Dm, nullptr, 0, 0.f, M, warm);
   QUAMBA_LAUNCH_CHECK();
   return QUAMBA_OK;
 }
 
 int launch_add_rmsnorm_quant_partial(const int32_t *partial, int splits, float m_out, __half *res, const __half *weight,
-                                     float eps, float inv_s, int8_t *u_q, int M, int Dm, hipStream_t st) {
+                                     float eps, float inv_s, int8_t *u_q, int M, int Dm, hipStream_t st, ReadAhead ahead) {
   if (Dm % 8 != 0 || Dm > 8 * 256 * RMS_MAX_PER_THREAD)
     return fail(QUAMBA_EUNSUPPORTED, "add_rmsnorm_quant: d_model=%d must be a multiple of 8 and <= %d", Dm,
                 8 * 256 * RMS_MAX_PER_THREAD);
   if (!partial || splits < 1 || splits > 8 || !aligned(partial, 16))
     return fail(QUAMBA_EINVAL, "add_rmsnorm_quant: %d partial sums", splits);
-  hipLaunchKernelGGL(add_rmsnorm_quant_kernel<true>, dim3(M), dim3(256), 0, st, nullptr, res, weight, eps, inv_s, u_q,
-                     Dm, partial, splits, m_out);
+  const WarmLines warm = warm_lines_of(ahead.ptr, ahead.bytes);
+  hipLaunchKernelGGL(add_rmsnorm_quant_kernel<true>, dim3(M + warm.blocks), dim3(256), 0, st, nullptr, res, weight, eps, inv_s, u_q,
+                     Dm, partial, splits, m_out, M, warm);
   QUAMBA_LAUNCH_CHECK();
   return QUAMBA_OK;
 }

@@ -30,7 +30,11 @@ template <int K, int LOGM, typename TIn, bool TR>
 __global__ __launch_bounds__(threads_for(K << LOGM)) void hadamard_quant_kernel(const TIn *__restrict__ g, float inv_s,
                                                             int8_t *__restrict__ out,
                                                             float *__restrict__ out_f32,
-                                                            __half *__restrict__ out_f16) {
+                                                            __half *__restrict__ out_f16, int M, WarmLines warm) {
+  if ((int)blockIdx.x >= M) {  // appended workgroups only read ahead
+    warm_lines(warm, blockIdx.x - M);
+    return;
+  }
   constexpr int n = K << LOGM;
   constexpr int HT = threads_for(n);
   extern __shared__ __attribute__((aligned(16))) float row[];
@@ -139,7 +143,7 @@ __global__ __launch_bounds__(threads_for(K << LOGM)) void hadamard_out_proj_kern
 }
 
 template <int K, int LOGM, typename TIn, bool TR>
-int run(const TIn *g, int M, float inv_s, int8_t *out, float *out_f32, __half *out_f16, hipStream_t st) {
+int run(const TIn *g, int M, float inv_s, int8_t *out, float *out_f32, __half *out_f16, hipStream_t st, ReadAhead ahead) {
   constexpr int n = K << LOGM;
   constexpr size_t lds = (size_t)(n + n / 4) * sizeof(float);
   if (lds > 64 * 1024) {  // the attribute is per device: one bit per device index
@@ -153,18 +157,19 @@ int run(const TIn *g, int M, float inv_s, int8_t *out, float *out_f32, __half *o
       attr_set.fetch_or(bit, std::memory_order_release);
     }
   }
-  hipLaunchKernelGGL((hadamard_quant_kernel<K, LOGM, TIn, TR>), dim3(M), dim3(threads_for(n)), lds, st, g, inv_s, out,
-                     out_f32, out_f16);
+  const WarmLines warm = warm_lines_of(ahead.ptr, ahead.bytes);
+  hipLaunchKernelGGL((hadamard_quant_kernel<K, LOGM, TIn, TR>), dim3(M + warm.blocks), dim3(threads_for(n)), lds, st, g, inv_s, out,
+                     out_f32, out_f16, M, warm);
   QUAMBA_LAUNCH_CHECK();
   return QUAMBA_OK;
 }
 
 template <int K, typename TIn, bool TR>
-int dispatch_m(int m, const TIn *g, int M, float inv_s, int8_t *out, float *out_f32, __half *out_f16, hipStream_t st) {
+int dispatch_m(int m, const TIn *g, int M, float inv_s, int8_t *out, float *out_f32, __half *out_f16, hipStream_t st, ReadAhead ahead) {
   switch (m) {
 #define QUAMBA_CASE(LM) \
   case LM:              \
-    return run<K, LM, TIn, TR>(g, M, inv_s, out, out_f32, out_f16, st);
+    return run<K, LM, TIn, TR>(g, M, inv_s, out, out_f32, out_f16, st, ahead);
     QUAMBA_CASE(4)
     QUAMBA_CASE(5)
     QUAMBA_CASE(6)
@@ -213,25 +218,26 @@ bool hadamard_factor(int n, int *k, int *m) {
 
 namespace {
 template <typename TIn, bool TR>
-int dispatch_k(const TIn *g, int M, int n, float inv_s_y, int8_t *yH_q, float *yH_f32, __half *y_f16, hipStream_t st) {
+int dispatch_k(const TIn *g, int M, int n, float inv_s_y, int8_t *yH_q, float *yH_f32, __half *y_f16, hipStream_t st,
+               ReadAhead ahead = {}) {
   int k = 0, m = 0;
   if (!hadamard_factor(n, &k, &m) || m < 4)
     return fail(QUAMBA_EUNSUPPORTED, "hadamard: n=%d is not k*2^m with k in (1,12,20) and m >= 4", n);
   if (M == 0) return QUAMBA_OK;
   switch (k) {
     case 1:
-      return dispatch_m<1, TIn, false>(m, g, M, inv_s_y, yH_q, yH_f32, y_f16, st);  // H_{2^m} is symmetric
+      return dispatch_m<1, TIn, false>(m, g, M, inv_s_y, yH_q, yH_f32, y_f16, st, ahead);  // H_{2^m} is symmetric
     case 12:
-      return dispatch_m<12, TIn, TR>(m, g, M, inv_s_y, yH_q, yH_f32, y_f16, st);
+      return dispatch_m<12, TIn, TR>(m, g, M, inv_s_y, yH_q, yH_f32, y_f16, st, ahead);
     default:
-      return dispatch_m<20, TIn, TR>(m, g, M, inv_s_y, yH_q, yH_f32, y_f16, st);
+      return dispatch_m<20, TIn, TR>(m, g, M, inv_s_y, yH_q, yH_f32, y_f16, st, ahead);
   }
 }
 }  // namespace
 
 int launch_hadamard_quant(const __half *g, int M, int n, float inv_s_y, int8_t *yH_q, float *yH_f32,
-                          hipStream_t st) {
-  return dispatch_k<__half, false>(g, M, n, inv_s_y, yH_q, yH_f32, nullptr, st);
+                          hipStream_t st, ReadAhead ahead) {
+  return dispatch_k<__half, false>(g, M, n, inv_s_y, yH_q, yH_f32, nullptr, st, ahead);
 }
 
 namespace {

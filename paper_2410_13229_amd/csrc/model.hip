@@ -11,6 +11,8 @@
 // is a skinny product that streams E once: an fp16 MFMA kernel with fp32 accumulation.
 // Generation keeps the current token, the step counter and the token log on the device, so one
 // step is a fixed sequence of launches that can be replayed from a HIP graph.
+#include <algorithm>
+
 #include "common.h"
 #include "device_util.h"
 
@@ -380,7 +382,11 @@ int run_model(const quamba_model *m, const int32_t *tokens, int Bt, int L, bool 
   __half *res_other = reinterpret_cast<__half *>(base + c.res2);
   // generation with more sequences: where out_proj splits K over the grid, the next block's add + norm +
   // quantization adds up the partial sums (the last block's output is stored as usual for the final norm)
-  OutPartial prev{false, 1, nullptr, 0.f};
+  OutPartial prev{false, false, 1, nullptr, 0.f};
+  // Weights of a stack that does not fit the 256 MB last-level cache arrive cold in every block.  The norm (a workgroup per sequence, 3 us)
+  // reads 16 MB of in_proj's ahead, the Hadamard launch out_proj's: 16 blocks of the 2.8B layer, 4 / 16 / 64 sequences 610 / 679 / 886
+  // -> 586 / 651 / 847 us a step (more than 16 MB outlasts the norm: 20 MB 868, 26 MB 869 at 64).
+  const bool cold = decode && (double)m->n_layers * Di * (3.0 * Dm + 2.0 * m->dims.dt_rank + 2.0 * N) > 256e6;
   for (int l = 0; !stacked && l < m->n_layers; ++l) {
     const quamba_layer &ly = m->layers[l];
     float *ssm = ssm_states + (size_t)l * Bt * Di * N;
@@ -393,15 +399,17 @@ int run_model(const quamba_model *m, const int32_t *tokens, int Bt, int L, bool 
       res = res_other;
       res_other = tmp;
     } else {
+      ReadAhead ahead;
+      if (cold) ahead = ReadAhead{ly.q.W_in, std::min<size_t>((size_t)2 * Di * Dm, 16u << 20)};
       if (prev.splits > 1)
         rc = launch_add_rmsnorm_quant_partial(prev.partial, prev.splits, prev.m_out, res,
                                               reinterpret_cast<const __half *>(ly.norm_w), m->eps, ly.s.inv_s_u, u_q, M,
-                                              Dm, st);
+                                              Dm, st, ahead);
       else
         rc = launch_add_rmsnorm_quant(out, res, reinterpret_cast<const __half *>(ly.norm_w), m->eps, ly.s.inv_s_u,
-                                      u_q, M, Dm, st);
+                                      u_q, M, Dm, st, ahead);
       if (rc != QUAMBA_OK) return rc;
-      prev = OutPartial{decode && l + 1 < m->n_layers, 1, nullptr, 0.f};
+      prev = OutPartial{decode && l + 1 < m->n_layers, cold, 1, nullptr, 0.f};
       rc = mixer_run_q(&m->dims, &ly.q, &ly.s, u_q, Bt, L, decode, out, ssm, cs, base + c.mixer, c.mixer_bytes, st,
                        &prev, (!decode && l + 1 < m->n_layers) ? &m->layers[l + 1].q : nullptr, !decode && l + 1 == m->n_layers);
     }

@@ -127,3 +127,26 @@ def test_two_steps_in_flight():
         assert torch.equal(logits, want[-4]) and torch.equal(tok, want[-3])
         assert torch.equal(ssm, want[-2]) and torch.equal(conv, want[-1])
     del keep
+
+
+@pytest.mark.parametrize("Bt", [3, 20])
+def test_weights_read_ahead_change_nothing(Bt):
+    """A stack whose weights exceed the last-level cache (the same block seven times: 280 MB): norm and Hadamard launches with workgroups that
+    read ahead, against the blocks one by one through their own entry points."""
+    d, m, keep = _model(2560, 5120, 160, 1, 13)
+    E, norms, layers = keep
+    n = 7
+    m = Q.make_model(d, E, norms[1], layers * n, 1e-5)
+    got = _steps(d, m, n, Bt, 0, steps=1)
+    ssm, conv = _states(d, n, Bt, 5)
+    tok = torch.arange(Bt, dtype=torch.int32, device=DEV) * 40 + 3
+    res, out = E[tok.long().clamp(0, VOCAB - 1)].contiguous(), torch.zeros((Bt, 2560), dtype=torch.float16, device=DEV)
+    u_q, ws = empty((Bt, 2560), torch.int8), workspace(Q.quamba_workspace_bytes(d, Bt, 1))
+    q, sc, norm = layers[0]
+    for l in range(n):
+        Q.quamba_add_rmsnorm_quant(out, res, norm, 1e-5, Q.scales_to_dict(sc)["inv_s_u"], u_q, Bt, 2560)
+        Q.quamba_mixer_decode_q(d, q, sc, u_q, Bt, out, ssm[l], conv[l], None, ws)
+    y, logits = empty((Bt, 2560), torch.float16), empty((Bt, VOCAB), torch.float32)
+    Q.quamba_final_norm(out, res, norms[1], 1e-5, Bt, 1, 2560, y)
+    Q.quamba_lm_head(y, E, Bt, VOCAB, 2560, logits)
+    assert torch.equal(got[0], logits) and torch.equal(got[2], ssm) and torch.equal(got[3], conv)
