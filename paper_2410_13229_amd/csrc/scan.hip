@@ -448,6 +448,7 @@ __global__ __launch_bounds__(256) void scan_carry_kernel(Dev p, float *__restric
 }
 
 // ---------------------------------------------------------------- prefill: one sweep per sequence
+// (Described for two states per lane; with few channels a lane owns one, 16 lanes per channel and 16 channels per workgroup.)
 // The chunked form pays for its parallelism over L with every exponential twice (pass 1 and pass 3).
 // When sequences x channels alone give several waves per SIMD, one sweep over each whole sequence is
 // cheaper.  A lane owns two of the 16 states of one channel (8 lanes per channel, 8 channels per wave,
@@ -476,17 +477,43 @@ __device__ __forceinline__ float dpp_f(float v) {
 // its own instruction order hides latencies: the LDS reads of group g + 1 are in flight under group g, the 16
 // exponentials of a group are issued ahead of the two recurrence chains that consume them, and the gate of
 // group g - 1 (a serial chain with two transcendentals) is spread between them.
-template <int NK, int XM, bool LAT>
+// B and C of a lane's states in one LDS word
+template <int SPL>
+struct BCWord {
+  typedef float4 type;
+};
+template <>
+struct BCWord<1> {
+  typedef float2 type;
+};
+template <int SPL>
+using BCOf = typename BCWord<SPL>::type;
+template <int SPL>
+__device__ __forceinline__ float b_of(const BCOf<SPL> &w, int k) {
+  return k == 0 ? w.x : w.y;
+}
+template <int SPL>
+__device__ __forceinline__ float c_dot(const BCOf<SPL> &w, const float (&h)[SPL]) {
+  if constexpr (SPL == 2) return __builtin_fmaf(w.w, h[1], w.z * h[0]);
+  else return w.y * h[0];
+}
+
+template <int NK, int XM, bool LAT, int SPL>
 __global__ __launch_bounds__(SW_THREADS, LAT ? 1 : 3) void scan_sweep_kernel(Dev p, float *__restrict__ ssm_state) {
+  static_assert(SPL == 2 || (SPL == 1 && LAT), "one state per lane: the latency-ordered form only");
+  constexpr int LPC = NS / SPL;                    // lanes per channel
+  constexpr int CPW = 64 / LPC;                    // channels per wave
+  constexpr int CH = CPW * (SW_THREADS / 64);      // channels per workgroup
+  constexpr int NM = CH / 16;                      // 16-channel tiles of dt
   constexpr bool FUSE_DT = NK > 0;
   constexpr int NKR = FUSE_DT ? NK : 1;
-  __shared__ __attribute__((aligned(16))) float2 sDU[SW_SB][SW_CH + 1];  // (dt, dt x); odd pitch: a tile's token rows on different banks
-  __shared__ __attribute__((aligned(16))) float4 sBC[SW_SB][NS / 2];     // (B[2g], B[2g+1], C[2g], C[2g+1])
-  __shared__ float sDX[SW_SB][SW_CH + 1];                                 // D x
-  __shared__ __attribute__((aligned(4))) int8_t sZ[SW_SB][SW_CH + 4];    // z code
+  __shared__ __attribute__((aligned(16))) float2 sDU[SW_SB][CH + 1];  // (dt, dt x); odd pitch: a tile's token rows on different banks
+  __shared__ __attribute__((aligned(16))) BCOf<SPL> sBC[SW_SB][LPC];     // B of a lane's states, then C
+  __shared__ float sDX[SW_SB][CH + 1];                                 // D x
+  __shared__ __attribute__((aligned(4))) int8_t sZ[SW_SB][CH + 4];    // z code
   // Workgroups go to the 8 XCDs round-robin by index: give one XCD consecutive channel blocks, so the
   // blocks that share 128-byte lines of x, z and g share an L2.
-  const int nblk = p.Di / SW_CH;
+  const int nblk = p.Di / CH;
   const int bx = blockIdx.x;
   if (bx >= nblk) {  // appended workgroups only read ahead
     warm_read(p.warm, (bx - nblk) * gridDim.y + blockIdx.y, p.warm.blocks * gridDim.y);
@@ -494,23 +521,18 @@ __global__ __launch_bounds__(SW_THREADS, LAT ? 1 : 3) void scan_sweep_kernel(Dev
   }
   const int cb = (nblk % 8 == 0) ? (bx & 7) * (nblk >> 3) + (bx >> 3) : bx;
   const int b = blockIdx.y;
-  const int ch0 = cb * SW_CH;
+  const int ch0 = cb * CH;
   const size_t seq0 = (size_t)b * p.L;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-  // ---- recurrence role: channel chl of the workgroup, states 2 ng and 2 ng + 1
-  const int ng = lane & 7, chl = 8 * wave + (lane >> 3), chg = ch0 + chl;
-  float a20, a21, h0 = 0.f, h1 = 0.f;
-  {
-    const unsigned short aw = *reinterpret_cast<const unsigned short *>(p.A_q + (size_t)chg * NS + 2 * ng);
-    a20 = static_cast<float>(static_cast<int8_t>(aw & 0xff)) * (p.s_A * LOG2E);
-    a21 = static_cast<float>(static_cast<int8_t>(aw >> 8)) * (p.s_A * LOG2E);
-    if (ssm_state) {
-      const float2 hv = *reinterpret_cast<const float2 *>(ssm_state + ((size_t)b * p.Di + chg) * NS + 2 * ng);
-      h0 = hv.x;
-      h1 = hv.y;
-    }
+  // ---- recurrence role: channel chl of the workgroup, states SPL ng .. of it; the lane finishes token nt of every eight
+  const int ng = lane & (LPC - 1), nt = ng & 7, chl = CPW * wave + lane / LPC, chg = ch0 + chl;
+  float a2[SPL], h[SPL];
+#pragma unroll
+  for (int k = 0; k < SPL; ++k) {
+    a2[k] = static_cast<float>(p.A_q[(size_t)chg * NS + SPL * ng + k]) * (p.s_A * LOG2E);
+    h[k] = ssm_state ? ssm_state[((size_t)b * p.Di + chg) * NS + SPL * ng + k] : 0.f;
   }
   const bool up4 = (ng & 4) != 0, up2 = (ng & 2) != 0, up1 = (ng & 1) != 0;
 
@@ -518,16 +540,16 @@ __global__ __launch_bounds__(SW_THREADS, LAT ? 1 : 3) void scan_sweep_kernel(Dev
   // 16-token tile; register r of result m is channel 16 m + 4 (lane / 16) + r of the workgroup.  Both
   // operands take the 16 bytes at k = 64 s + 16 (lane / 16) of their row.
   const int tokl = lane & 15, kq = lane >> 4;
-  float bias_r[8], Dv_r[8];
+  float bias_r[4 * NM], Dv_r[4 * NM];
 #pragma unroll
-  for (int r = 0; r < 8; ++r) {
+  for (int r = 0; r < 4 * NM; ++r) {
     const int c = ch0 + 16 * (r >> 2) + 4 * kq + (r & 3);
     bias_r[r] = p.dt_bias[c];
     Dv_r[r] = p.s_D * static_cast<float>(p.D_q[c]);
   }
-  v4i wfrag[2][NKR];
+  v4i wfrag[NM][NKR];
 #pragma unroll
-  for (int m = 0; m < 2; ++m)
+  for (int m = 0; m < NM; ++m)
 #pragma unroll
     for (int s = 0; s < NKR; ++s) {
       wfrag[m][s] = v4i{0, 0, 0, 0};
@@ -540,7 +562,7 @@ __global__ __launch_bounds__(SW_THREADS, LAT ? 1 : 3) void scan_sweep_kernel(Dev
 
   struct Pre {
     v4i a[NKR];
-    unsigned x[2], z[2], dtc[2];
+    unsigned x[NM], z[NM], dtc[NM];
     unsigned bq, cq;
   };
   auto issue = [&](Pre &r, int sb) {
@@ -554,7 +576,7 @@ __global__ __launch_bounds__(SW_THREADS, LAT ? 1 : 3) void scan_sweep_kernel(Dev
       }
     }
 #pragma unroll
-    for (int m = 0; m < 2; ++m) {
+    for (int m = 0; m < NM; ++m) {
       const int c = ch0 + 16 * m + 4 * kq;
       r.x[m] = *reinterpret_cast<const unsigned *>(p.x_q + row * p.Di + c);
       r.z[m] = *reinterpret_cast<const unsigned *>(p.z_q + row * p.ldz + c);
@@ -570,7 +592,7 @@ __global__ __launch_bounds__(SW_THREADS, LAT ? 1 : 3) void scan_sweep_kernel(Dev
     const int tok = sb * SW_SB + tl;
     const bool valid = tok < p.L;
 #pragma unroll
-    for (int m = 0; m < 2; ++m) {
+    for (int m = 0; m < NM; ++m) {
       unsigned pk;
       if constexpr (FUSE_DT) {
         v4i acc = {0, 0, 0, 0};
@@ -598,15 +620,18 @@ __global__ __launch_bounds__(SW_THREADS, LAT ? 1 : 3) void scan_sweep_kernel(Dev
     }
     const int quarter = tid & 3, tb = tid >> 2;
     const bool validb = sb * SW_SB + tb < p.L;
+    float Bv[4], Cv[4];
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      float4 v;
-      v.x = p.s_B * static_cast<float>(static_cast<int8_t>(r.bq >> (16 * q)));
-      v.y = p.s_B * static_cast<float>(static_cast<int8_t>(r.bq >> (16 * q + 8)));
-      v.z = p.s_C * static_cast<float>(static_cast<int8_t>(r.cq >> (16 * q)));
-      v.w = p.s_C * static_cast<float>(static_cast<int8_t>(r.cq >> (16 * q + 8)));
-      if (!validb) v = make_float4(0.f, 0.f, 0.f, 0.f);
-      sBC[tb][2 * quarter + q] = v;
+    for (int e = 0; e < 4; ++e) {
+      Bv[e] = validb ? p.s_B * static_cast<float>(static_cast<int8_t>(r.bq >> (8 * e))) : 0.f;
+      Cv[e] = validb ? p.s_C * static_cast<float>(static_cast<int8_t>(r.cq >> (8 * e))) : 0.f;
+    }
+    if constexpr (SPL == 2) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q) sBC[tb][2 * quarter + q] = make_float4(Bv[2 * q], Bv[2 * q + 1], Cv[2 * q], Cv[2 * q + 1]);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sBC[tb][4 * quarter + e] = make_float2(Bv[e], Cv[e]);
     }
   };
 
@@ -616,7 +641,8 @@ __global__ __launch_bounds__(SW_THREADS, LAT ? 1 : 3) void scan_sweep_kernel(Dev
   const auto rg = buffer_over(p.g16 + seq0 * p.Di, p.L * p.Di * 2);
   const auto ry = p.y_f32 ? buffer_over(p.y_f32 + seq0 * p.Di, p.L * p.Di * 4) : buffer_over(p.x_q, 0);
   auto store_g = [&](int tok, float gv) {
-    const unsigned e = tok >= 0 && tok < p.L ? static_cast<unsigned>(tok * p.Di + chg) : 0x1fffffffu;
+    const bool mine = LPC == 8 || ng < 8;  // with sixteen lanes per channel both halves hold the sums
+    const unsigned e = mine && tok >= 0 && tok < p.L ? static_cast<unsigned>(tok * p.Di + chg) : 0x1fffffffu;
     buffer_store_f16(rg, 2 * e, 0, gv);
     buffer_store_f32(ry, 4 * e, 0, gv);
   };
@@ -625,14 +651,16 @@ __global__ __launch_bounds__(SW_THREADS, LAT ? 1 : 3) void scan_sweep_kernel(Dev
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const float2 du = sDU[8 * g + j][chl];
-      const float4 bc = sBC[8 * g + j][ng];
-      const float e0 = exp2_fast(du.x * a20), e1 = exp2_fast(du.x * a21);
-      h0 = __builtin_fmaf(e0, h0, du.y * bc.x);
-      h1 = __builtin_fmaf(e1, h1, du.y * bc.y);
-      yp[j] = __builtin_fmaf(bc.w, h1, bc.z * h0);
+      const BCOf<SPL> bc = sBC[8 * g + j][ng];
+      float e[SPL];
+#pragma unroll
+      for (int k = 0; k < SPL; ++k) e[k] = exp2_fast(du.x * a2[k]);
+#pragma unroll
+      for (int k = 0; k < SPL; ++k) h[k] = __builtin_fmaf(e[k], h[k], du.y * b_of<SPL>(bc, k));
+      yp[j] = c_dot<SPL>(bc, h);
     }
-    const float dx = sDX[8 * g + ng][chl];
-    const float zv = p.s_z * static_cast<float>(sZ[8 * g + ng][chl]);
+    const float dx = sDX[8 * g + nt][chl];
+    const float zv = p.s_z * static_cast<float>(sZ[8 * g + nt][chl]);
     // lanes 0-3 of a channel keep tokens 0-3 and take their partner's (lane 7 - i) sums for them, lanes 4-7
     // the same for tokens 4-7; then pairs of tokens inside quads, then single tokens
     float q4[4], q2[2];
@@ -648,13 +676,13 @@ __global__ __launch_bounds__(SW_THREADS, LAT ? 1 : 3) void scan_sweep_kernel(Dev
     }
     const float keep = up1 ? q2[1] : q2[0], send = up1 ? q2[0] : q2[1];
     const float y = keep + dpp_f<0xB1>(send) + dx;  // quad_perm [1, 0, 3, 2]
-    store_g(tok0 + ng, silu_gate(y, zv));
+    store_g(tok0 + nt, silu_gate(y, zv));
   };
 
   // ---- the latency-ordered form of the same group
   struct Rec {
     float2 du[8];
-    float4 bc[8];
+    BCOf<SPL> bc[8];
     float dx;
     int z;
   };
@@ -664,24 +692,27 @@ __global__ __launch_bounds__(SW_THREADS, LAT ? 1 : 3) void scan_sweep_kernel(Dev
       r.du[j] = sDU[8 * g + j][chl];
       r.bc[j] = sBC[8 * g + j][ng];
     }
-    r.dx = sDX[8 * g + ng][chl];
-    r.z = static_cast<int>(sZ[8 * g + ng][chl]);
+    r.dx = sDX[8 * g + nt][chl];
+    r.z = static_cast<int>(sZ[8 * g + nt][chl]);
   };
   struct Pending {  // a group whose sums are complete and whose gate is still to be applied
     float y, zs;
     int tok;
   };
   auto group_lat = [&](const Rec &r, int tok0, Pending &pend) {
-    float e0[8], e1[8], ub0[8], ub1[8];
+    float e[8][SPL], ub[8][SPL];
     float gt = 0.f, gy = pend.y, gz = pend.zs;
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      const float m0 = r.du[j].x * a20, m1 = r.du[j].x * a21;
-      e0[j] = exp2_fast(m0);
-      ub0[j] = r.du[j].y * r.bc[j].x;
-      e1[j] = exp2_fast(m1);
-      ub1[j] = r.du[j].y * r.bc[j].y;
+      float m[SPL];
+#pragma unroll
+      for (int k = 0; k < SPL; ++k) m[k] = r.du[j].x * a2[k];
+#pragma unroll
+      for (int k = 0; k < SPL; ++k) {
+        e[j][k] = exp2_fast(m[k]);
+        ub[j][k] = r.du[j].y * b_of<SPL>(r.bc[j], k);
+      }
       // the previous group's gate, one step per token of this one
       if (j == 0) gt = exp2_fast(-gz * LOG2E);
       if (j == 2) gt = 1.f + gt;
@@ -693,9 +724,9 @@ __global__ __launch_bounds__(SW_THREADS, LAT ? 1 : 3) void scan_sweep_kernel(Dev
     float yp[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      h0 = __builtin_fmaf(e0[j], h0, ub0[j]);
-      h1 = __builtin_fmaf(e1[j], h1, ub1[j]);
-      yp[j] = __builtin_fmaf(r.bc[j].w, h1, r.bc[j].z * h0);
+#pragma unroll
+      for (int k = 0; k < SPL; ++k) h[k] = __builtin_fmaf(e[j][k], h[k], ub[j][k]);
+      yp[j] = c_dot<SPL>(r.bc[j], h);
     }
     __builtin_amdgcn_sched_barrier(0);
     float q4[4], q2[2];
@@ -710,9 +741,11 @@ __global__ __launch_bounds__(SW_THREADS, LAT ? 1 : 3) void scan_sweep_kernel(Dev
       q2[k] = keep + dpp_f<0x4E>(send);
     }
     const float keep = up1 ? q2[1] : q2[0], send = up1 ? q2[0] : q2[1];
-    pend.y = keep + dpp_f<0xB1>(send) + r.dx;
+    float y = keep + dpp_f<0xB1>(send);
+    if constexpr (LPC == 16) y += dpp_f<0x128>(y);  // row_ror 8: the other half of the channel's lanes
+    pend.y = y + r.dx;
     pend.zs = p.s_z * static_cast<float>(r.z);
-    pend.tok = tok0 + ng;
+    pend.tok = tok0 + nt;
   };
   auto flush = [&](Pending &pend) {  // the gate of the last group of a superblock
     store_g(pend.tok, silu_gate(pend.y, pend.zs));
@@ -746,8 +779,11 @@ __global__ __launch_bounds__(SW_THREADS, LAT ? 1 : 3) void scan_sweep_kernel(Dev
     if (more) produce(pre, sb + 1);
     __syncthreads();
   }
-  if (ssm_state)
-    *reinterpret_cast<float2 *>(ssm_state + ((size_t)b * p.Di + chg) * NS + 2 * ng) = make_float2(h0, h1);
+  if (ssm_state) {
+    float *dst = ssm_state + ((size_t)b * p.Di + chg) * NS + SPL * ng;
+    if constexpr (SPL == 2) *reinterpret_cast<float2 *>(dst) = make_float2(h[0], h[1]);
+    else dst[0] = h[0];
+  }
 }
 
 // ---------------------------------------------------------------- decode: one step
@@ -1039,6 +1075,11 @@ bool sweep_layout_ok(const ScanArgs &a) {
   return aligned(a.dt_q, 4);
 }
 
+// Few channels (int8 x on the calibrated grid): one state per lane and twice the workgroups, while they still find a CU each.  A lone wave pays
+// per instruction, and a token then takes it 47 ns instead of 64.5 (1536 wide: 1 x 256 tokens 44.5 -> 40.0 us a mixer, 2 x 500 66.7 -> 58.3; with
+// two such workgroups on some CUs, 1 x 512 x 5120, 95.3 -> 97.4).
+bool one_state_per_lane(int Bt, int Di) { return (long)Bt * (Di / 16) <= 256; }
+
 // Which form is faster, from fits to measured times (microseconds; W = workgroups of the sweep = Bt * Di / 32,
 // k = workgroups per CU):
 //   sweep    3.6 + L * s(k): a wave alone on its SIMD walks a token in 65 ns (a lone wave issues one instruction
@@ -1046,13 +1087,16 @@ bool sweep_layout_ok(const ScanArgs &a) {
 //            SIMD is busy, 40 ns per token and wave
 //   chunked  30 + L * (W / 256) * 52 ns: three launches and the carry, every exponential taken twice
 // so the sweep takes the short sequences and the batches, the chunked form a long single sequence.
+// With one state per lane the sweep takes 3.6 + L 47 ns; the chunked form at those widths 21 + L * (W / 256) * 65 ns (1536 wide, 1 x 256 to 900
+// and 2 x 200 to 500 tokens: the same time at 500 tokens of one sequence).
 double sweep_us(int Bt, int L, int Di) {
   const int k = (int)std::ceil((double)Bt * (Di / SW_CH) / 256.0);
   return 3.6 + L * (k <= 1 ? 0.0645 : (k == 2 ? 0.098 : 0.040 * k));
 }
 
-bool sweep_is_cheaper(int Bt, int L, int Di) {
+bool sweep_is_cheaper(int Bt, int L, int Di, bool one_state) {
   const double W = (double)Bt * (Di / SW_CH);
+  if (one_state) return 3.6 + L * 0.047 < 21.0 + (double)L * (W / 256.0) * 0.065;
   return sweep_us(Bt, L, Di) < 30.0 + (double)L * (W / 256.0) * 0.052;
 }
 
@@ -1076,11 +1120,11 @@ bool read_ahead_pays(int Bt, int L, int Di, size_t bytes, bool sweep) {
   return bytes < 20000000 && (double)tokens * (double)bytes <= 2.2e10 && (!sweep || (fits && (double)bytes / 2e6 <= sweep_us(Bt, L, Di)));
 }
 
-template <int NK, int XM, bool LAT>
+template <int NK, int XM, bool LAT, int SPL = 2>
 int run_sweep(const Dev &p, const ScanArgs &a, hipStream_t st) {
   Dev q = p;
   if (q.warm.n16[0] || q.warm.n16[1] || q.warm.n16[2]) q.warm.blocks = sweep_warm_blocks(a.Bt);
-  hipLaunchKernelGGL((scan_sweep_kernel<NK, XM, LAT>), dim3(a.Di / SW_CH + q.warm.blocks, a.Bt), dim3(SW_THREADS), 0, st, q,
+  hipLaunchKernelGGL((scan_sweep_kernel<NK, XM, LAT, SPL>), dim3(a.Di / (16 * SPL) + q.warm.blocks, a.Bt), dim3(SW_THREADS), 0, st, q,
                      a.ssm_state);
   QUAMBA_LAUNCH_CHECK();
   return QUAMBA_OK;
@@ -1092,6 +1136,11 @@ template <int XM>
 int dispatch_sweep(const Dev &p, const ScanArgs &a, hipStream_t st) {
   const bool lat = XM == X_I8 && (long)a.Bt * (a.Di / SW_CH) <= 256;
   if constexpr (XM == X_I8) {
+    if (lat && one_state_per_lane(a.Bt, a.Di)) {
+      if (!a.dtlow_q) return run_sweep<0, XM, true, 1>(p, a, st);
+      if (a.R <= 192) return run_sweep<3, XM, true, 1>(p, a, st);
+      return run_sweep<4, XM, true, 1>(p, a, st);
+    }
     if (lat) {
       if (!a.dtlow_q) return run_sweep<0, XM, true>(p, a, st);
       if (a.R <= 192) return run_sweep<3, XM, true>(p, a, st);
@@ -1110,7 +1159,7 @@ int launch_scan_prefill(const ScanArgs &a, void *ws, size_t ws_bytes, hipStream_
     return fail(QUAMBA_EWORKSPACE, "scan: workspace %zu < %zu", ws_bytes, scan_workspace_bytes(a.Bt, a.L, a.Di));
   Dev p = make_dev(a);
   const int variant = g_scan_variant_hook.load(std::memory_order_relaxed);
-  const bool sweep = variant != 1 && sweep_layout_ok(a) && (variant == 2 || sweep_is_cheaper(a.Bt, a.L, a.Di));
+  const bool sweep = variant != 1 && sweep_layout_ok(a) && (variant == 2 || sweep_is_cheaper(a.Bt, a.L, a.Di, scan_x_mode(a) == X_I8 && one_state_per_lane(a.Bt, a.Di)));
   if (a.warm_if_it_pays && !read_ahead_pays(a.Bt, a.L, a.Di, a.warm_bytes[0], sweep)) p.warm = WarmRanges{};
   if (sweep) {
     switch (scan_x_mode(a)) {
@@ -1231,5 +1280,5 @@ int launch_scan_step(const ScanArgs &a, hipStream_t st) {
 extern "C" void quamba_debug_set_scan_variant(int v) { quamba::g_scan_variant_hook.store(v); }
 extern "C" int quamba_debug_last_block_reads_ahead(int batch, int L, int d_model, int d_inner) {
   if (batch < 1 || L < 1 || d_model < 16 || d_inner < 16 || d_inner % quamba::SW_CH) return 0;
-  return quamba::read_ahead_pays(batch, L, d_inner, (size_t)d_model * d_inner, quamba::sweep_is_cheaper(batch, L, d_inner));
+  return quamba::read_ahead_pays(batch, L, d_inner, (size_t)d_model * d_inner, quamba::sweep_is_cheaper(batch, L, d_inner, quamba::one_state_per_lane(batch, d_inner)));
 }

@@ -316,7 +316,9 @@ def scan_variant(request):
                                               (9, 40, 1024, True),  # more than one workgroup per CU in the sweep
                                               # sequence ends on either side of the sweep's 64-token superblocks and 8-token groups
                                               (5, 65, 64, True), (1, 63, 32, False), (3, 127, 96, True), (2, 64, 64, False),
-                                              (1, 71, 160, True)])
+                                              (1, 71, 160, True),
+                                              # the widest rows of one state per lane (256 workgroups), and just past them two
+                                              (4, 65, 1024, True), (5, 65, 1024, True), (5, 63, 1024, False), (5, 131, 1024, True)])
 def test_scan_prefill(Bt, L, Di, with_h0, scan_variant):
     rng = np.random.default_rng(L * 31 + Di)
     sc, x, dt, xz, dbc, A, D, bias = _scan_inputs(rng, Bt, L, Di)
@@ -348,7 +350,9 @@ def test_scan_prefill(Bt, L, Di, with_h0, scan_variant):
                                                 (9, 70, 1024, 64, True),  # more than one sweep workgroup per CU
                                                 # whole workgroups of channels and dt_rank <= 160: the chunked pass stages its
                                                 # dt_proj operands in LDS (one piece per row, an odd number of pieces, nine)
-                                                (2, 200, 256, 16, True), (1, 333, 512, 80, False), (1, 97, 768, 144, True)])
+                                                (2, 200, 256, 16, True), (1, 333, 512, 80, False), (1, 97, 768, 144, True),
+                                                # two states per lane in the form for at most one sweep workgroup per CU
+                                                (5, 129, 1024, 48, True), (6, 65, 1024, 256, False)])
 def test_scan_prefill_with_fused_dt_proj(Bt, L, Di, R, with_h0, scan_variant):
     """dt_q computed inside the scan's first pass: bit-exact codes, same scan tolerances."""
     rng = np.random.default_rng(L * 17 + Di + R)
