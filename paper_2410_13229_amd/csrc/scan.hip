@@ -1075,10 +1075,11 @@ bool sweep_layout_ok(const ScanArgs &a) {
   return aligned(a.dt_q, 4);
 }
 
-// Few channels (int8 x on the calibrated grid): one state per lane and twice the workgroups, while they still find a CU each.  A lone wave pays
-// per instruction, and a token then takes it 47 ns instead of 64.5 (1536 wide: 1 x 256 tokens 44.5 -> 40.0 us a mixer, 2 x 500 66.7 -> 58.3; with
-// two such workgroups on some CUs, 1 x 512 x 5120, 95.3 -> 97.4).
-bool one_state_per_lane(int Bt, int Di) { return (long)Bt * (Di / 16) <= 256; }
+// Few channels (int8 x on the calibrated grid): one state per lane and twice the workgroups, while they find a CU each and leave some to the
+// workgroups that read ahead in a stack (256 of them leave none).  A lone wave pays per instruction, and a token then takes it 47 ns
+// instead of 64.5 (1536 wide: 1 x 256 tokens 44.5 -> 40.0 us a mixer, 2 x 500 66.7 -> 58.3; with two such workgroups on some CUs,
+// 1 x 512 x 5120, 95.3 -> 97.4).
+bool one_state_per_lane(int Bt, int Di) { return (long)Bt * (Di / 16) <= 192; }
 
 // Which form is faster, from fits to measured times (microseconds; W = workgroups of the sweep = Bt * Di / 32,
 // k = workgroups per CU):
@@ -1112,8 +1113,8 @@ int sweep_warm_blocks(int Bt) { return std::max(1, 96 / Bt); }  // per sequence:
 //     the read at 2 TB/s and small projections, 1680 tokens of the 2.8B layer (16 x 32 156.7 -> 152.3, 1 x 1152 248.9 -> 241.1,
 //     9 x 179 238.5 -> 233.3, 64 x 1 164.6 -> 166.2; 8 x 512 414 -> 427, 1 x 4096 464 -> 472), up to 20 MB (Jamba's layer, 33 MB:
 //     27 x 21 312 -> 304, but 52 x 9 329 -> 341)
-bool read_ahead_pays(int Bt, int L, int Di, size_t bytes, bool sweep) {
-  const long wgs = (long)Bt * (Di / SW_CH), rest = wgs % 256, tokens = (long)Bt * L;
+bool read_ahead_pays(int Bt, int L, int Di, size_t bytes, bool sweep, bool one_state) {
+  const long wgs = (long)Bt * (Di / (sweep && one_state ? SW_CH / 2 : SW_CH)), rest = wgs % 256, tokens = (long)Bt * L;
   const bool fits = rest + (long)sweep_warm_blocks(Bt) * Bt <= 256;
   if (bytes < 12000000) return false;
   if (sweep && wgs <= 768) return fits && rest > 0 && tokens <= 2048 && (double)bytes / 3.5e6 <= sweep_us(Bt, L, Di);
@@ -1159,8 +1160,9 @@ int launch_scan_prefill(const ScanArgs &a, void *ws, size_t ws_bytes, hipStream_
     return fail(QUAMBA_EWORKSPACE, "scan: workspace %zu < %zu", ws_bytes, scan_workspace_bytes(a.Bt, a.L, a.Di));
   Dev p = make_dev(a);
   const int variant = g_scan_variant_hook.load(std::memory_order_relaxed);
-  const bool sweep = variant != 1 && sweep_layout_ok(a) && (variant == 2 || sweep_is_cheaper(a.Bt, a.L, a.Di, scan_x_mode(a) == X_I8 && one_state_per_lane(a.Bt, a.Di)));
-  if (a.warm_if_it_pays && !read_ahead_pays(a.Bt, a.L, a.Di, a.warm_bytes[0], sweep)) p.warm = WarmRanges{};
+  const bool one_state = scan_x_mode(a) == X_I8 && one_state_per_lane(a.Bt, a.Di);
+  const bool sweep = variant != 1 && sweep_layout_ok(a) && (variant == 2 || sweep_is_cheaper(a.Bt, a.L, a.Di, one_state));
+  if (a.warm_if_it_pays && !read_ahead_pays(a.Bt, a.L, a.Di, a.warm_bytes[0], sweep, one_state)) p.warm = WarmRanges{};
   if (sweep) {
     switch (scan_x_mode(a)) {
       case X_E4M3: return dispatch_sweep<X_E4M3>(p, a, st);
@@ -1280,5 +1282,6 @@ int launch_scan_step(const ScanArgs &a, hipStream_t st) {
 extern "C" void quamba_debug_set_scan_variant(int v) { quamba::g_scan_variant_hook.store(v); }
 extern "C" int quamba_debug_last_block_reads_ahead(int batch, int L, int d_model, int d_inner) {
   if (batch < 1 || L < 1 || d_model < 16 || d_inner < 16 || d_inner % quamba::SW_CH) return 0;
-  return quamba::read_ahead_pays(batch, L, d_inner, (size_t)d_model * d_inner, quamba::sweep_is_cheaper(batch, L, d_inner, quamba::one_state_per_lane(batch, d_inner)));
+  const bool one_state = quamba::one_state_per_lane(batch, d_inner);
+  return quamba::read_ahead_pays(batch, L, d_inner, (size_t)d_model * d_inner, quamba::sweep_is_cheaper(batch, L, d_inner, one_state), one_state);
 }

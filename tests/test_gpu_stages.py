@@ -317,8 +317,8 @@ def scan_variant(request):
                                               # sequence ends on either side of the sweep's 64-token superblocks and 8-token groups
                                               (5, 65, 64, True), (1, 63, 32, False), (3, 127, 96, True), (2, 64, 64, False),
                                               (1, 71, 160, True),
-                                              # the widest rows of one state per lane (256 workgroups), and just past them two
-                                              (4, 65, 1024, True), (5, 65, 1024, True), (5, 63, 1024, False), (5, 131, 1024, True)])
+                                              # the widest rows of one state per lane (192 workgroups), and past them two
+                                              (3, 65, 1024, True), (4, 65, 1024, True), (5, 65, 1024, True), (5, 63, 1024, False), (5, 131, 1024, True)])
 def test_scan_prefill(Bt, L, Di, with_h0, scan_variant):
     rng = np.random.default_rng(L * 31 + Di)
     sc, x, dt, xz, dbc, A, D, bias = _scan_inputs(rng, Bt, L, Di)
