@@ -15,7 +15,8 @@
 // per work item at a power-of-two stride, transforms them in registers and scatters them back.
 // The last pass covers the lowest four index bits, so every work item ends with 16 adjacent
 // outputs, which it scales, rounds, clamps and stores as one 16-byte word.  The LDS row is
-// padded by 4 floats every 16 so that this 16-byte-per-lane pass is bank-conflict free.
+// padded by 4 floats every 16 so that this 16-byte-per-lane pass is bank-conflict free.  The passes are
+// in hadamard_row.h; the kernel of a whole generation stack runs them too.
 #include <atomic>
 
 #include "common.h"
