@@ -616,6 +616,12 @@ int quamba_probe_rate(int probe, int waves_per_simd, int iters, double *instr_pe
  *                                      them, before the launcher cuts rows; -1 = few-row streaming kernel, -2 = not served
  *   quamba_debug_xfmt_column_tiles(M, N, K)  x_proj of the 8-bit float formats: column tiles per wave, 1 = the
  *                                      column groups are spread over the grid; 0 = not served
+ *   quamba_debug_decode_stack_words(d_model, d_inner, dt_rank, batch, role, item, out, cap)  generation of a stack
+ *                                      in one launch: the words that an item of a role (0 in_proj, 1 x_proj, 2 scan
+ *                                      step, 3 out_proj) deals with in a block, four numbers each in out[cap][4]: buffer
+ *                                      (0 residual stream, 1 x, 2 z, 3 x_proj output, 4 gated output), word, tag minus
+ *                                      number of the block, 0 = written / 1 = awaited with this tag / 2 = watched
+ *                                      until this tag or a later one; returns their number, -1 = no such item
  *   quamba_debug_last_block_reads_ahead(batch, L, d_model, d_inner)  1 = the scan of a stack's last block reads
  *                                      that block's out_proj weights ahead in a prefill
  * ------------------------------------------------------------------------------------- */
@@ -628,6 +634,7 @@ void quamba_debug_set_scan_variant(int v);
 void quamba_debug_set_decode_stack(int v);
 int quamba_debug_gemm_kind(int M, int N, int K);
 int quamba_debug_xfmt_column_tiles(int M, int N, int K);
+int quamba_debug_decode_stack_words(int d_model, int d_inner, int dt_rank, int batch, int role, int item, int32_t *out, int cap);
 int quamba_debug_last_block_reads_ahead(int batch, int L, int d_model, int d_inner);
 
 #ifdef __cplusplus

@@ -126,6 +126,17 @@ __device__ __host__ __forceinline__ int pair_at(int row, int pair) {  // residua
 __device__ __host__ __forceinline__ int gate_at(int d) {  // gated output: channels d, d + 1
   return d / (BC_THREADS / 4) * (2 * LINE) + d % (BC_THREADS / 4) / 2;
 }
+__device__ __host__ __forceinline__ int dbc_at(int row, int quad) { return quad * LINE + row; }  // x_proj codes: four columns
+
+// The words watched by wait_ahead, spread over the workgroups: item idx of a role first watches a word of the role in front, then one that it awaits.
+__device__ __host__ __forceinline__ int in_front(int idx, int nC) { return idx % nC * (2 * LINE); }         // g of the block before
+__device__ __host__ __forceinline__ int in_watch(int idx, int nD) { return idx * 37 % nD * LINE; }          // s
+__device__ __host__ __forceinline__ int x_front(int idx) { return idx * LINE; }                             // s
+__device__ __host__ __forceinline__ int x_watch(int idx, int n) { return quad_at(idx * 37 % (n / 4)); }     // x
+__device__ __host__ __forceinline__ int scan_front(int idx) { return quad_at(idx); }                        // x
+__device__ __host__ __forceinline__ int scan_watch(int idx, int nB) { return idx % nB * LINE; }             // dbc
+__device__ __host__ __forceinline__ int out_front(int idx, int nB) { return idx % nB * LINE; }              // dbc
+__device__ __host__ __forceinline__ int out_watch(int idx, int nC) { return idx * 37 % nC * (2 * LINE); }   // g
 
 // Polls base[idx[j]] until all N words carry `tag`; the payloads are left in v.
 template <int N>
@@ -151,14 +162,18 @@ __device__ __forceinline__ void wait_words(const u64 *base, const int (&idx)[N],
   }
 }
 
+// Does this tag end a watch?  A later one does as well: nothing keeps the word in front from being overwritten before the watching wave has looked (a gated
+// output of the block before may be, by channels whose z codes other columns form).
+__device__ __host__ __forceinline__ bool watch_ends(unsigned tag, unsigned wanted) { return tag >= wanted; }
+
 // What one wave of a role does for all of them before wait_words reads every word: it watches one of the awaited words, and before that,
 // at a slow pace, one word of the role in front.  All words of all waiting workgroups polled all the time keep the memory
 // side so busy that the stores they wait for hardly get through.
 __device__ __forceinline__ void wait_ahead(const u64 *front, unsigned front_tag, const u64 *word, unsigned tag, bool dead) {
   int tries = 0;
   if (front)
-    for (; static_cast<unsigned>(word_load(front) >> 32) != front_tag && !dead && tries < WAIT_TRIES; ++tries) __builtin_amdgcn_s_sleep(FRONT_PACE);
-  for (; static_cast<unsigned>(word_load(word) >> 32) != tag && !dead && tries < WAIT_TRIES; ++tries) __builtin_amdgcn_s_sleep(PACE);
+    for (; !watch_ends(static_cast<unsigned>(word_load(front) >> 32), front_tag) && !dead && tries < WAIT_TRIES; ++tries) __builtin_amdgcn_s_sleep(FRONT_PACE);
+  for (; !watch_ends(static_cast<unsigned>(word_load(word) >> 32), tag) && !dead && tries < WAIT_TRIES; ++tries) __builtin_amdgcn_s_sleep(PACE);
 }
 
 // A scale read now: left to the compiler, the scalar load of a descriptor field lands where the value is needed, behind the waits.
@@ -281,7 +296,7 @@ __device__ __forceinline__ void role_in(const StackArgs &p, int l, int idx, int8
   }
   const float inv_s_u = now(q->inv_s_u), m_in_x = now(q->m_in_x), m_in_z = now(q->m_in_z), s_cw = now(q->s_cw), s_xpre = now(q->s_xpre),
               inv_s_x = now(q->inv_s_x);
-  if (wave == 0) wait_ahead(l ? p.w.g + idx % p.nC * (2 * LINE) : nullptr, l, p.w.s + idx * 37 % p.nD * LINE, l + 1, dead);
+  if (wave == 0) wait_ahead(l ? p.w.g + in_front(idx, p.nC) : nullptr, l, p.w.s + in_watch(idx, p.nD), l + 1, dead);
   sync();
   {  // the rows, as whole lines, into LDS
     constexpr int NWORD = (MB * PF * 512 + 64 * A_WAVES - 1) / (64 * A_WAVES);
@@ -413,7 +428,7 @@ __device__ __forceinline__ void role_x(const StackArgs &p, int l, int idx, int8_
 #pragma unroll
     for (int j = 0; j < 4; ++j) w[r][j] = gload<v4i>(q->W_x + (size_t)(n0 + j) * n + min(tid + BC_THREADS * r, nch - 1) * 16);
   const float m_x = now(n0 < p.R ? q->m_x_dt : (n0 < p.R + NS ? q->m_x_B : q->m_x_C));
-  if (wave == 0) wait_ahead(p.w.s + idx * LINE, l + 1, p.w.x + quad_at(idx * 37 % (n / 4)), l + 1, dead);
+  if (wave == 0) wait_ahead(p.w.s + x_front(idx), l + 1, p.w.x + x_watch(idx, n), l + 1, dead);
   sync();
   constexpr int NWORD = (n / 4 + BC_THREADS - 1) / BC_THREADS;
 #pragma unroll
@@ -454,7 +469,7 @@ __device__ __forceinline__ void role_x(const StackArgs &p, int l, int idx, int8_
     for (int wv = 0; wv < BC_WAVES; ++wv)
 #pragma unroll
       for (int j = 0; j < 4; ++j) a[j] += red[wv][tid * 4 + j];
-    word_store(p.w.dbc + idx * LINE + tid, requant_pack4(a, m_x), l + 1);
+    word_store(p.w.dbc + dbc_at(tid, idx), requant_pack4(a, m_x), l + 1);
   }
 }
 
@@ -496,7 +511,7 @@ __device__ __forceinline__ void role_scan(const StackArgs &p, int l, int idx, in
   }
   const float m_dt = now(q->m_dt), s_x = now(q->s_x), s_dt = now(q->s_dt), s_z = now(q->s_z), s_B = now(q->s_B), s_C = now(q->s_C),
               s_A = now(q->s_A), s_D = now(q->s_D);
-  if (tid < 64) wait_ahead(p.w.x + quad_at(idx), l + 1, p.w.dbc + idx % p.nB * LINE, l + 1, dead);
+  if (tid < 64) wait_ahead(p.w.x + scan_front(idx), l + 1, p.w.dbc + scan_watch(idx, p.nB), l + 1, dead);
   sync();
   unsigned xw[MB], zw[MB];
   {
@@ -507,7 +522,7 @@ __device__ __forceinline__ void role_scan(const StackArgs &p, int l, int idx, in
     wait_words(p.w.z, at, l + 1, zw, p.w.ctrl, dead);
   }
   for (int i = tid; i < MB * (NX / 4); i += BC_THREADS) {
-    const int at[1] = {i % (NX / 4) * LINE + i / (NX / 4)};
+    const int at[1] = {dbc_at(i / (NX / 4), i % (NX / 4))};
     unsigned dw[1];
     wait_words(p.w.dbc, at, l + 1, dw, p.w.ctrl, dead);
     reinterpret_cast<unsigned *>(sdbc)[i] = dw[0];
@@ -598,7 +613,7 @@ __device__ __forceinline__ void role_out(const StackArgs &p, int l, int idx, flo
     else to[k] = pad(i) * 4;
     asm volatile("" : "+v"(at[k]), "+v"(to[k]));
   }
-  if (wave == 0) wait_ahead(p.w.dbc + idx % p.nB * LINE, l + 1, p.w.g + idx * 37 % p.nC * (2 * LINE), l + 1, dead);
+  if (wave == 0) wait_ahead(p.w.dbc + out_front(idx, p.nB), l + 1, p.w.g + out_watch(idx, p.nC), l + 1, dead);
   sync();
 #pragma unroll
   for (int r = 0; r < MB; ++r) {
@@ -801,14 +816,23 @@ bool fits(int groups, size_t lds) {
   return groups <= v;
 }
 
+// Items of each role in one block.
+struct Items {
+  int nA, nB, nC, nD;
+};
+Items stack_items(int Dm, int Di, int R) {
+  return Items{(2 * Di + A_COLS - 1) / A_COLS, (R + 2 * NS) / 4, (Di * 4 + BC_THREADS - 1) / BC_THREADS, (Dm + D_COLS - 1) / D_COLS};
+}
+
 template <int K, int LOGM, int MB, typename Begin>
 int run_stack(const StackArgs &args, const Begin &begin, bool *served, hipStream_t st) {
   constexpr int n = K << LOGM;
   StackArgs p = args;
-  p.nA = (2 * p.Di + A_COLS - 1) / A_COLS;
-  p.nB = (p.R + 2 * NS) / 4;
-  p.nC = (p.Di * 4 + BC_THREADS - 1) / BC_THREADS;
-  p.nD = (p.Dm + D_COLS - 1) / D_COLS;
+  const Items items = stack_items(p.Dm, n, p.R);
+  p.nA = items.nA;
+  p.nB = items.nB;
+  p.nC = items.nC;
+  p.nD = items.nD;
   p.x_row = stack_x_row(n);
   p.g_row = stack_g_row(n);
   const int G = std::max(std::max(p.nA, p.nD), p.nB + p.nC);
@@ -873,6 +897,66 @@ int launch_decode_stack(const quamba_model *m, const int32_t *tokens, int Bt, fl
   return QUAMBA_OK;
 }
 
+// The words one item of a role (0 = A, 1 = B, 2 = C, 3 = D) deals with in a block, as the kernel forms their places; four numbers for each: buffer (0 s, 1 x, 2 z,
+// 3 dbc, 4 g), word, tag minus number of the block, how (0 written, 1 awaited with this tag, 2 watched until this tag or a later one).
+// Returns how many there are; the first `cap` are stored.
+int stack_words(int Dm, int Di, int R, int Bt, int role, int item, int32_t *out, int cap) {
+  const Items n = stack_items(Dm, Di, R);
+  const int count[4] = {n.nA, n.nB, n.nC, n.nD};
+  if (role < 0 || role > 3 || item < 0 || item >= count[role] || Bt < 1 || Bt > 2) return -1;
+  const int xr = stack_x_row(Di), gr = stack_g_row(Di);
+  int k = 0;
+  auto put = [&](int buffer, int word, int tag, int how) {
+    if (k < cap) {
+      const int32_t e[4] = {buffer, word, tag, how};
+      std::copy(e, e + 4, out + 4 * k);
+    }
+    ++k;
+  };
+  for (int m = 0; m < Bt; ++m) {
+    if (role == 0) {
+      for (int i = 0; i < Dm / 2; ++i) put(0, pair_at(m, i), 1, 1);
+      for (int c = item * A_COLS; c < std::min((item + 1) * A_COLS, 2 * Di); c += 4)
+        put(c < Di ? 1 : 2, m * xr + quad_at((c < Di ? c : c - Di) / 4), 1, 0);
+    } else if (role == 1) {
+      for (int i = 0; i < Di / 4; ++i) put(1, m * xr + quad_at(i), 1, 1);
+      put(3, dbc_at(m, item), 1, 0);
+    } else if (role == 2) {
+      for (int d = item * (BC_THREADS / 4); d < std::min((item + 1) * (BC_THREADS / 4), Di); ++d) {
+        put(1, m * xr + quad_at(d / 4), 1, 1);
+        put(2, m * xr + quad_at(d / 4), 1, 1);
+        if (d % 2 == 0) put(4, m * gr + gate_at(d), 1, 0);
+      }
+      for (int i = 0; i < n.nB; ++i) put(3, dbc_at(m, i), 1, 1);
+    } else {
+      for (int i = 0; i < Di / 2; ++i) put(4, m * gr + gate_at(2 * i), 1, 1);
+      for (int c = item * D_COLS; c < std::min((item + 1) * D_COLS, Dm); c += 2) {
+        put(0, pair_at(m, c / 2), 1, 1);
+        put(0, pair_at(m, c / 2), 2, 0);
+      }
+    }
+  }
+  const int watch = watch_ends(2, 1) ? 2 : 1;
+  if (role == 0) {
+    put(4, in_front(item, n.nC), 0, watch);
+    put(0, in_watch(item, n.nD), 1, watch);
+  } else if (role == 1) {
+    put(0, x_front(item), 1, watch);
+    put(1, x_watch(item, Di), 1, watch);
+  } else if (role == 2) {
+    put(1, scan_front(item), 1, watch);
+    put(3, scan_watch(item, n.nB), 1, watch);
+  } else {
+    put(3, out_front(item, n.nB), 1, watch);
+    put(4, out_watch(item, n.nC), 1, watch);
+  }
+  return k;
+}
+
 }  // namespace quamba
 
+extern "C" int quamba_debug_decode_stack_words(int d_model, int d_inner, int dt_rank, int batch, int role, int item, int32_t *out, int cap) {
+  if (d_model < 16 || d_inner < 16 || dt_rank < 16 || (cap > 0 && !out)) return -1;
+  return quamba::stack_words(d_model, d_inner, dt_rank, batch, role, item, out, cap);
+}
 extern "C" void quamba_debug_set_decode_stack(int v) { quamba::g_decode_stack_hook.store(v); }

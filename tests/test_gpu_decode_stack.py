@@ -129,6 +129,31 @@ def test_two_steps_in_flight():
     del keep
 
 
+@pytest.mark.parametrize("Bt", [1, 2])
+def test_four_users_for_many_steps(Bt):
+    """Four streams that keep the GPU full, so that the launches of a step start piecemeal and hold one another up: a workgroup
+    may be late at any word of the hand-over."""
+    n, steps = 16, 40
+    d, m, keep = _model(2560, 5120, 160, n, 14)
+    want = _steps(d, m, n, Bt, 1, steps=steps)
+    for rep in range(4):
+        streams, runs = [torch.cuda.Stream() for _ in range(4)], []
+        for _ in streams:
+            ssm, conv = _states(d, n, Bt, 5)
+            runs.append((torch.arange(Bt, dtype=torch.int32, device=DEV) * 40 + 3, empty((Bt, VOCAB), torch.float32), ssm, conv,
+                         workspace(Q.quamba_model_workspace_bytes(m, Bt, 1))))
+        torch.cuda.synchronize()
+        for _ in range(steps):
+            for s, (tok, logits, ssm, conv, ws) in zip(streams, runs):
+                Q.quamba_model_decode(m, tok, Bt, logits, tok, ssm, conv, ws, s.cuda_stream)
+        torch.cuda.synchronize()
+        print("four users", Bt, "repetition", rep, flush=True)
+        for tok, logits, ssm, conv, _ in runs:
+            assert torch.equal(logits, want[-4]) and torch.equal(tok, want[-3])
+            assert torch.equal(ssm, want[-2]) and torch.equal(conv, want[-1])
+    del keep
+
+
 @pytest.mark.parametrize("Bt", [3, 20])
 def test_weights_read_ahead_change_nothing(Bt):
     """A stack whose weights exceed the last-level cache (the same block seven times: 280 MB): norm and Hadamard launches with workgroups that
