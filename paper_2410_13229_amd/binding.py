@@ -732,14 +732,14 @@ def quamba_debug_last_block_reads_ahead(batch, L, d_model, d_inner) -> bool:
 
 
 def quamba_debug_decode_stack_words(d_model, d_inner, dt_rank, batch, role, item):
-    """Rows (buffer, word, tag minus number of the block, how) of one item, or None where there is no such item."""
+    """(buffer, word, tag minus number of the block, how) of one word after the other, as a ctypes array; None: no such item."""
     args = [int(v) for v in (d_model, d_inner, dt_rank, batch, role, item)]
     n = lib().quamba_debug_decode_stack_words(*args, None, 0)
     if n < 0:
         return None
     out = (C.c_int32 * (4 * n))()
     lib().quamba_debug_decode_stack_words(*args, out, n)
-    return [tuple(out[4 * k:4 * k + 4]) for k in range(n)]
+    return out
 
 
 # ---- diagnostics: instruction-rate probes

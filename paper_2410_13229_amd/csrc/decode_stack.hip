@@ -131,7 +131,7 @@ __device__ __host__ __forceinline__ int dbc_at(int row, int quad) { return quad 
 // The words watched by wait_ahead, spread over the workgroups: item idx of a role first watches a word of the role in front, then one that it awaits.
 __device__ __host__ __forceinline__ int in_front(int idx, int nC) { return idx % nC * (2 * LINE); }         // g of the block before
 __device__ __host__ __forceinline__ int in_watch(int idx, int nD) { return idx * 37 % nD * LINE; }          // s
-__device__ __host__ __forceinline__ int x_front(int idx) { return idx * LINE; }                             // s
+__device__ __host__ __forceinline__ int x_front(int idx, int nD) { return idx % nD * LINE; }                // s
 __device__ __host__ __forceinline__ int x_watch(int idx, int n) { return quad_at(idx * 37 % (n / 4)); }     // x
 __device__ __host__ __forceinline__ int scan_front(int idx) { return quad_at(idx); }                        // x
 __device__ __host__ __forceinline__ int scan_watch(int idx, int nB) { return idx % nB * LINE; }             // dbc
@@ -428,7 +428,7 @@ __device__ __forceinline__ void role_x(const StackArgs &p, int l, int idx, int8_
 #pragma unroll
     for (int j = 0; j < 4; ++j) w[r][j] = gload<v4i>(q->W_x + (size_t)(n0 + j) * n + min(tid + BC_THREADS * r, nch - 1) * 16);
   const float m_x = now(n0 < p.R ? q->m_x_dt : (n0 < p.R + NS ? q->m_x_B : q->m_x_C));
-  if (wave == 0) wait_ahead(p.w.s + x_front(idx), l + 1, p.w.x + x_watch(idx, n), l + 1, dead);
+  if (wave == 0) wait_ahead(p.w.s + x_front(idx, p.nD), l + 1, p.w.x + x_watch(idx, n), l + 1, dead);
   sync();
   constexpr int NWORD = (n / 4 + BC_THREADS - 1) / BC_THREADS;
 #pragma unroll
@@ -749,10 +749,10 @@ __global__ __launch_bounds__(STACK_THREADS) void decode_stack_kernel(StackArgs p
 }
 
 // Descriptors of up to CHUNK_LAYERS blocks; the first launch also sets up the words: the residual stream of block 0 is the embedding
-// of the token (plus zero, as the first add of the separate kernels has it), all other words and the control words zero.
+// of the token (plus zero, as the first add of the separate kernels has it), all other words (those between the lines among them) and the control
+// words zero.
 __global__ __launch_bounds__(256) void stack_begin_kernel(LayerChunk chunk, StackLayer *dst, int count, const __half *E,
-                                                          const int32_t *tokens, int M, int Dm, int vocab, Words w, u64 *clear,
-                                                          unsigned n_clear) {
+                                                          const int32_t *tokens, int M, int Dm, int vocab, Words w, unsigned n_words) {
   if (blockIdx.x == 0) {
     // (read through the argument segment: indexing the by-value struct would copy it to scratch first)
     typedef __attribute__((address_space(4))) const unsigned *args_t;
@@ -760,17 +760,19 @@ __global__ __launch_bounds__(256) void stack_begin_kernel(LayerChunk chunk, Stac
     for (int i = threadIdx.x; i < count * (int)(sizeof(StackLayer) / 4); i += 256) reinterpret_cast<unsigned *>(dst)[i] = src[i];
   }
   if (!E) return;
+  // the words of the residual stream come first
   const unsigned i = blockIdx.x * 256 + threadIdx.x;
-  if (i < n_clear) clear[i] = 0;
-  const unsigned per = Dm / 2;
-  if (i < M * per) {
-    const int m = i / per, c = i % per;
+  if (i >= n_words) return;
+  u64 word = 0;
+  const int slot = i % LINE, m = slot / (D_COLS / 2), c = i / LINE * (D_COLS / 2) + slot % (D_COLS / 2);
+  if (m < M && c < Dm / 2) {  // i = pair_at(m, c)
     const int tok = min(max(tokens[m], 0), vocab - 1);
     const __half2 e = reinterpret_cast<const __half2 *>(E + (size_t)tok * Dm)[c];
     const unsigned lo = __half_as_ushort(__float2half_rn(0.f + __half2float(__low2half(e))));
     const unsigned hi = __half_as_ushort(__float2half_rn(0.f + __half2float(__high2half(e))));
-    w.s[pair_at(m, c)] = (1ull << 32) | lo | (hi << 16);
+    word = (1ull << 32) | lo | (hi << 16);
   }
+  w.s[i] = word;
 }
 
 struct StackCarve {
@@ -788,7 +790,7 @@ StackCarve stack_carve(int n_layers, int M, int Dm, int Di, int R) {
   };
   c.layers = take((size_t)n_layers * sizeof(StackLayer));
   c.s = take((size_t)((Dm + D_COLS - 1) / D_COLS) * LINE * 8);
-  c.x = take((size_t)M * stack_x_row(Di) * 8);  // from here on cleared
+  c.x = take((size_t)M * stack_x_row(Di) * 8);
   c.z = take((size_t)M * stack_x_row(Di) * 8);
   c.dbc = take((size_t)(R + 2 * NS) / 4 * LINE * 8);
   c.g = take((size_t)M * stack_g_row(Di) * 8);
@@ -881,11 +883,10 @@ int launch_decode_stack(const quamba_model *m, const int32_t *tokens, int Bt, fl
                                     s.inv_s_x, s.m_x_dt, s.m_x_B, s.m_x_C, s.m_dt, s.s_x, s.s_dt, s.s_z, s.s_B, s.s_C, s.s_A, s.s_D,
                                     s.inv_s_y, s.m_out, 0.f};
       }
-      const unsigned n_clear = l0 ? 0u : (unsigned)((c.total - c.x) / 8);
-      const unsigned n = l0 ? 1u : std::max<unsigned>(n_clear, (unsigned)(Bt * Dm / 2));
-      hipLaunchKernelGGL(stack_begin_kernel, dim3((n + 255) / 256), dim3(256), 0, st, chunk,
+      const unsigned n_words = l0 ? 0u : (unsigned)((c.total - c.s) / 8);
+      hipLaunchKernelGGL(stack_begin_kernel, dim3(std::max(1u, (n_words + 255) / 256)), dim3(256), 0, st, chunk,
                          const_cast<StackLayer *>(a.layers) + l0, count,
-                         l0 ? nullptr : reinterpret_cast<const __half *>(m->embedding), tokens, Bt, Dm, m->vocab, a.w, words(c.x), n_clear);
+                         l0 ? nullptr : reinterpret_cast<const __half *>(m->embedding), tokens, Bt, Dm, m->vocab, a.w, n_words);
       QUAMBA_LAUNCH_CHECK();
     }
     return QUAMBA_OK;
@@ -941,7 +942,7 @@ int stack_words(int Dm, int Di, int R, int Bt, int role, int item, int32_t *out,
     put(4, in_front(item, n.nC), 0, watch);
     put(0, in_watch(item, n.nD), 1, watch);
   } else if (role == 1) {
-    put(0, x_front(item), 1, watch);
+    put(0, x_front(item, n.nD), 1, watch);
     put(1, x_watch(item, Di), 1, watch);
   } else if (role == 2) {
     put(1, scan_front(item), 1, watch);

@@ -64,6 +64,8 @@ def _steps(d, m, n_layers, Bt, hook, steps=2, fill=0):
 
 @pytest.mark.parametrize("Dm,Di,R,n_layers,Bt", [
     (80, 1536, 16, 3, 1),     # fewer columns than workgroups, Hadamard items that leave a wave half empty
+    (64, 1536, 16, 3, 1),     # 12 items of x_proj watch 7 lines of the residual stream
+    (704, 1536, 256, 3, 2),   # 72 watch 71
     (208, 1536, 48, 2, 2),    # a ragged last group of out_proj columns
     (768, 1536, 48, 23, 1),   # more blocks than descriptors in one launch
     (1024, 2048, 64, 2, 2),   # an order that is a power of two
