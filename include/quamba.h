@@ -540,14 +540,22 @@ int quamba_model_prefill(const quamba_model *model, const int32_t *tokens, int B
                          float *logits, int32_t *next_token, float *ssm_states,
                          quamba_half *conv_states, void *ws, size_t ws_bytes, void *stream);
 
-/* One generation step on the carried states (in/out): tokens int32 [Bt]. */
+/* One generation step on the carried states (in/out): tokens int32 [Bt].
+ *
+ * With one or two sequences and at least two blocks (d_inner 1536, 2048, 2560, 3072, 4096 or 5120, d_model up to 2560 on
+ * 256 CUs) all blocks run in one launch, whose workgroups hand values to one another through memory.  Every wait in it is
+ * bounded by a number of polls (35 ms of polling at least; no wait of a step that runs takes 1 ms).  Should one run out all the
+ * same, the step says so: its logits are NaN, its next_token is -1 for every sequence, and the states are left undefined; the
+ * call itself has returned QUAMBA_OK by then, as with any launch.  The step may run beside others on other streams, whose states
+ * and workspaces are their own; while it has the GPU, other streams' kernels mostly wait (it takes (d_model + 9) / 10,
+ * d_inner / 20 or d_inner / 48 + dt_rank / 4 + 8 of the CUs, whichever is most). */
 int quamba_model_decode(const quamba_model *model, const int32_t *tokens, int Bt, float *logits,
                         int32_t *next_token, float *ssm_states, quamba_half *conv_states,
                         void *ws, size_t ws_bytes, void *stream);
 
 /* Greedy generation of n_new tokens per sequence from first_tokens [Bt] (device; typically the
  * next_token of the prefill): step i feeds the token chosen by step i - 1.  tokens_out int32
- * [n_new, Bt] receives the chosen tokens.  The current token, the step counter and the log stay
+ * [n_new, Bt] receives the chosen tokens (-1 from a step on whose waits ran out, see quamba_model_decode).  The current token, the step counter and the log stay
  * on the device, so a step is a fixed sequence of launches: with use_graph != 0 the first step
  * runs eagerly, the second is captured from `stream` (which must not be the default stream)
  * into a HIP graph, and the graph is replayed for the rest; the call then returns after the last
@@ -610,7 +618,9 @@ int quamba_probe_rate(int probe, int waves_per_simd, int iters, double *instr_pe
  *                                      the two by the library's estimate for the shape)
  *   quamba_debug_set_decode_stack(v)   generation of a stack with one or two sequences: 1 = four launches a block,
  *                                      2 = all blocks in one launch, its work items taken from a counter as when
- *                                      the GPU is shared; 0 = default (all blocks in one launch where served)
+ *                                      the GPU is shared; 3 = all blocks in one launch whose first input never
+ *                                      arrives (its waits run out, about 0.3 s a step); 0 = default (all blocks in one
+ *                                      launch where served)
  * Host-only queries of what is chosen for a shape with the full workspace, for tests of the rules:
  *   quamba_debug_gemm_kind(M, N, K)    configuration of an int8 GEMM as quamba_debug_set_gemm_variant counts
  *                                      them, before the launcher cuts rows; -1 = few-row streaming kernel, -2 = not served

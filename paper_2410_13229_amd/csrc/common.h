@@ -247,6 +247,6 @@ int mixer_decode_norm(const quamba_dims *d, const quamba_qweights *qw, const qua
 int check_model_layer(const quamba_qweights *qw, const quamba_scales *sc);
 // generation with one or two sequences: all blocks of the stack in one launch, where the shape and the device allow (*served)
 int launch_decode_stack(const quamba_model *m, const int32_t *tokens, int Bt, float *ssm, __half *conv, __half *out, __half *res,
-                        void *ws, size_t ws_bytes, hipStream_t st, bool *served);
+                        void *ws, size_t ws_bytes, hipStream_t st, bool *served, const unsigned **gave_up);
 
 }  // namespace quamba

@@ -23,8 +23,8 @@
 // do so within a bounded time they are all resident, and each keeps its own items (the walk above).  If not (another
 // kernel holds part of the GPU), the ones that run take the items from a counter, in an order in which an item only waits for
 // items with lower numbers, which somebody already holds: any number of workgroups gets through (all resident, that form
-// takes 1195 us).  Every wait is bounded (WAIT_TRIES polls, far beyond any wait that can occur); a workgroup that gives up marks the
-// step, whose output is then NaN.
+// takes 1195 us).  Every wait is bounded (WAIT_TRIES polls, 35 ms and more where no wait of a step that runs takes one); a role's waves that have given up
+// hand nothing on any more, so everything behind them gives up as well, down to the outputs, which are NaN.
 //
 // Arithmetic, operand order and rounding are those of the separate kernels (decode_in_kernel, gemv_i8_kernel, scan_step_kernel,
 // hadamard_out_proj_kernel): same bits.
@@ -36,7 +36,7 @@
 
 namespace quamba {
 
-// 0: on where it is served, 1: off, 2: on, with the work items taken from the counter
+// 0: on where it is served, 1: off, 2: on, with the work items taken from the counter, 3: on, the first block's input never handed over
 std::atomic<int> g_decode_stack_hook{0};
 
 namespace {
@@ -79,7 +79,7 @@ struct Words {  // tagged words, [M] rows each: residual stream, x codes, z code
   unsigned *ctrl;  // control words, one per 256 bytes
 };
 constexpr int CTRL_STRIDE = 64, CTRL_WORDS = 12;
-enum { C_SUB = 0 /* 8 sign-in counters */, C_TOP = 8, C_MODE = 9, C_TICKET = 10, C_DEAD = 11 };
+enum { C_SUB = 0 /* 8 sign-in counters */, C_TOP = 8, C_MODE = 9, C_TICKET = 10, C_GAVE_UP = 11 };
 
 struct StackArgs {
   const StackLayer *layers;
@@ -138,10 +138,21 @@ __device__ __host__ __forceinline__ int scan_watch(int idx, int nB) { return idx
 __device__ __host__ __forceinline__ int out_front(int idx, int nB) { return idx % nB * LINE; }              // dbc
 __device__ __host__ __forceinline__ int out_watch(int idx, int nC) { return idx * 37 % nC * (2 * LINE); }   // g
 
+// How long the waves of a role wait.  A thread that runs out of polls tells the others of its role (an LDS word that is never cleared; they see it behind their next
+// barrier) and the control word that the selection of the token reads.  From the next item on the role (`gone`) polls once.
+struct Patience {
+  unsigned *ctrl, *role_gave_up;
+  bool gone;
+  __device__ __forceinline__ void give_up() const {
+    __hip_atomic_store(ctrl + C_GAVE_UP * CTRL_STRIDE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(role_gave_up, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+  __device__ __forceinline__ bool gave_up() const { return __hip_atomic_load(role_gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != 0; }
+};
+
 // Polls base[idx[j]] until all N words carry `tag`; the payloads are left in v.
 template <int N>
-__device__ __forceinline__ void wait_words(const u64 *base, const int (&idx)[N], unsigned tag, unsigned (&v)[N], unsigned *ctrl,
-                                           bool &dead) {
+__device__ __forceinline__ void wait_words(const u64 *base, const int (&idx)[N], unsigned tag, unsigned (&v)[N], const Patience &patience) {
   for (int tries = 0;; ++tries) {
     u64 t[N];
 #pragma unroll
@@ -153,9 +164,8 @@ __device__ __forceinline__ void wait_words(const u64 *base, const int (&idx)[N],
       v[j] = static_cast<unsigned>(t[j]);
     }
     if (ok) break;
-    if (dead || tries >= WAIT_TRIES) {
-      if (!dead) __hip_atomic_store(ctrl + C_DEAD * CTRL_STRIDE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      dead = true;
+    if (patience.gone || tries >= WAIT_TRIES) {
+      patience.give_up();
       break;
     }
     __builtin_amdgcn_s_sleep(RETRY_PACE);
@@ -169,11 +179,11 @@ __device__ __host__ __forceinline__ bool watch_ends(unsigned tag, unsigned wante
 // What one wave of a role does for all of them before wait_words reads every word: it watches one of the awaited words, and before that,
 // at a slow pace, one word of the role in front.  All words of all waiting workgroups polled all the time keep the memory
 // side so busy that the stores they wait for hardly get through.
-__device__ __forceinline__ void wait_ahead(const u64 *front, unsigned front_tag, const u64 *word, unsigned tag, bool dead) {
+__device__ __forceinline__ void wait_ahead(const u64 *front, unsigned front_tag, const u64 *word, unsigned tag, const Patience &patience) {
   int tries = 0;
   if (front)
-    for (; !watch_ends(static_cast<unsigned>(word_load(front) >> 32), front_tag) && !dead && tries < WAIT_TRIES; ++tries) __builtin_amdgcn_s_sleep(FRONT_PACE);
-  for (; !watch_ends(static_cast<unsigned>(word_load(word) >> 32), tag) && !dead && tries < WAIT_TRIES; ++tries) __builtin_amdgcn_s_sleep(PACE);
+    for (; !watch_ends(static_cast<unsigned>(word_load(front) >> 32), front_tag) && !patience.gone && tries < WAIT_TRIES; ++tries) __builtin_amdgcn_s_sleep(FRONT_PACE);
+  for (; !watch_ends(static_cast<unsigned>(word_load(word) >> 32), tag) && !patience.gone && tries < WAIT_TRIES; ++tries) __builtin_amdgcn_s_sleep(PACE);
 }
 
 // A scale read now: left to the compiler, the scalar load of a descriptor field lands where the value is needed, behind the waits.
@@ -259,7 +269,7 @@ struct InShared {
 // ---- role A: residual stream -> norm -> codes -> in_proj for A_COLS columns -> conv step on those of x
 template <int MB>
 __device__ __forceinline__ void role_in(const StackArgs &p, int l, int idx, int8_t *sA, InShared<MB> &sh, const RoleBarrier &sync,
-                                        bool &dead) {
+                                        const Patience &patience) {
   const LayerRef q = layer_ref(p.layers, l);
   idx = fresh(idx);
   const int tid = fresh_tid(0), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -296,7 +306,7 @@ __device__ __forceinline__ void role_in(const StackArgs &p, int l, int idx, int8
   }
   const float inv_s_u = now(q->inv_s_u), m_in_x = now(q->m_in_x), m_in_z = now(q->m_in_z), s_cw = now(q->s_cw), s_xpre = now(q->s_xpre),
               inv_s_x = now(q->inv_s_x);
-  if (wave == 0) wait_ahead(l ? p.w.g + in_front(idx, p.nC) : nullptr, l, p.w.s + in_watch(idx, p.nD), l + 1, dead);
+  if (wave == 0) wait_ahead(l ? p.w.g + in_front(idx, p.nC) : nullptr, l, p.w.s + in_watch(idx, p.nD), l + 1, patience);
   sync();
   {  // the rows, as whole lines, into LDS
     constexpr int NWORD = (MB * PF * 512 + 64 * A_WAVES - 1) / (64 * A_WAVES);
@@ -308,7 +318,7 @@ __device__ __forceinline__ void role_in(const StackArgs &p, int l, int idx, int8
       const int i = min(tid + 64 * A_WAVES * k, words - 1);
       at[k] = pair_at(MB == 1 ? 0 : i / per_row, MB == 1 ? i : i % per_row);
     }
-    wait_words(p.w.s, at, l + 1, v, p.w.ctrl, dead);
+    wait_words(p.w.s, at, l + 1, v, patience);
 #pragma unroll
     for (int k = 0; k < NWORD; ++k)
       if (tid + 64 * A_WAVES * k < words) sh.s[tid + 64 * A_WAVES * k] = v[k];
@@ -395,7 +405,7 @@ __device__ __forceinline__ void role_in(const StackArgs &p, int l, int idx, int8
     if (lane < AC) sh.sums[m][wave * AC + lane] = mine;
   }
   sync();
-  if (fin) {
+  if (fin && !patience.gave_up()) {
     int a4[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) a4[j] = sh.sums[fm][4 * (tid % quads) + j];
@@ -416,7 +426,7 @@ __device__ __forceinline__ void role_in(const StackArgs &p, int l, int idx, int8
 
 // ---- role B: x_proj for four columns; the threads split K in 16-byte pieces
 template <int n, int MB>
-__device__ __forceinline__ void role_x(const StackArgs &p, int l, int idx, int8_t *sx, int (*red)[MB * 4], const RoleBarrier &sync, bool &dead) {
+__device__ __forceinline__ void role_x(const StackArgs &p, int l, int idx, int8_t *sx, int (*red)[MB * 4], const RoleBarrier &sync, const Patience &patience) {
   const LayerRef q = layer_ref(p.layers, l);
   idx = fresh(idx);
   const int tid = fresh_tid(64 * (A_WAVES + D_WAVES)), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -428,7 +438,7 @@ __device__ __forceinline__ void role_x(const StackArgs &p, int l, int idx, int8_
 #pragma unroll
     for (int j = 0; j < 4; ++j) w[r][j] = gload<v4i>(q->W_x + (size_t)(n0 + j) * n + min(tid + BC_THREADS * r, nch - 1) * 16);
   const float m_x = now(n0 < p.R ? q->m_x_dt : (n0 < p.R + NS ? q->m_x_B : q->m_x_C));
-  if (wave == 0) wait_ahead(p.w.s + x_front(idx, p.nD), l + 1, p.w.x + x_watch(idx, n), l + 1, dead);
+  if (wave == 0) wait_ahead(p.w.s + x_front(idx, p.nD), l + 1, p.w.x + x_watch(idx, n), l + 1, patience);
   sync();
   constexpr int NWORD = (n / 4 + BC_THREADS - 1) / BC_THREADS;
 #pragma unroll
@@ -437,7 +447,7 @@ __device__ __forceinline__ void role_x(const StackArgs &p, int l, int idx, int8_
     unsigned v[NWORD];
 #pragma unroll
     for (int k = 0; k < NWORD; ++k) at[k] = m * p.x_row + quad_at(min(tid + BC_THREADS * k, n / 4 - 1));
-    wait_words(p.w.x, at, l + 1, v, p.w.ctrl, dead);
+    wait_words(p.w.x, at, l + 1, v, patience);
 #pragma unroll
     for (int k = 0; k < NWORD; ++k)
       if (tid + BC_THREADS * k < n / 4) reinterpret_cast<unsigned *>(sx)[m * (n / 4) + tid + BC_THREADS * k] = v[k];
@@ -463,7 +473,7 @@ __device__ __forceinline__ void role_x(const StackArgs &p, int l, int idx, int8_
     if (lane < 4) red[wave][m * 4 + lane] = mine;
   }
   sync();
-  if (tid < MB) {
+  if (tid < MB && !patience.gave_up()) {
     int a[4] = {0, 0, 0, 0};
 #pragma unroll
     for (int wv = 0; wv < BC_WAVES; ++wv)
@@ -486,7 +496,7 @@ __device__ __forceinline__ float silu_gate(float y, float z) {
 
 // ---- role C: one step of the scan with dt_proj inside, four lanes per channel, which walk the sequences
 template <int Di, int MB>
-__device__ __forceinline__ void role_scan(const StackArgs &p, int l, int idx, int8_t *sdbc, const RoleBarrier &sync, bool &dead) {
+__device__ __forceinline__ void role_scan(const StackArgs &p, int l, int idx, int8_t *sdbc, const RoleBarrier &sync, const Patience &patience) {
   const LayerRef q = layer_ref(p.layers, l);
   idx = fresh(idx);
   const int tid = fresh_tid(64 * (A_WAVES + D_WAVES));
@@ -511,23 +521,24 @@ __device__ __forceinline__ void role_scan(const StackArgs &p, int l, int idx, in
   }
   const float m_dt = now(q->m_dt), s_x = now(q->s_x), s_dt = now(q->s_dt), s_z = now(q->s_z), s_B = now(q->s_B), s_C = now(q->s_C),
               s_A = now(q->s_A), s_D = now(q->s_D);
-  if (tid < 64) wait_ahead(p.w.x + scan_front(idx), l + 1, p.w.dbc + scan_watch(idx, p.nB), l + 1, dead);
+  if (tid < 64) wait_ahead(p.w.x + scan_front(idx), l + 1, p.w.dbc + scan_watch(idx, p.nB), l + 1, patience);
   sync();
   unsigned xw[MB], zw[MB];
   {
     int at[MB];
 #pragma unroll
     for (int m = 0; m < MB; ++m) at[m] = m * p.x_row + quad_at(d / 4);
-    wait_words(p.w.x, at, l + 1, xw, p.w.ctrl, dead);
-    wait_words(p.w.z, at, l + 1, zw, p.w.ctrl, dead);
+    wait_words(p.w.x, at, l + 1, xw, patience);
+    wait_words(p.w.z, at, l + 1, zw, patience);
   }
   for (int i = tid; i < MB * (NX / 4); i += BC_THREADS) {
     const int at[1] = {dbc_at(i / (NX / 4), i % (NX / 4))};
     unsigned dw[1];
-    wait_words(p.w.dbc, at, l + 1, dw, p.w.ctrl, dead);
+    wait_words(p.w.dbc, at, l + 1, dw, patience);
     reinterpret_cast<unsigned *>(sdbc)[i] = dw[0];
   }
   sync();
+  const bool hand_on = live && !patience.gave_up();
   const int sh = 8 * (d & 3);
 #pragma unroll
   for (int m = 0; m < MB; ++m) {
@@ -567,7 +578,7 @@ __device__ __forceinline__ void role_scan(const StackArgs &p, int l, int idx, in
     const unsigned g = __half_as_ushort(__float2half_rn(silu_gate(y, zv)));
     // the neighbouring channel's (lane ^ 4, at lanes that are multiples of 8: four lanes up the row)
     const unsigned g1 = static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(g), 0x104, 0xf, 0xf, true));  // row_shl 4
-    if (live) {
+    if (hand_on) {
       if ((tid & 7) == 0) word_store(p.w.g + m * p.g_row + gate_at(d), g | (g1 << 16), l + 1);
       *reinterpret_cast<float4 *>(hp + (size_t)m * Di * NS) = make_float4(h[0], h[1], h[2], h[3]);
     }
@@ -577,7 +588,7 @@ __device__ __forceinline__ void role_scan(const StackArgs &p, int l, int idx, in
 // ---- role D: Hadamard + quantization of every row (each workgroup for itself), out_proj for D_COLS columns, residual add
 template <int K, int LOGM, int MB>
 __device__ __forceinline__ void role_out(const StackArgs &p, int l, int idx, float *row, int (*red)[MB * D_COLS],
-                                         const RoleBarrier &sync, bool &dead) {
+                                         const RoleBarrier &sync, const Patience &patience) {
   const LayerRef q = layer_ref(p.layers, l);
   idx = fresh(idx);
   const int tid = fresh_tid(64 * A_WAVES), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -602,7 +613,7 @@ __device__ __forceinline__ void role_out(const StackArgs &p, int l, int idx, flo
   const bool fin = tid < MB * D_COLS && fc < Dm;
   const int s_at[1] = {pair_at(fr, fc / 2)};
   unsigned res[1] = {0};
-  if (fin) wait_words(p.w.s, s_at, l + 1, res, p.w.ctrl, dead);
+  if (fin) wait_words(p.w.s, s_at, l + 1, res, patience);
   // where this thread's words lie and go: formed now, not behind the wait
   int at[(n / 2 + NT - 1) / NT], to[(n / 2 + NT - 1) / NT];
 #pragma unroll
@@ -613,7 +624,7 @@ __device__ __forceinline__ void role_out(const StackArgs &p, int l, int idx, flo
     else to[k] = pad(i) * 4;
     asm volatile("" : "+v"(at[k]), "+v"(to[k]));
   }
-  if (wave == 0) wait_ahead(p.w.dbc + out_front(idx, p.nB), l + 1, p.w.g + out_watch(idx, p.nC), l + 1, dead);
+  if (wave == 0) wait_ahead(p.w.dbc + out_front(idx, p.nB), l + 1, p.w.g + out_watch(idx, p.nC), l + 1, patience);
   sync();
 #pragma unroll
   for (int r = 0; r < MB; ++r) {
@@ -622,7 +633,7 @@ __device__ __forceinline__ void role_out(const StackArgs &p, int l, int idx, flo
     unsigned g[NWORD];
 #pragma unroll
     for (int k = 0; k < NWORD; ++k) at[k] += r ? p.g_row : 0;
-    wait_words(p.w.g, at, l + 1, g, p.w.ctrl, dead);
+    wait_words(p.w.g, at, l + 1, g, patience);
 #pragma unroll
     for (int k = 0; k < NWORD; ++k)
       if (tid + NT * k < n / 2) {
@@ -655,6 +666,7 @@ __device__ __forceinline__ void role_out(const StackArgs &p, int l, int idx, flo
     if (lane < D_COLS) red[wave][r * D_COLS + lane] = mine;
   }
   sync();
+  const bool gave_up = patience.gave_up();
   if (fin) {
     int a = 0;
 #pragma unroll
@@ -666,13 +678,13 @@ __device__ __forceinline__ void role_out(const StackArgs &p, int l, int idx, flo
     __half o = __float2half_rn(y);
     const __half rh = __ushort_as_half(static_cast<unsigned short>((fc & 1) ? res[0] >> 16 : res[0] & 0xffffu));
     if (l + 1 == p.n_layers) {
-      if (dead || ctrl_load(p.w.ctrl + C_DEAD * CTRL_STRIDE)) o = __ushort_as_half(static_cast<unsigned short>(0x7e00));
+      if (gave_up) o = __ushort_as_half(static_cast<unsigned short>(0x7e00));
       p.out[(size_t)fr * Dm + fc] = o;
       p.res[(size_t)fr * Dm + fc] = rh;
     } else {
       const unsigned t = __half_as_ushort(__float2half_rn(__half2float(o) + __half2float(rh)));
       const unsigned t1 = __shfl_down(t, 1);
-      if ((fc & 1) == 0) word_store(p.w.s + s_at[0], t | (t1 << 16), l + 2);
+      if ((fc & 1) == 0 && !gave_up) word_store(p.w.s + s_at[0], t | (t1 << 16), l + 2);
     }
   }
 }
@@ -686,13 +698,12 @@ __global__ __launch_bounds__(STACK_THREADS) void decode_stack_kernel(StackArgs p
   __shared__ __attribute__((aligned(16))) int8_t sx[MB * n];            // role B's codes
   __shared__ __attribute__((aligned(16))) int8_t sdbc[MB * (256 + 2 * NS)];
   __shared__ int red_x[BC_WAVES][MB * 4], red_out[D_WAVES][MB * D_COLS];
-  __shared__ unsigned count[3];
+  __shared__ unsigned count[3], gave_up[3];
   __shared__ int s_word;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int G = gridDim.x;
   unsigned *ctrl = p.w.ctrl;
-  bool dead = false;
-  if (tid < 3) count[tid] = 0;
+  if (tid < 3) count[tid] = gave_up[tid] = 0;
   if (tid == 0) {
     unsigned mode = 2;
     if (!p.from_counter) {
@@ -736,14 +747,15 @@ __global__ __launch_bounds__(STACK_THREADS) void decode_stack_kernel(StackArgs p
       item_d = r;
     }
     if (l >= p.n_layers) break;
+    const bool gone = __builtin_amdgcn_readfirstlane(gave_up[role]) != 0;
     if (role == 0) {
-      if (item_a >= 0) role_in<MB>(p, l, item_a, sA, sIn, sync, dead);
+      if (item_a >= 0) role_in<MB>(p, l, item_a, sA, sIn, sync, Patience{ctrl, &gave_up[0], gone});
     } else if (role == 1) {
-      if (item_d >= 0) role_out<K, LOGM, MB>(p, l, item_d, row, red_out, sync, dead);
+      if (item_d >= 0) role_out<K, LOGM, MB>(p, l, item_d, row, red_out, sync, Patience{ctrl, &gave_up[1], gone});
     } else if (item_x >= 0) {
-      role_x<n, MB>(p, l, item_x, sx, red_x, sync, dead);
+      role_x<n, MB>(p, l, item_x, sx, red_x, sync, Patience{ctrl, &gave_up[2], gone});
     } else if (item_c >= 0) {
-      role_scan<n, MB>(p, l, item_c, sdbc, sync, dead);
+      role_scan<n, MB>(p, l, item_c, sdbc, sync, Patience{ctrl, &gave_up[2], gone});
     }
   }
 }
@@ -752,7 +764,7 @@ __global__ __launch_bounds__(STACK_THREADS) void decode_stack_kernel(StackArgs p
 // of the token (plus zero, as the first add of the separate kernels has it), all other words (those between the lines among them) and the control
 // words zero.
 __global__ __launch_bounds__(256) void stack_begin_kernel(LayerChunk chunk, StackLayer *dst, int count, const __half *E,
-                                                          const int32_t *tokens, int M, int Dm, int vocab, Words w, unsigned n_words) {
+                                                          const int32_t *tokens, int M, int Dm, int vocab, Words w, unsigned n_words, unsigned first_tag) {
   if (blockIdx.x == 0) {
     // (read through the argument segment: indexing the by-value struct would copy it to scratch first)
     typedef __attribute__((address_space(4))) const unsigned *args_t;
@@ -770,7 +782,7 @@ __global__ __launch_bounds__(256) void stack_begin_kernel(LayerChunk chunk, Stac
     const __half2 e = reinterpret_cast<const __half2 *>(E + (size_t)tok * Dm)[c];
     const unsigned lo = __half_as_ushort(__float2half_rn(0.f + __half2float(__low2half(e))));
     const unsigned hi = __half_as_ushort(__float2half_rn(0.f + __half2float(__high2half(e))));
-    word = (1ull << 32) | lo | (hi << 16);
+    word = (static_cast<u64>(first_tag) << 32) | lo | (hi << 16);
   }
   w.s[i] = word;
 }
@@ -851,9 +863,9 @@ int run_stack(const StackArgs &args, const Begin &begin, bool *served, hipStream
 }  // namespace
 
 // All blocks of a generation step from tokens [Bt]; leaves the last block's output and the residual stream before its add in `out`
-// and `res`, the states advanced.  *served = false (and nothing launched): the general path has to run.
+// and `res`, the states advanced; **gave_up is then nonzero if a wait in it was given up.  *served = false (and nothing launched): the general path has to run.
 int launch_decode_stack(const quamba_model *m, const int32_t *tokens, int Bt, float *ssm, __half *conv, __half *out, __half *res,
-                        void *ws, size_t ws_bytes, hipStream_t st, bool *served) {
+                        void *ws, size_t ws_bytes, hipStream_t st, bool *served, const unsigned **gave_up) {
   *served = false;
   const int hook = g_decode_stack_hook.load(std::memory_order_relaxed);
   const int Dm = m->dims.d_model, Di = m->dims.d_inner, R = m->dims.dt_rank;
@@ -871,6 +883,7 @@ int launch_decode_stack(const quamba_model *m, const int32_t *tokens, int Bt, fl
   auto words = [&](size_t at) { return reinterpret_cast<u64 *>(base + at); };
   a.w = Words{words(c.s), words(c.x), words(c.z), words(c.dbc), words(c.g), reinterpret_cast<unsigned *>(base + c.ctrl)};
   a.from_counter = hook == 2;
+  *gave_up = a.w.ctrl + C_GAVE_UP * CTRL_STRIDE;
   auto begin = [&]() -> int {
     for (int l0 = 0; l0 < m->n_layers; l0 += CHUNK_LAYERS) {
       LayerChunk chunk{};
@@ -886,7 +899,7 @@ int launch_decode_stack(const quamba_model *m, const int32_t *tokens, int Bt, fl
       const unsigned n_words = l0 ? 0u : (unsigned)((c.total - c.s) / 8);
       hipLaunchKernelGGL(stack_begin_kernel, dim3(std::max(1u, (n_words + 255) / 256)), dim3(256), 0, st, chunk,
                          const_cast<StackLayer *>(a.layers) + l0, count,
-                         l0 ? nullptr : reinterpret_cast<const __half *>(m->embedding), tokens, Bt, Dm, m->vocab, a.w, n_words);
+                         l0 ? nullptr : reinterpret_cast<const __half *>(m->embedding), tokens, Bt, Dm, m->vocab, a.w, n_words, hook == 3 ? 0u : 1u);
       QUAMBA_LAUNCH_CHECK();
     }
     return QUAMBA_OK;

@@ -213,11 +213,13 @@ __global__ __launch_bounds__(256) void head_kernel(const __half *__restrict__ y,
   }
 }
 
-// Selection from the head's per-workgroup partials [P, Bt]: one workgroup per token.
+// Selection from the head's per-workgroup partials [P, Bt]: one workgroup per token.  A step whose waits were given up (*gave_up, where there are any) has no
+// token, and neither has what follows it in the log: -1.
 __global__ __launch_bounds__(256) void argmax_partials_kernel(const float *__restrict__ pmax,
                                                               const int32_t *__restrict__ pidx, int P, int Bt,
-                                                              int32_t *__restrict__ next, int32_t *__restrict__ log,
-                                                              const int32_t *__restrict__ step) {
+                                                              int32_t *__restrict__ next, int32_t *log,
+                                                              const int32_t *__restrict__ step,
+                                                              const unsigned *__restrict__ gave_up) {
   const int b = blockIdx.x;
   float best = -INFINITY;
   int bi = 0x7fffffff;
@@ -246,7 +248,8 @@ __global__ __launch_bounds__(256) void argmax_partials_kernel(const float *__res
     __syncthreads();
   }
   if (threadIdx.x == 0) {
-    const int r = si[0] == 0x7fffffff ? 0 : si[0];  // a row of NaNs selects token 0
+    int r = si[0] == 0x7fffffff ? 0 : si[0];  // a row of NaNs selects token 0
+    if (gave_up && (*gave_up || (log && *step > 0 && log[(size_t)(*step - 1) * Bt + b] < 0))) r = -1;
     next[b] = r;
     if (log) log[(size_t)(*step) * Bt + b] = r;
   }
@@ -362,12 +365,13 @@ int run_model(const quamba_model *m, const int32_t *tokens, int Bt, int L, bool 
   // generation with one or two sequences: all blocks in one launch
   const bool fused = decode && mixer_decode_norm_available(&m->dims, Bt);
   bool stacked = false;
+  const unsigned *gave_up = nullptr;
   if (fused && mixer_decode_fuses_dt()) {
     for (int l = 0; l < m->n_layers; ++l) {
       const int rc = check_model_layer(&m->layers[l].q, &m->layers[l].s);
       if (rc != QUAMBA_OK) return rc;
     }
-    const int rc = launch_decode_stack(m, tokens, Bt, ssm_states, conv_states, out, res, base + c.mixer, c.mixer_bytes, st, &stacked);
+    const int rc = launch_decode_stack(m, tokens, Bt, ssm_states, conv_states, out, res, base + c.mixer, c.mixer_bytes, st, &stacked, &gave_up);
     if (rc != QUAMBA_OK) return rc;
   }
   if (!stacked) {
@@ -424,7 +428,8 @@ int run_model(const quamba_model *m, const int32_t *tokens, int Bt, int L, bool 
                      reinterpret_cast<const __half *>(m->embedding), Bt, m->vocab, Dm, logits, pmax, pidx);
   QUAMBA_LAUNCH_CHECK();
   if (next) {
-    hipLaunchKernelGGL(argmax_partials_kernel, dim3(Bt), dim3(256), 0, st, pmax, pidx, P, Bt, next, log, step);
+    hipLaunchKernelGGL(argmax_partials_kernel, dim3(Bt), dim3(256), 0, st, pmax, pidx, P, Bt, next, log, step,
+                       stacked ? gave_up : nullptr);
     QUAMBA_LAUNCH_CHECK();
   }
   return QUAMBA_OK;

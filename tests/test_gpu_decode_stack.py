@@ -156,6 +156,34 @@ def test_four_users_for_many_steps(Bt):
     del keep
 
 
+@pytest.mark.parametrize("Dm,Di,R,Bt", [(768, 1536, 48, 1), (1024, 2048, 64, 2)])
+def test_a_step_that_gives_up_says_so_and_the_next_one_is_whole(Dm, Di, R, Bt):
+    """The first input of the chain is held back, so that every bounded wait behind it runs out: NaN and -1, nothing finite."""
+    d, m, keep = _model(Dm, Di, R, 3, 15)
+    want = _steps(d, m, 3, Bt, 1)
+    ssm, conv = _states(d, 3, Bt, 5)
+    ws = workspace(Q.quamba_model_workspace_bytes(m, Bt, 1))
+    first = torch.arange(Bt, dtype=torch.int32, device=DEV) * 40 + 3
+    tok, logits, toks = first.clone(), empty((Bt, VOCAB), torch.float32), empty((3, Bt), torch.int32)
+    Q.quamba_debug_set_decode_stack(3)
+    try:
+        Q.quamba_model_decode(m, tok, Bt, logits, tok, ssm, conv, ws)
+        assert torch.isnan(logits).all() and (tok == -1).all()
+        Q.quamba_model_generate(m, first, Bt, 1, toks, ssm, conv, ws, 0)
+        assert (toks[0] == -1).all()
+    finally:
+        Q.quamba_debug_set_decode_stack(0)
+    got = []
+    ssm, conv = _states(d, 3, Bt, 5)
+    tok = first.clone()
+    for _ in range(2):
+        Q.quamba_model_decode(m, tok, Bt, logits, tok, ssm, conv, ws)
+        got += [logits.clone(), tok.clone()]
+    for a, b in zip(got + [ssm, conv], want):
+        assert torch.equal(a, b)
+    del keep
+
+
 @pytest.mark.parametrize("Bt", [3, 20])
 def test_weights_read_ahead_change_nothing(Bt):
     """A stack whose weights exceed the last-level cache (the same block seven times: 280 MB): norm and Hadamard launches with workgroups that
