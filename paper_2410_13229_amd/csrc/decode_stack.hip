@@ -811,9 +811,12 @@ StackCarve stack_carve(int n_layers, int M, int Dm, int Di, int R) {
   return c;
 }
 
+// LDS of role D's row
+constexpr size_t row_bytes(int n) { return (size_t)(n + n / 4) * sizeof(float); }
+
 // Does the current device hold `groups` workgroups of this kernel at once (as far as the runtime can tell)?
 template <int K, int LOGM, int MB>
-bool fits(int groups, size_t lds) {
+bool fits(int groups) {
   static std::atomic<int> known[64];
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return false;
@@ -821,7 +824,7 @@ bool fits(int groups, size_t lds) {
   int v = slot.load(std::memory_order_relaxed);
   if (v == 0) {
     int per_cu = 0, cus = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_stack_kernel<K, LOGM, MB>, STACK_THREADS, lds) != hipSuccess ||
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_stack_kernel<K, LOGM, MB>, STACK_THREADS, row_bytes(K << LOGM)) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
       return false;
     v = per_cu * cus;
@@ -833,13 +836,14 @@ bool fits(int groups, size_t lds) {
 // Items of each role in one block.
 struct Items {
   int nA, nB, nC, nD;
+  int groups() const { return std::max(std::max(nA, nD), nB + nC); }  // workgroups, one item of each role for each
 };
 Items stack_items(int Dm, int Di, int R) {
   return Items{(2 * Di + A_COLS - 1) / A_COLS, (R + 2 * NS) / 4, (Di * 4 + BC_THREADS - 1) / BC_THREADS, (Dm + D_COLS - 1) / D_COLS};
 }
 
 template <int K, int LOGM, int MB, typename Begin>
-int run_stack(const StackArgs &args, const Begin &begin, bool *served, hipStream_t st) {
+int run_stack(const StackArgs &args, const Begin &begin, hipStream_t st) {
   constexpr int n = K << LOGM;
   StackArgs p = args;
   const Items items = stack_items(p.Dm, n, p.R);
@@ -849,15 +853,27 @@ int run_stack(const StackArgs &args, const Begin &begin, bool *served, hipStream
   p.nD = items.nD;
   p.x_row = stack_x_row(n);
   p.g_row = stack_g_row(n);
-  const int G = std::max(std::max(p.nA, p.nD), p.nB + p.nC);
-  const size_t lds = (size_t)(n + n / 4) * sizeof(float);
-  *served = fits<K, LOGM, MB>(G, lds);
-  if (!*served) return QUAMBA_OK;
   const int rc = begin();
   if (rc != QUAMBA_OK) return rc;
-  hipLaunchKernelGGL((decode_stack_kernel<K, LOGM, MB>), dim3(G), dim3(STACK_THREADS), lds, st, p);
+  hipLaunchKernelGGL((decode_stack_kernel<K, LOGM, MB>), dim3(items.groups()), dim3(STACK_THREADS), row_bytes(n), st, p);
   QUAMBA_LAUNCH_CHECK();
   return QUAMBA_OK;
+}
+
+// The widths that are built: d_inner = K << LOGM
+#define QUAMBA_STACK_WIDTHS(CASE) CASE(12, 7) CASE(1, 11) CASE(20, 7) CASE(12, 8) CASE(1, 12) CASE(20, 8)
+
+// Is a step of this shape served in one launch on the current device?
+bool stack_served(int n_layers, int Bt, int Dm, int Di, int R, size_t ws_bytes) {
+  // (one block alone: no weights to read ahead)
+  if (g_decode_stack_hook.load(std::memory_order_relaxed) == 1 || Bt < 1 || Bt > 2 || n_layers < 2 || Dm > PF * 1024 || R > 256) return false;
+  if (stack_carve(n_layers, Bt, Dm, Di, R).total > ws_bytes || (long long)n_layers * 4096 > 0x7fffffffLL) return false;
+  const int groups = stack_items(Dm, Di, R).groups();
+#define QUAMBA_CASE(K, LM) \
+  if (Di == K << LM) return Bt == 1 ? fits<K, LM, 1>(groups) : fits<K, LM, 2>(groups);
+  QUAMBA_STACK_WIDTHS(QUAMBA_CASE)
+#undef QUAMBA_CASE
+  return false;
 }
 
 }  // namespace
@@ -866,15 +882,11 @@ int run_stack(const StackArgs &args, const Begin &begin, bool *served, hipStream
 // and `res`, the states advanced; **gave_up is then nonzero if a wait in it was given up.  *served = false (and nothing launched): the general path has to run.
 int launch_decode_stack(const quamba_model *m, const int32_t *tokens, int Bt, float *ssm, __half *conv, __half *out, __half *res,
                         void *ws, size_t ws_bytes, hipStream_t st, bool *served, const unsigned **gave_up) {
-  *served = false;
-  const int hook = g_decode_stack_hook.load(std::memory_order_relaxed);
   const int Dm = m->dims.d_model, Di = m->dims.d_inner, R = m->dims.dt_rank;
-  // (one block alone: no weights to read ahead)
-  if (hook == 1 || Bt < 1 || Bt > 2 || m->n_layers < 2 || Dm > PF * 1024 || R > 256) return QUAMBA_OK;
-  int k = 0, lm = 0;
-  if (!hadamard_factor(Di, &k, &lm)) return QUAMBA_OK;
+  *served = stack_served(m->n_layers, Bt, Dm, Di, R, ws_bytes);
+  if (!*served) return QUAMBA_OK;
+  const int hook = g_decode_stack_hook.load(std::memory_order_relaxed);
   const StackCarve c = stack_carve(m->n_layers, Bt, Dm, Di, R);
-  if (c.total > ws_bytes || (long long)m->n_layers * 4096 > 0x7fffffffLL) return QUAMBA_OK;
   char *base = static_cast<char *>(ws);
   StackArgs a{};
   a.layers = reinterpret_cast<const StackLayer *>(base + c.layers);
@@ -904,11 +916,11 @@ int launch_decode_stack(const quamba_model *m, const int32_t *tokens, int Bt, fl
     }
     return QUAMBA_OK;
   };
-#define QUAMBA_CASE(KK, LM)                                                                         \
-  if (k == KK && lm == LM) return Bt == 1 ? run_stack<KK, LM, 1>(a, begin, served, st) : run_stack<KK, LM, 2>(a, begin, served, st);
-  QUAMBA_CASE(12, 7) QUAMBA_CASE(1, 11) QUAMBA_CASE(20, 7) QUAMBA_CASE(12, 8) QUAMBA_CASE(1, 12) QUAMBA_CASE(20, 8)
+#define QUAMBA_CASE(K, LM) \
+  if (Di == K << LM) return Bt == 1 ? run_stack<K, LM, 1>(a, begin, st) : run_stack<K, LM, 2>(a, begin, st);
+  QUAMBA_STACK_WIDTHS(QUAMBA_CASE)
 #undef QUAMBA_CASE
-  return QUAMBA_OK;
+  return fail(QUAMBA_EUNSUPPORTED, "decode: d_inner=%d is not served in one launch", Di);
 }
 
 // The words one item of a role (0 = A, 1 = B, 2 = C, 3 = D) deals with in a block, as the kernel forms their places; four numbers for each: buffer (0 s, 1 x, 2 z,
@@ -972,5 +984,10 @@ int stack_words(int Dm, int Di, int R, int Bt, int role, int item, int32_t *out,
 extern "C" int quamba_debug_decode_stack_words(int d_model, int d_inner, int dt_rank, int batch, int role, int item, int32_t *out, int cap) {
   if (d_model < 16 || d_inner < 16 || dt_rank < 16 || (cap > 0 && !out)) return -1;
   return quamba::stack_words(d_model, d_inner, dt_rank, batch, role, item, out, cap);
+}
+extern "C" int quamba_debug_decode_stack_served(const quamba_dims *d, int n_layers, int batch) {
+  using namespace quamba;
+  if (check_model_dims(d) != QUAMBA_OK || batch < 1 || !mixer_decode_norm_available(d, batch) || !mixer_decode_fuses_dt()) return 0;
+  return stack_served(n_layers, batch, d->d_model, d->d_inner, d->dt_rank, mixer_workspace_bytes(d, batch, 1));
 }
 extern "C" void quamba_debug_set_decode_stack(int v) { quamba::g_decode_stack_hook.store(v); }

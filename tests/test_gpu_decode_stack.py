@@ -74,11 +74,12 @@ def _steps(d, m, n_layers, Bt, hook, steps=2, fill=0):
     (2048, 4096, 128, 2, 1),
     (2560, 5120, 160, 2, 1),  # every CU
     (2560, 5120, 160, 2, 2),
-    (3072, 1536, 16, 2, 2),   # the widest d_model; more out_proj columns than 256 workgroups take: launch by launch
+    (2560, 1536, 16, 2, 2),   # as many workgroups for out_proj as there are CUs
 ])
 def test_one_launch_gives_the_bits_of_separate_launches(Dm, Di, R, n_layers, Bt):
     """Integer sums and the same fp32 operations in the same order: equal, not close."""
     d, m, keep = _model(Dm, Di, R, n_layers, Dm + Di + Bt)
+    assert Q.quamba_debug_decode_stack_served(d, n_layers, Bt)
     want = _steps(d, m, n_layers, Bt, 1)
     assert torch.isfinite(want[0]).all() and want[0].std() > 0
     for hook, fill in ((0, 0), (0, 255), (2, 1)):
@@ -88,8 +89,26 @@ def test_one_launch_gives_the_bits_of_separate_launches(Dm, Di, R, n_layers, Bt)
     del keep
 
 
+@pytest.mark.parametrize("Dm,Di,R,n_layers,Bt", [
+    (2576, 1536, 16, 2, 2),   # more out_proj columns than 256 workgroups take
+    (3072, 1536, 16, 2, 2),
+    (3088, 1536, 16, 2, 1),   # more than role A's registers hold of a weight row
+    (768, 1536, 272, 2, 1),   # dt_rank
+    (96, 192, 16, 2, 1), (1024, 8192, 64, 2, 1),  # widths that are not built
+    (768, 1536, 48, 1, 1),    # one block
+    (768, 1536, 48, 2, 3),    # three sequences
+])
+def test_other_shapes_run_launch_by_launch(Dm, Di, R, n_layers, Bt):
+    d, m, keep = _model(Dm, Di, R, n_layers, 16)
+    assert not Q.quamba_debug_decode_stack_served(d, n_layers, Bt)
+    for a, b in zip(_steps(d, m, n_layers, Bt, 0, fill=255), _steps(d, m, n_layers, Bt, 1)):
+        assert torch.equal(a, b)
+    del keep
+
+
 def test_generation_from_a_graph():
     d, m, keep = _model(768, 1536, 48, 4, 11)
+    assert Q.quamba_debug_decode_stack_served(d, 4, 1)
     outs = []
     for hook, graph in ((1, 0), (0, 0), (0, 1), (0, 1)):
         ssm, conv = _states(d, 4, 1, 5)
@@ -112,6 +131,7 @@ def test_generation_from_a_graph():
 def test_two_steps_in_flight():
     """Two streams, states and workspaces of their own, their launches interleaved: neither step waits for the other's workgroups."""
     d, m, keep = _model(2560, 5120, 160, 2, 12)
+    assert Q.quamba_debug_decode_stack_served(d, 2, 1)
     want = _steps(d, m, 2, 1, 1, steps=6)
     torch.cuda.synchronize()
     streams = [torch.cuda.Stream() for _ in range(2)]
@@ -137,6 +157,7 @@ def test_four_users_for_many_steps(Bt):
     may be late at any word of the hand-over."""
     n, steps = 16, 40
     d, m, keep = _model(2560, 5120, 160, n, 14)
+    assert Q.quamba_debug_decode_stack_served(d, n, Bt)
     want = _steps(d, m, n, Bt, 1, steps=steps)
     for rep in range(4):
         streams, runs = [torch.cuda.Stream() for _ in range(4)], []
@@ -160,6 +181,7 @@ def test_four_users_for_many_steps(Bt):
 def test_a_step_that_gives_up_says_so_and_the_next_one_is_whole(Dm, Di, R, Bt):
     """The first input of the chain is held back, so that every bounded wait behind it runs out: NaN and -1, nothing finite."""
     d, m, keep = _model(Dm, Di, R, 3, 15)
+    assert Q.quamba_debug_decode_stack_served(d, 3, Bt)
     want = _steps(d, m, 3, Bt, 1)
     ssm, conv = _states(d, 3, Bt, 5)
     ws = workspace(Q.quamba_model_workspace_bytes(m, Bt, 1))
