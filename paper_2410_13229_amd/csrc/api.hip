@@ -350,7 +350,7 @@ int run_mixer(const quamba_dims *d, const quamba_qweights *qw, const quamba_scal
     return QUAMBA_OK;
   }
   ReadAhead ahead;
-  if (defer_out && defer_out->cold) ahead = ReadAhead{qw->W_outH, (size_t)Dm * Di};
+  if (defer_out && defer_out->ahead) ahead = ReadAhead{qw->W_outH, defer_out->ahead};
   QUAMBA_TRY(launch_hadamard_quant(g16, M, Di, sc->inv_s_y, gH_q, t.gH_f32, st, ahead));
   QUAMBA_TRY(tap_copy(t.gH_q, gH_q, (size_t)M * Di, st));
   // out_proj with the folded weight, fp16 out; the multiplier carries s_y s_WoutH / n
@@ -362,7 +362,7 @@ int run_mixer(const quamba_dims *d, const quamba_qweights *qw, const quamba_scal
       const int splits = out_plan.k_splits();
       if (splits > 1 && splits <= 8) {
         e.defer_reduce = true;
-        *defer_out = OutPartial{true, defer_out->cold, splits, reinterpret_cast<const int32_t *>(base + p.gemm), sc->m_out};
+        *defer_out = OutPartial{true, defer_out->ahead, splits, reinterpret_cast<const int32_t *>(base + p.gemm), sc->m_out};
       }
     }
     QUAMBA_TRY(launch_gemm_i8(gH_q, Di, qw->W_outH, Di, M, Dm, Di, e, base + p.gemm, p.gemm_bytes, st, &out_plan));

@@ -120,7 +120,7 @@ int launch_requant_dyn(const int32_t *acc, int8_t *out, int M, int N, int e0, in
 int launch_dyn_export(const unsigned *slot, float *out, hipStream_t st);
 
 // memory that the launches after this one will read (weights of a stack too large for the last-level cache): extra workgroups
-// of a launch that leaves most CUs idle read it, so that it waits in the cache
+// of a short launch that leaves CUs or the memory idle read it, so that it waits in the cache
 struct ReadAhead {
   const void *ptr = nullptr;
   size_t bytes = 0;
@@ -214,7 +214,7 @@ size_t mixer_workspace_bytes(const quamba_dims *d, int Bt, int L);
 // the mixer's workspace: valid until the next mixer call on it) and the multiplier of the sums.
 struct OutPartial {
   bool want;
-  bool cold;  // set by the caller: the stack's weights exceed the last-level cache, read this block's out_proj weights ahead
+  size_t ahead;  // set by the caller: bytes of this block's out_proj weights that the Hadamard launch reads ahead
   int splits;
   const int32_t *partial;
   float m_out;

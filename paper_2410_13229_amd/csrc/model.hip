@@ -348,6 +348,23 @@ int check_model(const quamba_model *m) {
   return QUAMBA_OK;
 }
 
+// Weights of a stack that does not fit the 256 MB last-level cache arrive cold in every block of a generation step.  The norm's launch (a workgroup per
+// sequence, 3 us) reads part of in_proj's ahead, the Hadamard launch out_proj's.  Measured at d_model 768 to 5120 with 3 to 512 sequences,
+// against none (stacks of 250 to 470 MB):
+//   in_proj   half of it, at most 16 MB, up to 128 sequences: 1.01 to 1.05 times as fast (2.8B layers 3 / 16 / 64: 1.02 / 1.04 / 1.05).  More
+//             outlasts the norm (all 17 MB at d_model 2048, 3 sequences: 0.98), and beyond 128 sequences the norm has too little idle
+//             (160 to 512: 0.98 to 0.99)
+//   out_proj  all of it: up to 64 sequences where it has no more than 19 MB (1.00 to 1.02; 33 MB 0.98, 52 MB 0.98), with more sequences, and with
+//             them a longer scan and Hadamard launch, at any size (1.00 to 1.04, 52 MB with 256 sequences 1.02)
+struct DecodeAhead {
+  size_t in, out;
+};
+DecodeAhead decode_ahead(int n_layers, int M, int Dm, int Di, int R) {
+  if ((double)n_layers * Di * (3.0 * Dm + 2.0 * R + 2.0 * 16) <= 256e6) return DecodeAhead{0, 0};
+  const size_t out = (size_t)Dm * Di;
+  return DecodeAhead{M <= 128 ? std::min<size_t>(out, 16u << 20) : 0, M > 64 || out <= 20000000 ? out : 0};
+}
+
 // One pass of the whole model over tokens [Bt, L] (decode: L == 1 on carried states).
 int run_model(const quamba_model *m, const int32_t *tokens, int Bt, int L, bool decode, float *logits_out,
               int32_t *next, int32_t *log, float *ssm_states, __half *conv_states, char *base, const Carve &c,
@@ -386,11 +403,9 @@ int run_model(const quamba_model *m, const int32_t *tokens, int Bt, int L, bool 
   __half *res_other = reinterpret_cast<__half *>(base + c.res2);
   // generation with more sequences: where out_proj splits K over the grid, the next block's add + norm +
   // quantization adds up the partial sums (the last block's output is stored as usual for the final norm)
-  OutPartial prev{false, false, 1, nullptr, 0.f};
-  // Weights of a stack that does not fit the 256 MB last-level cache arrive cold in every block.  The norm (a workgroup per sequence, 3 us)
-  // reads 16 MB of in_proj's ahead, the Hadamard launch out_proj's: 16 blocks of the 2.8B layer, 4 / 16 / 64 sequences 610 / 679 / 886
-  // -> 586 / 651 / 847 us a step (more than 16 MB outlasts the norm: 20 MB 868, 26 MB 869 at 64).
-  const bool cold = decode && (double)m->n_layers * Di * (3.0 * Dm + 2.0 * m->dims.dt_rank + 2.0 * N) > 256e6;
+  OutPartial prev{false, 0, 1, nullptr, 0.f};
+  // generation with weights that arrive cold in every block: bytes of them read ahead
+  const DecodeAhead cold = decode ? decode_ahead(m->n_layers, M, Dm, Di, m->dims.dt_rank) : DecodeAhead{0, 0};
   for (int l = 0; !stacked && l < m->n_layers; ++l) {
     const quamba_layer &ly = m->layers[l];
     float *ssm = ssm_states + (size_t)l * Bt * Di * N;
@@ -404,7 +419,7 @@ int run_model(const quamba_model *m, const int32_t *tokens, int Bt, int L, bool 
       res_other = tmp;
     } else {
       ReadAhead ahead;
-      if (cold) ahead = ReadAhead{ly.q.W_in, std::min<size_t>((size_t)2 * Di * Dm, 16u << 20)};
+      if (cold.in) ahead = ReadAhead{ly.q.W_in, cold.in};
       if (prev.splits > 1)
         rc = launch_add_rmsnorm_quant_partial(prev.partial, prev.splits, prev.m_out, res,
                                               reinterpret_cast<const __half *>(ly.norm_w), m->eps, ly.s.inv_s_u, u_q, M,
@@ -413,7 +428,7 @@ int run_model(const quamba_model *m, const int32_t *tokens, int Bt, int L, bool 
         rc = launch_add_rmsnorm_quant(out, res, reinterpret_cast<const __half *>(ly.norm_w), m->eps, ly.s.inv_s_u,
                                       u_q, M, Dm, st, ahead);
       if (rc != QUAMBA_OK) return rc;
-      prev = OutPartial{decode && l + 1 < m->n_layers, cold, 1, nullptr, 0.f};
+      prev = OutPartial{decode && l + 1 < m->n_layers, cold.out, 1, nullptr, 0.f};
       rc = mixer_run_q(&m->dims, &ly.q, &ly.s, u_q, Bt, L, decode, out, ssm, cs, base + c.mixer, c.mixer_bytes, st,
                        &prev, (!decode && l + 1 < m->n_layers) ? &m->layers[l + 1].q : nullptr, !decode && l + 1 == m->n_layers);
     }
@@ -452,6 +467,12 @@ int check_run(const quamba_model *m, const void *tokens, int Bt, int L, const vo
 }  // namespace quamba
 
 using namespace quamba;
+
+extern "C" long long quamba_debug_decode_reads_ahead(int n_layers, int batch, int d_model, int d_inner, int dt_rank, int out_proj) {
+  if (n_layers < 1 || batch < 1 || d_model < 16 || d_inner < 16) return 0;
+  const DecodeAhead a = decode_ahead(n_layers, batch, d_model, d_inner, dt_rank);
+  return (long long)(out_proj ? a.out : a.in);
+}
 
 extern "C" {
 

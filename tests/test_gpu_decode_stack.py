@@ -206,7 +206,7 @@ def test_a_step_that_gives_up_says_so_and_the_next_one_is_whole(Dm, Di, R, Bt):
     del keep
 
 
-@pytest.mark.parametrize("Bt", [3, 20])
+@pytest.mark.parametrize("Bt", [3, 20, 70, 130])  # both, both, both with more than 64 sequences, out_proj alone
 def test_weights_read_ahead_change_nothing(Bt):
     """A stack whose weights exceed the last-level cache (the same block seven times: 280 MB): norm and Hadamard launches with workgroups that
     read ahead, against the blocks one by one through their own entry points."""

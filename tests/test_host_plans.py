@@ -48,3 +48,16 @@ def test_128_by_96_tiles_are_taken_where_that_was_measured_to_pay(M, N, K, taken
 ])
 def test_last_block_reads_ahead_only_where_that_was_measured_to_pay(batch, L, Dm, Di, ahead):
     assert Q.quamba_debug_last_block_reads_ahead(batch, L, Dm, Di) == ahead
+
+
+@pytest.mark.parametrize("n_layers,batch,Dm,Di,R,in_proj,out_proj", [
+    (64, 64, 2560, 5120, 160, 2560 * 5120, 2560 * 5120), (64, 128, 2560, 5120, 160, 2560 * 5120, 2560 * 5120),
+    (64, 129, 2560, 5120, 160, 0, 2560 * 5120), (64, 512, 2560, 5120, 160, 0, 2560 * 5120),  # too many sequences beside the norm
+    (14, 3, 2048, 4096, 128, 2048 * 4096, 2048 * 4096),                                       # half of in_proj, not all
+    (4, 64, 4096, 8192, 256, 16 << 20, 0), (4, 65, 4096, 8192, 256, 16 << 20, 4096 * 8192),   # 33 MB outlast a short Hadamard launch
+    (6, 3, 3072, 6144, 192, 16 << 20, 3072 * 6144), (3, 256, 5120, 10240, 320, 0, 5120 * 10240),
+    (6, 3, 2560, 5120, 160, 0, 0), (7, 3, 2560, 5120, 160, 2560 * 5120, 2560 * 5120),         # the stack stays in the cache, or not
+])
+def test_generation_reads_weights_ahead_where_that_was_measured_to_pay(n_layers, batch, Dm, Di, R, in_proj, out_proj):
+    got = [Q.quamba_debug_decode_reads_ahead(n_layers, batch, Dm, Di, R, k) for k in (0, 1)]
+    assert got == [in_proj, out_proj]
