@@ -634,6 +634,7 @@ int quamba_probe_rate(int probe, int waves_per_simd, int iters, double *instr_pe
  *                                      until this tag or a later one; returns their number, -1 = no such item
  *   quamba_debug_decode_stack_served(dims, n_layers, batch)  1 = generation with this batch runs all blocks in one
  *                                      launch on the current device (asks the device; 0 without one)
+ *   quamba_debug_percentile_workgroups(values)  workgroups that count bins for the percentile of so many values
  *   quamba_debug_decode_reads_ahead(n_layers, batch, d_model, d_inner, dt_rank, out_proj)  bytes of in_proj's (out_proj
  *                                      != 0: out_proj's) weights of a block that generation launch by launch reads ahead
  *   quamba_debug_last_block_reads_ahead(batch, L, d_model, d_inner)  1 = the scan of a stack's last block reads
@@ -650,6 +651,7 @@ int quamba_debug_gemm_kind(int M, int N, int K);
 int quamba_debug_xfmt_column_tiles(int M, int N, int K);
 int quamba_debug_decode_stack_words(int d_model, int d_inner, int dt_rank, int batch, int role, int item, int32_t *out, int cap);
 int quamba_debug_decode_stack_served(const quamba_dims *dims, int n_layers, int batch);
+int quamba_debug_percentile_workgroups(long long values);
 long long quamba_debug_decode_reads_ahead(int n_layers, int batch, int d_model, int d_inner, int dt_rank, int out_proj);
 int quamba_debug_last_block_reads_ahead(int batch, int L, int d_model, int d_inner);
 

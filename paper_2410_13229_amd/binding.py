@@ -31,7 +31,7 @@ __all__ = [
     "quamba_debug_set_fuse_dt", "quamba_debug_set_fuse_decode", "quamba_debug_set_scan_variant",
     "quamba_debug_set_decode_stack", "quamba_debug_gemm_kind", "quamba_debug_xfmt_column_tiles", "quamba_debug_last_block_reads_ahead",
     "quamba_debug_decode_stack_words", "quamba_debug_decode_stack_served",
-    "quamba_debug_decode_reads_ahead",
+    "quamba_debug_decode_reads_ahead", "quamba_debug_percentile_workgroups",
     "PROBE_FMA_F32", "PROBE_EXP_F32", "PROBE_SCAN_MIX", "PROBE_MFMA_I8", "PROBE_MFMA_I8_RANDOM",
     "PROBE_MUL_F32", "PROBE_FMA_EXP_INDEP", "PROBE_MIX_NOEXP", "PROBE_MIX_GROUPED",
     "quamba_probe_workspace_bytes", "quamba_probe_rate",
@@ -366,6 +366,8 @@ def lib():
     L.quamba_debug_decode_stack_served.restype = i
     L.quamba_debug_decode_reads_ahead.argtypes = [i, i, i, i, i, i]
     L.quamba_debug_decode_reads_ahead.restype = C.c_longlong
+    L.quamba_debug_percentile_workgroups.argtypes = [C.c_longlong]
+    L.quamba_debug_percentile_workgroups.restype = i
     L.quamba_probe_workspace_bytes.restype = sz
     L.quamba_probe_workspace_bytes.argtypes = [i]
     L.quamba_probe_rate.restype = C.c_int
@@ -734,6 +736,10 @@ def quamba_debug_xfmt_column_tiles(M, N, K) -> int:
 
 def quamba_debug_last_block_reads_ahead(batch, L, d_model, d_inner) -> bool:
     return bool(lib().quamba_debug_last_block_reads_ahead(int(batch), int(L), int(d_model), int(d_inner)))
+
+
+def quamba_debug_percentile_workgroups(values) -> int:
+    return int(lib().quamba_debug_percentile_workgroups(int(values)))
 
 
 def quamba_debug_decode_reads_ahead(n_layers, batch, d_model, d_inner, dt_rank, out_proj) -> int:

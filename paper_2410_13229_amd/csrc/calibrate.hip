@@ -3,6 +3,7 @@
 // for the scan input x, the Hadamard-space scale of the scan output and the folding of H_n
 // into W_out, followed by the per-tensor symmetric quantization of every weight (Eq. 2).
 // This runs once per layer.  4 x 256 tokens of the 2.8B layer: 54 GFLOP of fp32 input projection are the floor.
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstring>
@@ -543,10 +544,11 @@ __device__ unsigned select_prefix(const unsigned long long *hist, int passes, un
   return prefix;
 }
 
-// One workgroup per CU: in the first two passes all of them add to the same few bins, and additions to one word in memory come 14 ns
-// apart (1024 workgroups: 18 and 26 us for these passes of 4 x 256 tokens of the 2.8B layer, the calibration 886 us against 870; 128: 888;
-// copies of the bins in LDS change nothing).
-constexpr int HIST_WGS = 256;
+// Workgroups, one per 20480 values between one and three per CU: in the first two passes all of them add to the same few bins, and additions to one
+// word in memory come 14 ns apart, while many values need the loads of several workgroups per CU.  Calibration with 256 / 512 / 768 / 1024
+// of them: 1.6 M values (4 x 256 tokens of the 130M layer) 275 / 282 / 289 / 295 us, 5.2 M (4 x 256 of the 2.8B layer) 865 / 866 / 870 /
+// 876, 8.4 M 1054 / 1050 / 1053 / 1057, 12.6 M 1012 / 989 / 988 / 992, 21 M 2770 / 2721 / 2712 / 2711 (copies of the bins in LDS change nothing).
+int hist_workgroups(size_t n) { return (int)std::min<size_t>(std::max<size_t>(n / 20480, 256), 768); }
 
 __global__ __launch_bounds__(256) void select_hist_kernel(const float *__restrict__ x, size_t n, int pass,
                                                           unsigned long long rank, unsigned long long *hist) {
@@ -944,7 +946,7 @@ int calibrate(const quamba_dims *d, const quamba_fp_weights *w, const __half *ca
     if (rank < 1) rank = 1;
     if (rank > nx) rank = nx;
     for (int pass = 0; pass < 4; ++pass)
-      hipLaunchKernelGGL(select_hist_kernel, dim3(HIST_WGS), dim3(256), 0, st, x, nx, pass, (unsigned long long)rank, hist);
+      hipLaunchKernelGGL(select_hist_kernel, dim3(hist_workgroups(nx)), dim3(256), 0, st, x, nx, pass, (unsigned long long)rank, hist);
     hipLaunchKernelGGL(select_finish_kernel, dim3(1), dim3(256), 0, st, hist, (unsigned long long)rank, slots + S_COUNT);
     QUAMBA_LAUNCH_CHECK();
   }
@@ -1105,3 +1107,5 @@ int calibrate_xfmt(const quamba_dims *d, const quamba_fp_weights *w, const __hal
 }
 
 }  // namespace quamba
+
+extern "C" int quamba_debug_percentile_workgroups(long long values) { return values > 0 ? quamba::hist_workgroups((size_t)values) : 0; }

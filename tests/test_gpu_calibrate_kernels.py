@@ -143,6 +143,24 @@ def test_fp32_sums_run_over_k_in_order(Dm, Di, R, nb, L):
         assert np.array_equal(got[np.ix_(rows, cols)], _chain(a[rows], np.asarray(wt, np.float32)[cols])), name
 
 
+@pytest.mark.parametrize("M,workgroups", [(1, 256), (1027, 256), (1028, 257), (2048, 512), (3068, 767), (3100, 768)])
+def test_percentile_of_many_values(M, workgroups):
+    """The same at every size of the grid that counts: its least, one more, and its most."""
+    cfg, w, u = _case(16, 5120, 16, 1, M)
+    assert Q.quamba_debug_percentile_workgroups(M * 5120) == workgroups
+    ws = workspace(Q.quamba_calibrate_workspace_bytes(cfg, 1, M))
+    q = {k: empty(s, torch.int8) for k, s in (("W_in", (10240, 16)), ("conv_w", (5120, 4)), ("W_x", (48, 5120)), ("W_dt", (5120, 16)),
+                                              ("A", (5120, 16)), ("D", (5120,)), ("W_outH", (16, 5120)))}
+    q["conv_b"], q["dt_bias"] = empty((5120,), torch.float32), empty((5120,), torch.float32)
+    fw = {k: dev(v) for k, v in w.items()}
+    for percentile in (0.37, 99.999):
+        sc = Q.scales_to_dict(Q.quamba_calibrate(cfg, fw, dev(u), 1, M, percentile, q, ws))
+        x = np.abs(_left_in_workspace(ws, cfg, M)[2]).reshape(-1)
+        rank = max(int(math.ceil(percentile * x.size / 100.0)), 1) - 1
+        v = np.partition(x, rank)[rank]
+        assert v > 0 and np.float32(sc["s_x"]) == np.float32(np.float64(v) / 127.0)
+
+
 @pytest.mark.parametrize("kind", ["plain", "ties", "zero"])
 @pytest.mark.parametrize("percentile", [1e-7, 0.37, 50.0, 99.9, 99.999, 100.0])
 def test_percentile_picks_the_value_of_its_rank(kind, percentile):
