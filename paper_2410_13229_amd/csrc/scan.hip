@@ -472,11 +472,6 @@ __device__ __forceinline__ float dpp_f(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
 }
 
-// NK: k steps of 64 the dt_proj contraction may take (dt_rank <= 64 NK); 0: dt_q is read, not computed.
-// LAT: the form for one or two workgroups per CU, where a wave has its SIMD (almost) to itself and nothing but
-// its own instruction order hides latencies: the LDS reads of group g + 1 are in flight under group g, the 16
-// exponentials of a group are issued ahead of the two recurrence chains that consume them, and the gate of
-// group g - 1 (a serial chain with two transcendentals) is spread between them.
 // B and C of a lane's states in one LDS word
 template <int SPL>
 struct BCWord {
@@ -498,6 +493,12 @@ __device__ __forceinline__ float c_dot(const BCOf<SPL> &w, const float (&h)[SPL]
   else return w.y * h[0];
 }
 
+// NK: k steps of 64 the dt_proj contraction may take (dt_rank <= 64 NK); 0: dt_q is read, not computed.
+// LAT: the form for one or two workgroups per CU, where a wave has its SIMD (almost) to itself and nothing but
+// its own instruction order hides latencies: the LDS reads of group g + 1 are in flight under group g, the 16 (8)
+// exponentials of a group are issued ahead of the two recurrence chains (the one) that consume them, and the gate of
+// group g - 1 (a serial chain with two transcendentals) is spread between them.
+// SPL: states per lane.
 template <int NK, int XM, bool LAT, int SPL>
 __global__ __launch_bounds__(SW_THREADS, LAT ? 1 : 3) void scan_sweep_kernel(Dev p, float *__restrict__ ssm_state) {
   static_assert(SPL == 2 || (SPL == 1 && LAT), "one state per lane: the latency-ordered form only");
@@ -1088,17 +1089,18 @@ bool one_state_per_lane(int Bt, int Di) { return (long)Bt * (Di / 16) <= 192; }
 //            SIMD is busy, 40 ns per token and wave
 //   chunked  30 + L * (W / 256) * 52 ns: three launches and the carry, every exponential taken twice
 // so the sweep takes the short sequences and the batches, the chunked form a long single sequence.
-// With one state per lane the sweep takes 3.6 + L 47 ns; the chunked form at those widths 21 + L * (W / 256) * 65 ns (1536 wide, 1 x 256 to 900
-// and 2 x 200 to 500 tokens: the same time at 500 tokens of one sequence).
-double sweep_us(int Bt, int L, int Di) {
+// With one state per lane the sweep takes 3.6 + L 47 ns; the chunked form at those widths 21 + L * (W / 256) * 65 ns (fitted at 1536 wide, 1 x 256 to
+// 900 and 2 x 200 to 500 tokens; at 192 to 3072 wide, 1 to 16 sequences and 16 to 2048 tokens the form taken is the faster one or within 2 us of it).
+double sweep_us(int Bt, int L, int Di, bool one_state) {
   const int k = (int)std::ceil((double)Bt * (Di / SW_CH) / 256.0);
+  if (one_state) return 3.6 + L * 0.047;
   return 3.6 + L * (k <= 1 ? 0.0645 : (k == 2 ? 0.098 : 0.040 * k));
 }
 
 bool sweep_is_cheaper(int Bt, int L, int Di, bool one_state) {
   const double W = (double)Bt * (Di / SW_CH);
-  if (one_state) return 3.6 + L * 0.047 < 21.0 + (double)L * (W / 256.0) * 0.065;
-  return sweep_us(Bt, L, Di) < 30.0 + (double)L * (W / 256.0) * 0.052;
+  if (one_state) return sweep_us(Bt, L, Di, true) < 21.0 + (double)L * (W / 256.0) * 0.065;
+  return sweep_us(Bt, L, Di, false) < 30.0 + (double)L * (W / 256.0) * 0.052;
 }
 
 int sweep_warm_blocks(int Bt) { return std::max(1, 96 / Bt); }  // per sequence: about 96 workgroups in all
@@ -1117,8 +1119,8 @@ bool read_ahead_pays(int Bt, int L, int Di, size_t bytes, bool sweep, bool one_s
   const long wgs = (long)Bt * (Di / (sweep && one_state ? SW_CH / 2 : SW_CH)), rest = wgs % 256, tokens = (long)Bt * L;
   const bool fits = rest + (long)sweep_warm_blocks(Bt) * Bt <= 256;
   if (bytes < 12000000) return false;
-  if (sweep && wgs <= 768) return fits && rest > 0 && tokens <= 2048 && (double)bytes / 3.5e6 <= sweep_us(Bt, L, Di);
-  return bytes < 20000000 && (double)tokens * (double)bytes <= 2.2e10 && (!sweep || (fits && (double)bytes / 2e6 <= sweep_us(Bt, L, Di)));
+  if (sweep && wgs <= 768) return fits && rest > 0 && tokens <= 2048 && (double)bytes / 3.5e6 <= sweep_us(Bt, L, Di, one_state);
+  return bytes < 20000000 && (double)tokens * (double)bytes <= 2.2e10 && (!sweep || (fits && (double)bytes / 2e6 <= sweep_us(Bt, L, Di, one_state)));
 }
 
 template <int NK, int XM, bool LAT, int SPL = 2>

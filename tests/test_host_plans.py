@@ -41,6 +41,7 @@ def test_128_by_96_tiles_are_taken_where_that_was_measured_to_pay(M, N, K, taken
     (1, 512, 2560, 5120, True), (2, 256, 2560, 5120, True), (4, 512, 2560, 5120, True), (1, 256, 6144, 4096, True),
     (3, 512, 2560, 5120, False), (2, 512, 6144, 4096, False), (1, 256, 4096, 8192, False),  # no idle CUs in the last round
     (4, 1024, 768, 1536, False), (2, 512, 2048, 4096, False),                               # weights of 1 and 8 MB
+    (1, 16, 6144, 2560, False), (1, 20, 6144, 2560, True),                                  # one state per lane: 47 ns a token
     (1, 4, 2560, 5120, True), (1, 1, 2560, 5120, False), (1, 16, 6144, 4096, False),        # scans shorter than the read
     (1, 1456, 2560, 5120, True), (1, 4096, 2560, 5120, False), (1, 1024, 6144, 4096, False),  # chunked scans
     (16, 32, 2560, 5120, True), (64, 16, 2560, 5120, True), (64, 1, 2560, 5120, False), (6, 96, 2560, 5120, False),
