@@ -133,7 +133,7 @@ struct DynX {
 };
 
 // Steps shared by prefill (L >= 1, fresh conv history) and decode (L == 1, carried state).
-// `norm` (generation with at most 4 sequences only): the block input is not given but formed inside
+// `norm` (generation with as many sequences as the few-row kernels take, two unless tuned): the block input is not given but formed inside
 // the first kernel from the previous block's output and the residual stream.
 int run_mixer(const quamba_dims *d, const quamba_qweights *qw, const quamba_scales *sc, const __half *u,
               const int8_t *u_q_in, int Bt, int L, bool decode, __half *out, float *ssm_state,

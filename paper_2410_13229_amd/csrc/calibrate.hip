@@ -667,8 +667,6 @@ __global__ void clip_init_kernel(double *state) {
 
 constexpr size_t CLIP_WS_BYTES = 256 + CLIP_BLOCKS * sizeof(ClipPart);
 
-// Eq. 2 for several tensors in one launch: q = clamp(rne(x * inv_s)), four values per thread and step; every tensor is a
-// multiple of four long.  A segment marked `copy` is copied as fp32 instead.
 // The scale of a tensor with this largest magnitude (1 if it is zero) and its reciprocal, each rounded once from 64 bits.
 __host__ __device__ inline float scale_of(float m) { return m > 0.f ? (float)((double)m / 127.0) : 1.0f; }
 __host__ __device__ inline float inverse_scale(float m) { return (float)(1.0 / (double)scale_of(m)); }
@@ -684,6 +682,8 @@ struct QuantSegs {
 };
 constexpr int Q_PER_WG = 8192;
 
+// Eq. 2 for several tensors in one launch: q = clamp(rne(x * inv_s)), four values per thread and step; every tensor is a
+// multiple of four long.  A segment marked `copy` is copied as fp32 instead.
 __global__ __launch_bounds__(256) void quantize_f32_kernel(QuantSegs s) {
   int i = 0;
   while (blockIdx.x >= s.end[i]) ++i;

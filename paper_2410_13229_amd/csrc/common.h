@@ -229,7 +229,7 @@ int mixer_run_q(const quamba_dims *d, const quamba_qweights *qw, const quamba_sc
 // layer, 512 tokens: that projection 25.4 -> 18 us)
 int check_model_dims(const quamba_dims *d);
 
-// generation with at most 4 sequences: the block's own residual add + RMSNorm + quantization runs
+// generation with as many sequences as the few-row kernels take: the block's own residual add + RMSNorm + quantization runs
 // inside the mixer's first kernel.  res_out must not alias res_in.
 struct NormIn {
   const __half *out_prev, *res_in;

@@ -107,11 +107,6 @@ __device__ __forceinline__ void store_tiles(const v16i (&acc)[TN][TM], int m_bas
   }
 }
 
-// Same result, but the wave first lays its (TM*32) x (TN*32) block of finished int8 / fp16
-// values out row-major in a private LDS region and then writes it with 16 bytes per lane, so a
-// wave-level store covers whole runs of a row instead of 8-byte pieces of 32 different rows.
-// Needs N, ldo and the output base aligned to 16 bytes; `scratch` is this wave's region of
-// TM*32 * (TN*32 * sizeof(element) + 16) bytes, free of other use (callers barrier before).
 // The conv step's operands for the groups of four channels that one wave takes of a block of TM x TN tiles: of the block's groups in row-major
 // order lane + 64 (part * IT + it), part being the wave's among the PARTS that share the block.  Consecutive lanes take consecutive
 // groups of one row, so the 24-byte windows they touch are adjacent.
@@ -119,6 +114,7 @@ template <int TM, int TN, int PARTS>
 struct ConvBlock {
   static constexpr int GPR = TN * 8;                    // groups per block row (int8 output)
   static constexpr int IT = TM * 32 * GPR / 64 / PARTS;  // groups per lane
+  static_assert(IT * 64 * PARTS == TM * 32 * GPR, "the parts share the block's groups evenly");
   ConvWindow4 win[IT];
   v4i wv[IT], bv[IT];
 
@@ -169,6 +165,11 @@ struct ConvBlock {
   }
 };
 
+// Same result, but the wave first lays its (TM*32) x (TN*32) block of finished int8 / fp16
+// values out row-major in a private LDS region and then writes it with 16 bytes per lane, so a
+// wave-level store covers whole runs of a row instead of 8-byte pieces of 32 different rows.
+// Needs N, ldo and the output base aligned to 16 bytes; `scratch` is this wave's region of
+// TM*32 * (TN*32 * sizeof(element) + 16) bytes, free of other use (callers barrier before).
 template <int TM, int TN>
 __device__ __forceinline__ void store_tiles_rows(const v16i (&acc)[TN][TM], int m_base, int n_base, int lane,
                                                  int M, int N, const GemmEpilogue &epi, int8_t *scratch) {
@@ -607,7 +608,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC) void gemm_i8_dma_kernel(c
     // hold up the ring's first slices: 40.7 against 39.9 us at 64)
     __syncthreads();  // operand tiles are dead
     ConvBlock<TM, TN, CONV ? KG : 1> conv;
-    if constexpr (CONV) conv.load(epi, kg, lane, m0 + wm * WM, n0 + wn * WN, M, N);
+    if constexpr (CONV) conv.load(epi, kg, lane, m0 + wm * WM, n0 + wn * WN, M, N);  // (without a branch: behind one they come late, +0.5 us)
     if (kg >= 1) {
       v4i *part = reinterpret_cast<v4i *>(ring + ((kg - 1) * TILES + wtile) * PART);
 #pragma unroll

@@ -398,7 +398,7 @@ int run_model(const quamba_model *m, const int32_t *tokens, int Bt, int L, bool 
                        Dm, m->vocab, res, out);
     QUAMBA_LAUNCH_CHECK();
   }
-  // generation with at most 4 sequences: the add + norm + quantization runs inside each block's first
+  // generation with as many sequences as the few-row kernels take (two unless tuned): the add + norm + quantization runs inside each block's first
   // kernel, which reads one residual buffer and writes the other
   __half *res_other = reinterpret_cast<__half *>(base + c.res2);
   // generation with more sequences: where out_proj splits K over the grid, the next block's add + norm +
