@@ -542,13 +542,16 @@ int quamba_model_prefill(const quamba_model *model, const int32_t *tokens, int B
 
 /* One generation step on the carried states (in/out): tokens int32 [Bt].
  *
- * With one or two sequences and at least two blocks (d_inner 1536, 2048, 2560, 3072, 4096 or 5120, d_model up to 2560 on
- * 256 CUs) all blocks run in one launch, whose workgroups hand values to one another through memory.  Every wait in it is
+ * With one or two sequences and at least two blocks (d_inner 1536, 2048, 2560, 3072, 4096 (one sequence) or 5120, d_model up
+ * to 2560 on 256 CUs) all blocks run in one launch, whose workgroups hand values to one another through memory.  Every wait in it is
  * bounded by a number of polls (35 ms of polling at least; no wait of a step that runs takes 1 ms).  Should one run out all the
  * same, the step says so: its logits are NaN, its next_token is -1 for every sequence, and the states are left undefined; the
  * call itself has returned QUAMBA_OK by then, as with any launch.  The step may run beside others on other streams, whose states
- * and workspaces are their own; while it has the GPU, other streams' kernels mostly wait (it takes (d_model + 9) / 10,
- * d_inner / 20 or d_inner / 48 + dt_rank / 4 + 8 of the CUs, whichever is most). */
+ * and workspaces are their own; while it has its CUs ((d_model + 9) / 10, d_inner / 20 or
+ * d_inner / 48 + dt_rank / 4 + 8 of them, whichever is most), other streams' kernels get the rest: with d_inner from 4096 on
+ * several streams that run such steps at the same time are slower together than launch by launch (two of 2560 x 5120 by 9 %
+ * with one sequence each, by 32 % with two; one alone is 36 % and 17 % faster), and a program that works that way chooses the
+ * launches with quamba_debug_set_decode_stack(1); sequences in one call are faster than either. */
 int quamba_model_decode(const quamba_model *model, const int32_t *tokens, int Bt, float *logits,
                         int32_t *next_token, float *ssm_states, quamba_half *conv_states,
                         void *ws, size_t ws_bytes, void *stream);

@@ -5,11 +5,17 @@
 // spends most of its time on launch boundaries and on the first reads of cold weights behind them.  Here one workgroup per CU
 // stays for all blocks; eight of its waves have role A (40 columns of in_proj), five role D (10 columns of out_proj), three B or C,
 // and each role walks the blocks at its own pace.  A wave asks for its weights of the next block as soon as it is done with the last
-// (8 x 15 and 5 x 10 rows of 1 KB, all in registers) and then waits for its input, so the 40 MB of a block stream in
+// (8 x 15 and 5 x 10 rows of 1 KB, held in registers; with two sequences 18 to 26 registers a lane go to scratch) and then waits for its
+// input, so the 40 MB of a block stream in
 // under the other roles, and a hand-over costs one trip through the memory side (1.2 to 2 us among 256 workgroups) instead of
-// a launch boundary plus the first cold read.  64 blocks of the 2.8B layer: one sequence 1637 -> 1049 us a step, two 1936 -> 1610.  Bound by the
-// chain: of 16.5 us a block about 7 are hand-overs, 4 the Hadamard transform with its products, 3 in_proj (its weights
-// arrive 9 us early).
+// a launch boundary plus the first cold read.  64 blocks of the 2.8B layer: one sequence 1643 -> 1051 us a step, two 1939 -> 1605.  Bound by the
+// chain: of 15.4 us a block (one sequence) the four hand-overs take 1.2 to 2.4 each, norm + in_proj + conv 2.0, x_proj 1.0, the scan step 0.6,
+// Hadamard + out_proj 3.6 (with two sequences one transform after the other), the spread of the workgroups the rest; the weights are there 9 us early.
+//
+// The launch takes the CUs for the whole step (all 256 at 2560 x 5120, 77 at 768 x 1536; 16 waves of 128 registers fill one), so
+// several users on streams of their own share it only where it leaves CUs: 768 x 1536, one sequence each, one / two / four users 422 / 712 / 1415 us
+// launch by launch, 268 / 277 / 570 this way; 2560 x 5120, 64 blocks 1643 / 2083 / 3915 and 1054 / 2257 / 4464, two sequences each 1939 / 2434 /
+// 3970 and 1614 / 3205 / 6251.
 //
 // Hand-over: every 4 bytes of payload (four codes, or two halves) travel in one 8-byte word with a tag, the number of the block
 // plus one, written and read by relaxed 64-bit atomics at device scope.  A reader that sees its tag has the payload, so no
@@ -23,7 +29,7 @@
 // do so within a bounded time they are all resident, and each keeps its own items (the walk above).  If not (another
 // kernel holds part of the GPU), the ones that run take the items from a counter, in an order in which an item only waits for
 // items with lower numbers, which somebody already holds: any number of workgroups gets through (all resident, that form
-// takes 1195 us).  Every wait is bounded (WAIT_TRIES polls, 35 ms and more where no wait of a step that runs takes one); a role's waves that have given up
+// takes 1200 us).  Every wait is bounded (WAIT_TRIES polls, 35 ms and more where no wait of a step that runs takes one); a role's waves that have given up
 // hand nothing on any more, so everything behind them gives up as well, down to the outputs, which are NaN.
 //
 // Arithmetic, operand order and rounding are those of the separate kernels (decode_in_kernel, gemv_i8_kernel, scan_step_kernel,
@@ -860,8 +866,11 @@ int run_stack(const StackArgs &args, const Begin &begin, hipStream_t st) {
   return QUAMBA_OK;
 }
 
-// The widths that are built: d_inner = K << LOGM
-#define QUAMBA_STACK_WIDTHS(CASE) CASE(12, 7) CASE(1, 11) CASE(20, 7) CASE(12, 8) CASE(1, 12) CASE(20, 8)
+// What is built: d_inner = K << LOGM, sequences.  Two sequences of 4096 gain 3 % alone on the GPU (24 blocks 600 -> 582 us; the other widths 11 to
+// 20 %) and lose 27 to 46 % where two to four users run a step each at the same time (721 -> 992, 1045 -> 1921): launch by launch.
+#define QUAMBA_STACK_WIDTHS(CASE)                                                                                    \
+  CASE(12, 7, 1) CASE(12, 7, 2) CASE(1, 11, 1) CASE(1, 11, 2) CASE(20, 7, 1) CASE(20, 7, 2) CASE(12, 8, 1) CASE(12, 8, 2) \
+  CASE(1, 12, 1) CASE(20, 8, 1) CASE(20, 8, 2)
 
 // Is a step of this shape served in one launch on the current device?
 bool stack_served(int n_layers, int Bt, int Dm, int Di, int R, size_t ws_bytes) {
@@ -869,8 +878,8 @@ bool stack_served(int n_layers, int Bt, int Dm, int Di, int R, size_t ws_bytes) 
   if (g_decode_stack_hook.load(std::memory_order_relaxed) == 1 || Bt < 1 || Bt > 2 || n_layers < 2 || Dm > PF * 1024 || R > 256) return false;
   if (stack_carve(n_layers, Bt, Dm, Di, R).total > ws_bytes || (long long)n_layers * 4096 > 0x7fffffffLL) return false;
   const int groups = stack_items(Dm, Di, R).groups();
-#define QUAMBA_CASE(K, LM) \
-  if (Di == K << LM) return Bt == 1 ? fits<K, LM, 1>(groups) : fits<K, LM, 2>(groups);
+#define QUAMBA_CASE(K, LM, MB) \
+  if (Di == K << LM && Bt == MB) return fits<K, LM, MB>(groups);
   QUAMBA_STACK_WIDTHS(QUAMBA_CASE)
 #undef QUAMBA_CASE
   return false;
@@ -916,8 +925,8 @@ int launch_decode_stack(const quamba_model *m, const int32_t *tokens, int Bt, fl
     }
     return QUAMBA_OK;
   };
-#define QUAMBA_CASE(K, LM) \
-  if (Di == K << LM) return Bt == 1 ? run_stack<K, LM, 1>(a, begin, st) : run_stack<K, LM, 2>(a, begin, st);
+#define QUAMBA_CASE(K, LM, MB) \
+  if (Di == K << LM && Bt == MB) return run_stack<K, LM, MB>(a, begin, st);
   QUAMBA_STACK_WIDTHS(QUAMBA_CASE)
 #undef QUAMBA_CASE
   return fail(QUAMBA_EUNSUPPORTED, "decode: d_inner=%d is not served in one launch", Di);

@@ -95,6 +95,7 @@ def test_one_launch_gives_the_bits_of_separate_launches(Dm, Di, R, n_layers, Bt)
     (3088, 1536, 16, 2, 1),   # more than role A's registers hold of a weight row
     (768, 1536, 272, 2, 1),   # dt_rank
     (96, 192, 16, 2, 1), (1024, 8192, 64, 2, 1),  # widths that are not built
+    (2048, 4096, 128, 2, 2),  # two sequences of this width
     (768, 1536, 48, 1, 1),    # one block
     (768, 1536, 48, 2, 3),    # three sequences
 ])
