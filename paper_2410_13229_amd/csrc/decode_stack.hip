@@ -13,9 +13,9 @@
 // Hadamard + out_proj 3.6 (with two sequences one transform after the other), the spread of the workgroups the rest; the weights are there 9 us early.
 //
 // The launch takes the CUs for the whole step (all 256 at 2560 x 5120, 77 at 768 x 1536; 16 waves of 128 registers fill one), so
-// several users on streams of their own share it only where it leaves CUs: 768 x 1536, one sequence each, one / two / four users 422 / 712 / 1415 us
-// launch by launch, 268 / 277 / 570 this way; 2560 x 5120, 64 blocks 1643 / 2083 / 3915 and 1054 / 2257 / 4464, two sequences each 1939 / 2434 /
-// 3970 and 1614 / 3205 / 6251.
+// several users on streams of their own share it only where it leaves CUs: 768 x 1536, one sequence each, one / two / four users 425 / 680 / 1323 us
+// launch by launch, 268 / 278 / 564 this way; 2560 x 5120, 64 blocks 1637 / 2073 / 3919 and 1050 / 2270 / 4499, two sequences each 1938 / 2424 /
+// 3779 and 1605 / 3190 / 6195.
 //
 // Hand-over: every 4 bytes of payload (four codes, or two halves) travel in one 8-byte word with a tag, the number of the block
 // plus one, written and read by relaxed 64-bit atomics at device scope.  A reader that sees its tag has the payload, so no
