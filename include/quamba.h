@@ -558,7 +558,8 @@ int quamba_model_decode(const quamba_model *model, const int32_t *tokens, int Bt
 
 /* Greedy generation of n_new tokens per sequence from first_tokens [Bt] (device; typically the
  * next_token of the prefill): step i feeds the token chosen by step i - 1.  tokens_out int32
- * [n_new, Bt] receives the chosen tokens (-1 from a step on whose waits ran out, see quamba_model_decode).  The current token, the step counter and the log stay
+ * [n_new, Bt] receives the chosen tokens (-1 from a step on whose waits ran out, see
+ * quamba_model_decode).  The current token, the step counter and the log stay
  * on the device, so a step is a fixed sequence of launches: with use_graph != 0 the first step
  * runs eagerly, the second is captured from `stream` (which must not be the default stream)
  * into a HIP graph, and the graph is replayed for the rest; the call then returns after the last
@@ -604,7 +605,8 @@ int quamba_probe_rate(int probe, int waves_per_simd, int iters, double *instr_pe
  * one atomic word that a call reads once at its start, so a call is consistent in itself; a
  * hook changed while calls are in flight applies to whichever calls start after it.  Results
  * do not depend on them beyond what the tests of the alternative forms state (bit-identical,
- * except where a row's sum of squares is accumulated in another order).
+ * except where a row's sum of squares is accumulated in another order), but for one value that
+ * makes waits run out on purpose (3 of quamba_debug_set_decode_stack).
  *   quamba_debug_set_gemm_variant(v)   v >= 0 forces GEMM kernel configuration v (0..14) where the
  *                                      shape allows it, and switches the launcher's row split off;
  *                                      -1 = chosen per shape (default)
